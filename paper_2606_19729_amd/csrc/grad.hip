@@ -389,13 +389,40 @@ __global__ __launch_bounds__(256) void grad_kernel(GradParams p) {
 }
 
 // Fixed-order sums of the per-wave partials: parameters, objective, actions.
-__global__ __launch_bounds__(256) void grad_reduce_kernel(GradReduceParams p) {
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p.grad_params && q < p.n_params) {
-        float s = 0.0f;
-        for (int w = 0; w < p.n_waves; ++w) s += p.wpart[(size_t)w * p.n_params + q];
-        p.grad_params[q] = s;
+// The partials are read once and nothing else is done, so the kernel is bound
+// by the loads in flight: a block takes 64 consecutive parameters (one 256-byte
+// segment of each row) with 16 waves, wave w summing rows w, w + 16, ... in
+// four accumulators, and wave 0 adds the 16 wave sums in wave order.  (One
+// thread per parameter walking every row took 286 us for 1,024 rows of 5,316
+// parameters: the distillation gradient of 65,536 x 20 steps 1,154 -> 855 us,
+// the contrastive one of B = 1,000, 256 rows of 145,409, 10.95 -> 10.84 ms.)
+constexpr int kRedCols = 64, kRedWaves = 16;
+__global__ __launch_bounds__(kRedCols * kRedWaves) void grad_reduce_kernel(GradReduceParams p, int param_blocks) {
+    __shared__ double part[kRedWaves][kRedCols];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if ((int)blockIdx.x < param_blocks) {
+        const int q = blockIdx.x * kRedCols + lane;
+        const bool ok = q < p.n_params;
+        const float* col = p.wpart + (ok ? q : 0);
+        float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        int w = wave;
+        for (; w + 3 * kRedWaves < p.n_waves; w += 4 * kRedWaves)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s[e] += col[(size_t)(w + e * kRedWaves) * p.n_params];
+        for (; w < p.n_waves; w += kRedWaves) s[0] += col[(size_t)w * p.n_params];
+        float(*fp)[kRedCols] = reinterpret_cast<float(*)[kRedCols]>(part);
+        fp[wave][lane] = (s[0] + s[1]) + (s[2] + s[3]);
+        __syncthreads();
+        if (wave == 0 && ok) {
+            float t = 0.0f;
+#pragma unroll
+            for (int k = 0; k < kRedWaves; ++k) t += fp[k][lane];
+            p.grad_params[q] = t;
+        }
+        return;
     }
+    // the blocks after the parameters': action gradients, one value per thread
+    const int q = ((int)blockIdx.x - param_blocks) * (kRedCols * kRedWaves) + (int)threadIdx.x;
     if (p.grad_actions && q < p.n_action_values) {
         // q = (sequence k, step t, component j); tiles of sequence k are consecutive
         const int per_step = p.H * p.d_a;
@@ -405,10 +432,19 @@ __global__ __launch_bounds__(256) void grad_reduce_kernel(GradReduceParams p) {
             s += p.apart[(size_t)(k * p.tiles_per_seq + tl) * per_step + rem];
         p.grad_actions[q] = s;
     }
-    if (p.loss && q == 0) {
+    if (p.loss && (int)blockIdx.x == param_blocks) {
         double s = 0.0;
-        for (int w = 0; w < p.n_waves; ++w) s += (double)p.lpart[w];
-        p.loss[0] = (float)(s * p.scale);
+        for (int w = threadIdx.x; w < p.n_waves; w += kRedCols * kRedWaves) s += (double)p.lpart[w];
+        part[wave][lane] = s;
+        __syncthreads();
+        if (wave == 0) {
+            s = 0.0;
+#pragma unroll
+            for (int k = 0; k < kRedWaves; ++k) s += part[k][lane];
+#pragma unroll
+            for (int m = 1; m < 64; m <<= 1) s += __shfl_xor(s, m);
+            if (lane == 0) p.loss[0] = (float)(s * p.scale);
+        }
     }
 }
 
@@ -682,9 +718,12 @@ int nce_grad_blocks_per_cu(int shape, size_t lds) {
 }
 
 hipError_t launch_grad_reduce(const GradReduceParams& p, hipStream_t s) {
-    int n = p.n_params > p.n_action_values ? p.n_params : p.n_action_values;
-    if (n < 1) n = 1;
-    hipLaunchKernelGGL(grad_reduce_kernel, (n + 255) / 256, 256, 0, s, p);
+    constexpr int threads = kRedCols * kRedWaves;
+    const int param_blocks = p.grad_params ? (p.n_params + kRedCols - 1) / kRedCols : 0;
+    const int acts = p.grad_actions ? (p.n_action_values + threads - 1) / threads : 0;
+    const int more = acts > 0 ? acts : (p.loss ? 1 : 0);
+    if (param_blocks + more == 0) return hipSuccess;
+    hipLaunchKernelGGL(grad_reduce_kernel, param_blocks + more, threads, 0, s, p, param_blocks);
     return hipGetLastError();
 }
 
