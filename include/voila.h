@@ -568,7 +568,7 @@ voila_status_t voila_batch_capture(voila_batch_t batch, int32_t what, const void
 voila_status_t voila_batch_replay(voila_batch_t batch, void* stream);
 
 /* ---------------------------------------------------------------------------
- * Gradients through rollouts (adjoint with step checkpointing).  Rollout b:
+ * Gradients through rollouts (adjoint).  Rollout b:
  * s_0 = S0_b, s_{t+1} = s_t + f_T([s_t, a_{b,t}, w_{b,t}]).  Objectives:
  *   VOILA_OBJ_DISTILL  L = 1/(B H) sum_b sum_{t=1..H} ||s_{b,t} - T_{b,t}||^2:
  *                      the distillation loss of Eq. 3 applied along
@@ -578,8 +578,10 @@ voila_status_t voila_batch_replay(voila_batch_t batch, void* stream);
  * Outputs: the objective, its gradient with respect to the transition
  * network's parameters (W1, b1, W2, b2, W3, b3 concatenated, each as
  * nn.Linear stores it) and, for continuous actions, with respect to the
- * action sequences.  The forward pass stores a checkpoint every `checkpoint`
- * steps; the reverse sweep recomputes each segment from its checkpoint.
+ * action sequences.  The forward pass keeps every step's state in the
+ * workspace (d_s floats per rollout and step) and the reverse sweep recomputes
+ * each step's activations from it; `checkpoint` is checked and does not change
+ * the result.
  * Binary32 models of networks with two hidden layers of width 64 only
  * (otherwise VOILA_ERR_UNSUPPORTED).  Results are deterministic (fixed-order
  * reductions).
@@ -589,7 +591,7 @@ voila_status_t voila_batch_replay(voila_batch_t batch, void* stream);
 
 typedef struct {
     int32_t B, H;               /* rollouts (>= 1), horizon (0..64)                            */
-    int32_t checkpoint;         /* checkpoint interval in steps (>= 1)                          */
+    int32_t checkpoint;         /* >= 1; every step is kept whatever the interval               */
     const float* d_s0;          /* [B][d_s]                                                     */
     const void* d_actions;      /* discrete: int32 [B][H]; continuous: float [B/particles][H][d_a] */
     int32_t particles;          /* rollouts per continuous sequence (multiple of 32 when the

@@ -320,7 +320,7 @@ struct voila_model_s {
     int plan_bpc = 1, prop_bpc = 1, obs_bpc = 1, obs_roll_bpc = 1, pw_bpc = 1, nce_bpc = 1;
     bool has_grad = false;
     NetBlob grad_fwd{}, grad_bwd{};
-    int grad_bpc = 1, n_params = 0;
+    int n_params = 0;
     bool has_nce_grad = false;       // parameter derivative of the contrastive objective compiled
     NetBlob lik_bwd{};               // transposed likelihood pack
     const float* lik_w3 = nullptr;   // [width] output-layer weights of the likelihood network
@@ -338,8 +338,8 @@ namespace {
 constexpr const char* kLikSplitOnlyUpdate =
     "a likelihood network of another shape than the samplers' is used by the belief update only";
 constexpr int kGradWaves = 4;
-size_t grad_lds_bytes(const voila_model_s* m) {
-    return (size_t)m->grad_fwd.bytes + m->grad_bwd.bytes + (size_t)kGradWaves * 32 * 129 * sizeof(float);
+size_t grad_lds_bytes(const voila_model_s* m, int waves) {
+    return (size_t)m->grad_fwd.bytes + m->grad_bwd.bytes + grad_scratch_bytes(waves);
 }
 size_t nce_grad_lds_bytes(const voila_model_s* m) {
     return (size_t)m->lik_nce.bytes + m->lik_bwd.bytes + (size_t)kGradWaves * 32 * 129 * sizeof(float);
@@ -645,7 +645,6 @@ voila_status_t voila_model_create(const voila_model_desc_t* desc, int32_t device
         m->nce_wide_bpc = nce_wide_bwd_blocks_per_cu(dt);
         m->nce_wgrad_bpc = nce_wide_wgrad_blocks_per_cu(dt);
     }
-    if (m->has_grad) m->grad_bpc = grad_blocks_per_cu(shape, grad_lds_bytes(m));
     *out = m;
     return VOILA_OK;
 }
@@ -2246,32 +2245,30 @@ voila_status_t voila_batch_replay(voila_batch_t b, void* stream) {
 // ---------------------------------------------------------------------------
 namespace {
 struct GradWs {
-    float* ckpt;
-    float* segst;
+    float* states;
     float* wpart;
     float* lpart;
     float* apart;
     size_t bytes;
-    int blocks;
+    int blocks, waves;
 };
 GradWs carve_grad(const voila_model_s* m, const voila_grad_opts_t* o, char* base) {
     GradWs w{};
     const int n_tiles = (o->B + 31) / 32;
-    const int C = o->checkpoint, NC = (o->H + C - 1) / C;
-    const int want = (n_tiles + kGradWaves - 1) / kGradWaves;
-    const int cap = m->cus * m->grad_bpc;
-    w.blocks = std::max(1, std::min(want, cap));
-    const int n_waves = w.blocks * kGradWaves;
+    // one block per CU (the networks and eight waves' transposes take its LDS);
+    // few tiles spread over the CUs first, one wave each, since two waves on a
+    // SIMD share its matrix core
+    w.waves = std::max(1, std::min(kGradMaxWaves, (n_tiles + m->cus - 1) / m->cus));
+    w.blocks = std::max(1, std::min((n_tiles + w.waves - 1) / w.waves, m->cus));
     size_t off = 0;
     auto take = [&](size_t bytes) {
         char* p = base ? base + off : nullptr;
         off = align_up(off + bytes, 256);
         return reinterpret_cast<float*>(p);
     };
-    w.ckpt = take((size_t)o->B * std::max(NC, 1) * m->d_s * 4);
-    w.segst = take((size_t)o->B * (C + 1) * m->d_s * 4);
-    w.wpart = take((size_t)n_waves * m->n_params * 4);
-    w.lpart = take((size_t)n_waves * 4);
+    w.states = take((size_t)n_tiles * std::max(o->H, 1) * state_slots(m->d_s) * 64 * 4);
+    w.wpart = take((size_t)w.blocks * m->n_params * 4);
+    w.lpart = take((size_t)w.blocks * 4);
     w.apart = take((size_t)n_tiles * std::max(o->H, 1) * std::max(m->d_a, 1) * 4);
     w.bytes = off;
     return w;
@@ -2321,15 +2318,13 @@ voila_status_t voila_rollout_grad(voila_model_t m, const voila_grad_opts_t* o, v
     p.actions = o->d_actions;
     p.noise = o->d_noise;
     p.targets = o->d_targets;
-    p.ckpt = w.ckpt;
-    p.segst = w.segst;
+    p.states = w.states;
     p.wpart = w.wpart;
     p.lpart = w.lpart;
+    p.waves = w.waves;
     p.apart = o->d_grad_actions ? w.apart : nullptr;
     p.B = o->B;
     p.H = o->H;
-    p.C = o->checkpoint;
-    p.NC = (o->H + o->checkpoint - 1) / o->checkpoint;
     p.particles = m->n_actions > 0 ? 1 : o->particles;
     p.objective = o->objective;
     p.want_params = o->d_grad_params ? 1 : 0;
@@ -2344,7 +2339,7 @@ voila_status_t voila_rollout_grad(voila_model_t m, const voila_grad_opts_t* o, v
         d *= o->gamma;
     }
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    VOILA_CHECK_HIP(launch_grad(m->shape, p, w.blocks, grad_lds_bytes(m), s));
+    VOILA_CHECK_HIP(launch_grad(m->shape, p, w.blocks, grad_lds_bytes(m, w.waves), s));
     GradReduceParams r{};
     r.wpart = w.wpart;
     r.lpart = w.lpart;
@@ -2353,7 +2348,7 @@ voila_status_t voila_rollout_grad(voila_model_t m, const voila_grad_opts_t* o, v
     r.grad_actions = o->d_grad_actions;
     r.loss = o->d_loss_out;
     r.n_params = o->d_grad_params ? m->n_params : 0;
-    r.n_waves = w.blocks * kGradWaves;
+    r.n_waves = w.blocks;
     r.H = o->H;
     r.d_a = m->d_a;
     r.tiles_per_seq = m->n_actions > 0 ? 1 : o->particles / 32;

@@ -8,18 +8,18 @@
 // giving d/d(network parameters) and, for continuous actions, d/dA.
 //
 // One wave owns a tile of 32 rollouts.  The forward pass keeps the states in
-// registers and stores a checkpoint every C steps in the workspace.  The
-// reverse sweep walks the segments backwards: it recomputes the segment's
-// states from its checkpoint, then for each step (last first) recomputes the
-// step's activations, and back-propagates the state adjoint through the
-// layers with MFMAs whose A operands are the *transposed* weights packed so
-// that every adjoint comes out in exactly the register layout of the matching
-// forward activation (ReLU masks are register-wise).  Weight gradients
-// dW += dh h^T are products over the 32 rollouts of the tile: the wave writes
-// (dh, h) as [rollout][feature] rows into its own LDS scratch (row stride 129
-// floats, conflict-free) and accumulates them on MFMA with rollouts as the
-// reduction dimension.  Each wave writes its parameter-gradient partial once;
-// a second kernel sums the partials in a fixed order (deterministic).
+// registers and writes every step's to the workspace (16 bytes per rollout and
+// step, in the lanes' own layout); the reverse sweep reads them back, last step
+// first, recomputes the step's hidden activations, and back-propagates the
+// state adjoint through the layers with MFMAs whose A operands are the
+// *transposed* weights packed so that every adjoint comes out in exactly the
+// register layout of the matching forward activation (ReLU masks are
+// register-wise).  Weight gradients dW += dh h^T are products over the 32
+// rollouts of the tile: the wave writes (dh, h) as [rollout][feature] rows into
+// its own LDS scratch (row stride 97 floats) and accumulates them on MFMA with
+// rollouts as the reduction dimension.  A block's waves add their partial
+// gradients in wave order, each block writes one partial, and a second kernel
+// sums the blocks' in a fixed order (deterministic).
 #include "kernels.hpp"
 
 #include <math.h>
@@ -28,7 +28,8 @@ namespace voila {
 
 namespace {
 
-constexpr int kRow = 129;  // floats per rollout row of the transpose scratch
+constexpr int kRow = 129;    // floats per pair row of the contrastive kernel's transpose scratch
+constexpr int kRowR = 97;    // floats per rollout row of the rollout kernel's (two rows of waves per SIMD fit in LDS)
 
 // Fragment indices of the transposed pack: [T3: KS3 x HT][T2: 16HT x HT][T1: 16HT x 1]
 template <int D_S, int HT> struct BwdIdx {
@@ -44,13 +45,49 @@ __device__ __forceinline__ float lds_frag(const char* base, int f, int lane) {
 
 }  // namespace
 
+// Products whose result has four rows: v_mfma_f32_4x4x1 takes one k per
+// instruction and lane group for all 64 lanes in 8 cycles, where a 32-row tile
+// would compute 28 rows of padding in 64.
+__device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x4 mfma16(float a, float b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+// Fragment row of value m (of four, from feature f0 on) in a 32-row output
+// tile: feature f sits at row out_row(f / 2, f % 2).
+__device__ __forceinline__ int row_of(int f) { return out_row(f >> 1, f & 1); }
+// The two lane groups hold partial sums over their own k of the same four
+// values: lanes of group g get value 2 s + g in out[s].
+__device__ __forceinline__ void join_halves(const f32x4& d, float (&out)[2]) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(d[2 * s]), __float_as_uint(d[2 * s + 1]), false,
+                                                        false);
+        out[s] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+}
+
+// Adjoint of a tile per wave.  Bound by the matrix cores: per tile and step
+// 78 32x32x2 products to run the hidden layers, twice (forward, and again in
+// the reverse sweep: reading the activations back would cost 16 KB per tile and
+// step), 64 each for dW2 and dh1, and the equivalent of 40 for the rest.
+// The layers with four outputs (the network's own output, dW3, the state and
+// action adjoints) take 4-row products and dW1 (at most 16 columns) 16 x 16
+// ones; with 32-row tiles, and with the states recomputed from checkpoints
+// every five steps, the same step took 526.  Two waves per SIMD (256 registers
+// each) overlap one's LDS transposes with the other's products.  65,536
+// rollouts x 20 steps: the whole call 855 -> 557 us (about 340 us at the
+// matrix cores' rate).
 template <int D_S, int N_ACT, int D_A, int D_W>
-__global__ __launch_bounds__(256) void grad_kernel(GradParams p) {
+__global__ __launch_bounds__(kGradMaxWaves * 64) void grad_kernel(GradParams p) {
     constexpr int WIDTH = 64, NHID = 2, HT = 2;
     constexpr int D_AIN = N_ACT > 0 ? N_ACT : D_A;
     constexpr int SS = state_slots(D_S), SA = action_slots(D_AIN), SW = noise_slots(D_W);
     constexpr int D_IN = D_S + D_AIN + D_W;
-    static_assert(D_IN <= 31 && D_S <= 32, "inputs must fit one 32-row tile (column 31 carries the bias)");
+    static_assert(D_S == 4, "output and state adjoint are one four-row product");
+    static_assert(D_IN <= 15, "inputs must fit one 16-column tile (column 15 carries the bias)");
+    static_assert(N_ACT > 0 || D_A == 4, "action adjoints are one four-row product");
     typedef Net<DT_F32, WIDTH, NHID, in_slots(DT_F32, D_S, D_AIN, D_W)> NT;
     typedef BwdIdx<D_S, HT> BI;
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -60,21 +97,22 @@ __global__ __launch_bounds__(256) void grad_kernel(GradParams p) {
     const NetPtrs P = net_ptrs(smem, p.fwd);
     const char* bw = smem + p.fwd.bytes;
     const int lane = threadIdx.x & 63, g = lane >> 5, col = lane & 31;
-    const int wpb = blockDim.x >> 6, wave = threadIdx.x >> 6;
-    float* scr = reinterpret_cast<float*>(smem + p.fwd.bytes + p.bwd.bytes) + wave * 32 * kRow;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wpb = p.waves;  // waves that take tiles (the others only stage)
+    float* scr = reinterpret_cast<float*>(smem + p.fwd.bytes + p.bwd.bytes) + wave * 32 * kRowR;
 
     // weight-gradient accumulators (MFMA layouts) and per-lane bias sums
-    f32x16 gW1[HT], gW2[HT][HT], gW3[HT];
+    f32x4 gW1[4], gW3[2];
+    f32x16 gW2[HT][HT], gb2[HT];
+#pragma unroll
+    for (int a = 0; a < 4; ++a) gW1[a] = f32x4{};
 #pragma unroll
     for (int a = 0; a < HT; ++a) {
-        gW1[a] = f32x16{};
-        gW3[a] = f32x16{};
+        gW3[a] = f32x4{};
+        gb2[a] = f32x16{};
 #pragma unroll
         for (int b = 0; b < HT; ++b) gW2[a][b] = f32x16{};
     }
-    f32x16 gb2[HT];
-#pragma unroll
-    for (int a = 0; a < HT; ++a) gb2[a] = f32x16{};
     float gb3[SS];
 #pragma unroll
     for (int s = 0; s < SS; ++s) gb3[s] = 0.0f;
@@ -123,269 +161,273 @@ __global__ __launch_bounds__(256) void grad_kernel(GradParams p) {
         }
         return -1;
     };
+    // the two hidden layers' activations
+    auto hidden = [&](const float (&slots)[NT::IN_SLOTS], Act<DT_F32, HT>& h1, Act<DT_F32, HT>& h2) {
+        DirectSrc<DT_F32, 8 * HT> src(P.f0);
+        f32x16 acc[HT];
+        init_bias<HT>(acc, P.b0 + opaque_zero(), g);
+#pragma unroll
+        for (int c = 0; c < NT::IN_KS; ++c)
+#pragma unroll
+            for (int mt = 0; mt < HT; ++mt)
+                acc[mt] = mfma(src.load(FragIdx<NT>::first(c, mt), lane), slots[c], acc[mt]);
+        h1.set_relu(acc);
+        init_bias<HT>(acc, P.bh + opaque_zero(), g);
+#pragma unroll
+        for (int c = 0; c < NT::HID_KS; ++c)
+#pragma unroll
+            for (int mt = 0; mt < HT; ++mt)
+                acc[mt] = mfma(src.load(FragIdx<NT>::hidden(1, c, mt), lane), h1.b(c), acc[mt]);
+        h2.set_relu(acc);
+    };
+    // four values sum_k w[m][k] h[k] of the lane's column (m = 0..3): `frag0`
+    // holds the 32-row fragments of k-steps 0 .. 31, whose rows of the four
+    // features from f0 on are the A operand of every block of four lanes
+    auto four = [&](const char* frag0, int f0, const f32x16 (&h)[HT]) {
+        const float* a = reinterpret_cast<const float*>(frag0) + 32 * g + row_of(f0 + (lane & 3)) + opaque_zero();
+        f32x4 d[2] = {f32x4{}, f32x4{}};
+#pragma unroll
+        for (int c = 0; c < 16 * HT; ++c) d[c & 1] = mfma4(a[c * 64], h[c >> 4][c & 15], d[c & 1]);
+        return d[0] + d[1];
+    };
+
+    // the network's output: the same four values in every lane, summed over k in
+    // ascending order from the bias as a 32-row tile sums them (the matrix
+    // cores add one k at a time, whatever the shape), so that the rollouts are
+    // the plan kernel's bit for bit
+    auto output = [&](const f32x16 (&h)[HT]) {
+        const int row = row_of(lane & 3);
+        const float* a = reinterpret_cast<const float*>(P.fo) + row + opaque_zero();
+        f32x4 d;
+#pragma unroll
+        for (int m = 0; m < 4; ++m) d[m] = P.bo[row_of(m)];
+#pragma unroll
+        for (int c = 0; c < 16 * HT; ++c) {
+            const uint32_t v = __float_as_uint(h[c >> 4][c & 15]);
+            const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);  // both groups' k
+            d = mfma4(a[c * 64], __uint_as_float(r[0]), d);
+            d = mfma4(a[c * 64 + 32], __uint_as_float(r[1]), d);
+        }
+        return d;
+    };
 
     const int n_tiles = (p.B + 31) / 32;
-    for (long ub = blockIdx.x; ub * wpb < n_tiles; ub += gridDim.x) {
-        const int tile = (int)(ub * wpb + wave);
-        const bool tile_ok = tile < n_tiles;
-        const int b = (tile_ok ? tile : 0) * 32 + col;
-        const bool valid = tile_ok && b < p.B;
+    const int first_tile = (int)blockIdx.x * wpb + wave;
+    for (long tl = wave < wpb ? first_tile : n_tiles; tl < n_tiles; tl += (long)gridDim.x * wpb) {
+        const int tile = (int)tl;
+        const int b = tile * 32 + col;
+        const bool valid = b < p.B;
+        float* keep = p.states + (size_t)tile * p.H * (SS * 64) + lane;  // s_t slots of this lane, t < H
         float st[SS];
 #pragma unroll
         for (int s = 0; s < SS; ++s) {
             int f = 2 * s + g;
             st[s] = (valid && f < D_S) ? p.s0[(size_t)b * D_S + f] : 0.0f;
         }
-        // ---- forward with checkpoints
+        // ---- forward (rollouts past B stay at the origin: finite, no weight in any sum)
         for (int t = 0; t < p.H; ++t) {
-            if (t % p.C == 0 && valid)
 #pragma unroll
-                for (int s = 0; s < SS; ++s)
-                    if (2 * s + g < D_S) p.ckpt[((size_t)b * p.NC + t / p.C) * D_S + 2 * s + g] = st[s];
+            for (int s = 0; s < SS; ++s) keep[(size_t)(t * SS + s) * 64] = st[s];
             float slots[NT::IN_SLOTS];
             make_slots(slots, st, b, valid, t);
-            DirectSrc<DT_F32, 8 * HT> src(P.f0);
-            f32x16 d = run_net<NT>(src, P, P.b0, slots, lane, g);
+            Act<DT_F32, HT> h1, h2;
+            hidden(slots, h1, h2);
+            const f32x4 d = output(h2.v);
             float part = 0.0f;
 #pragma unroll
             for (int s = 0; s < SS; ++s) {
-                st[s] += d[s];
                 int f = 2 * s + g;
                 if (f < D_S && valid) {
+                    st[s] += g ? d[2 * s + 1] : d[2 * s];
                     float e = p.objective == 0 ? st[s] - p.targets[((size_t)b * p.H + t) * D_S + f] : st[s] - p.goal[f];
                     part += e * e;
                 }
             }
             loss_acc += p.objective == 0 ? part : -p.disc[t] * part;
         }
-        // ---- reverse sweep over the segments
+        // ---- reverse sweep
         float lam[SS];
 #pragma unroll
         for (int s = 0; s < SS; ++s) lam[s] = 0.0f;
-        for (int seg = (p.H - 1) / p.C; seg >= 0 && p.H > 0; --seg) {
-            const int t0 = seg * p.C, t1 = min(p.H, t0 + p.C);
-            // recompute the segment's states s_t0 .. s_t1 into the workspace
+        for (int t = p.H - 1; t >= 0; --t) {
+            // objective gradient at s_{t+1}
 #pragma unroll
             for (int s = 0; s < SS; ++s) {
                 int f = 2 * s + g;
-                st[s] = (valid && f < D_S) ? p.ckpt[((size_t)b * p.NC + seg) * D_S + f] : 0.0f;
+                if (f < D_S && valid) {
+                    float e = p.objective == 0 ? st[s] - p.targets[((size_t)b * p.H + t) * D_S + f] : st[s] - p.goal[f];
+                    lam[s] += (p.objective == 0 ? 2.0f * (float)p.scale : -2.0f * p.disc[t] * (float)p.scale) * e;
+                }
             }
-            for (int t = t0; t <= t1; ++t) {
-                if (valid)
 #pragma unroll
-                    for (int s = 0; s < SS; ++s)
-                        if (2 * s + g < D_S) p.segst[((size_t)b * (p.C + 1) + (t - t0)) * D_S + 2 * s + g] = st[s];
-                if (t == t1) break;
-                float slots[NT::IN_SLOTS];
-                make_slots(slots, st, b, valid, t);
-                DirectSrc<DT_F32, 8 * HT> src(P.f0);
-                f32x16 d = run_net<NT>(src, P, P.b0, slots, lane, g);
+            for (int s = 0; s < SS; ++s) st[s] = keep[(size_t)(t * SS + s) * 64];
+            // the activations of step t again
+            float slots[NT::IN_SLOTS];
+            make_slots(slots, st, b, valid, t);
+            Act<DT_F32, HT> h1, h2;
+            hidden(slots, h1, h2);
+            const bool wp = p.want_params != 0;
+            // (1) dW3 += lam h2^T: rows lam (0..3), h2 (4..67)
+            if (wp) {
+                __builtin_amdgcn_wave_barrier();
 #pragma unroll
-                for (int s = 0; s < SS; ++s) st[s] += d[s];
-            }
-            for (int t = t1 - 1; t >= t0; --t) {
-                float s_t[SS], s_n[SS];
-#pragma unroll
-                for (int s = 0; s < SS; ++s) {
-                    int f = 2 * s + g;
-                    s_t[s] = (valid && f < D_S) ? p.segst[((size_t)b * (p.C + 1) + (t - t0)) * D_S + f] : 0.0f;
-                    s_n[s] = (valid && f < D_S) ? p.segst[((size_t)b * (p.C + 1) + (t - t0 + 1)) * D_S + f] : 0.0f;
-                }
-                // objective gradient at s_{t+1}
-#pragma unroll
-                for (int s = 0; s < SS; ++s) {
-                    int f = 2 * s + g;
-                    if (f < D_S && valid) {
-                        float e = p.objective == 0 ? s_n[s] - p.targets[((size_t)b * p.H + t) * D_S + f] : s_n[s] - p.goal[f];
-                        lam[s] += (p.objective == 0 ? 2.0f * (float)p.scale : -2.0f * p.disc[t] * (float)p.scale) * e;
-                    }
-                }
-                // recompute the activations of step t
-                float slots[NT::IN_SLOTS];
-                make_slots(slots, s_t, b, valid, t);
-                f32x16 acc[HT];
-                Act<DT_F32, HT> h1, h2;
-                {
-                    DirectSrc<DT_F32, 8 * HT> src(P.f0);
-                    init_bias<HT>(acc, P.b0 + opaque_zero(), g);
-#pragma unroll
-                    for (int c = 0; c < NT::IN_KS; ++c)
-#pragma unroll
-                        for (int mt = 0; mt < HT; ++mt)
-                            acc[mt] = mfma(src.load(FragIdx<NT>::first(c, mt), lane), slots[c], acc[mt]);
-                    h1.set_relu(acc);
-                    init_bias<HT>(acc, P.bh + opaque_zero(), g);
-#pragma unroll
-                    for (int c = 0; c < NT::HID_KS; ++c)
-#pragma unroll
-                        for (int mt = 0; mt < HT; ++mt)
-                            acc[mt] = mfma(src.load(FragIdx<NT>::hidden(1, c, mt), lane), h1.b(c), acc[mt]);
-                    h2.set_relu(acc);
-                }
-                const bool wp = p.want_params != 0;
-                float lamv[16];
-#pragma unroll
-                for (int i = 0; i < 16; ++i) lamv[i] = (i < SS && valid) ? lam[i] : 0.0f;
-                // (1) dW3 += lam h2^T: rows lam (output features 0..31), h2 at 32..95
-                if (wp) {
-                    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) scr[col * kRow + 2 * i + g] = lamv[i];
-#pragma unroll
-                    for (int mt = 0; mt < HT; ++mt)
-#pragma unroll
-                        for (int i = 0; i < 16; ++i)
-                            scr[col * kRow + 32 + 32 * mt + out_row(i, g)] = valid ? h2.v[mt][i] : 0.0f;
-                    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                    for (int c = 0; c < 16; ++c) {
-                        const float* r = scr + (2 * c + g) * kRow;
-                        float ax = r[col];
-#pragma unroll
-                        for (int nt = 0; nt < HT; ++nt) gW3[nt] = mfma(ax, r[32 + 32 * nt + col], gW3[nt]);
-                    }
-#pragma unroll
-                    for (int s = 0; s < SS; ++s) gb3[s] += lamv[s];
-                }
-                // (2) dh2 = (W3^T lam) * [h2 > 0]
-                f32x16 dh2[HT];
-#pragma unroll
-                for (int mt = 0; mt < HT; ++mt) {
-                    const char* bwz = bw + opaque_zero();
-                    dh2[mt] = f32x16{};
-#pragma unroll
-                    for (int c = 0; c < BI::KS3; ++c) dh2[mt] = mfma(lds_frag(bwz, BI::t3(c, mt), lane), lam[c], dh2[mt]);
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) dh2[mt][i] = (valid && h2.v[mt][i] > 0.0f) ? dh2[mt][i] : 0.0f;
-                }
-                // (3) dW2 += dh2 h1^T: rows dh2 (0..63), h1 at 64..127; b2 += dh2
-                if (wp) {
-                    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                    for (int mt = 0; mt < HT; ++mt)
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) {
-                            scr[col * kRow + 32 * mt + out_row(i, g)] = dh2[mt][i];
-                            scr[col * kRow + 64 + 32 * mt + out_row(i, g)] = valid ? h1.v[mt][i] : 0.0f;
-                        }
-                    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                    for (int c = 0; c < 16; ++c) {
-                        const float* r = scr + (2 * c + g) * kRow;
-#pragma unroll
-                        for (int nt = 0; nt < HT; ++nt) {
-                            float bx = r[64 + 32 * nt + col];
-#pragma unroll
-                            for (int mt = 0; mt < HT; ++mt) gW2[mt][nt] = mfma(r[32 * mt + col], bx, gW2[mt][nt]);
-                        }
-                    }
-#pragma unroll
-                    for (int mt = 0; mt < HT; ++mt) gb2[mt] += dh2[mt];
-                }
-                // (4) dh1 = (W2^T dh2) * [h1 > 0]
-                f32x16 dh1[HT];
-#pragma unroll
-                for (int mt = 0; mt < HT; ++mt) dh1[mt] = f32x16{};
-#pragma unroll
-                for (int c0 = 0; c0 < 16 * HT; c0 += 8) {
-                    const char* bwz = bw + opaque_zero();
-#pragma unroll
-                    for (int c = c0; c < c0 + 8; ++c)
-#pragma unroll
-                        for (int mt = 0; mt < HT; ++mt)
-                            dh1[mt] = mfma(lds_frag(bwz, BI::t2(c, mt), lane), dh2[c >> 4][c & 15], dh1[mt]);
-                }
+                for (int s = 0; s < SS; ++s) scr[col * kRowR + 2 * s + g] = lam[s];
 #pragma unroll
                 for (int mt = 0; mt < HT; ++mt)
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) dh1[mt][i] = h1.v[mt][i] > 0.0f ? dh1[mt][i] : 0.0f;
-                // (5) dW1 (+ b1 through the ones column 31) += dh1 x^T: rows dh1 (0..63), x at 64..95
-                if (wp) {
-                    __builtin_amdgcn_wave_barrier();
+                    for (int i = 0; i < 16; ++i) scr[col * kRowR + 4 + 32 * mt + out_row(i, g)] = h2.v[mt][i];
+                __builtin_amdgcn_wave_barrier();
 #pragma unroll
-                    for (int mt = 0; mt < HT; ++mt)
+                for (int r = 0; r < 32; ++r)
+                    gW3[r & 1] = mfma4(scr[r * kRowR + (lane & 3)], scr[r * kRowR + 4 + lane], gW3[r & 1]);
 #pragma unroll
-                        for (int i = 0; i < 16; ++i) scr[col * kRow + 32 * mt + out_row(i, g)] = dh1[mt][i];
+                for (int s = 0; s < SS; ++s) gb3[s] += lam[s];
+            }
+            // (2) dh2 = (W3^T lam) * [h2 > 0]
+            f32x16 dh2[HT];
 #pragma unroll
-                    for (int j = 0; j < 16; ++j) scr[col * kRow + 64 + 16 * g + j] = (16 * g + j == 31) ? 1.0f : 0.0f;
+            for (int mt = 0; mt < HT; ++mt) {
+                const char* bwz = bw + opaque_zero();
+                dh2[mt] = f32x16{};
 #pragma unroll
-                    for (int s = 0; s < NT::IN_SLOTS; ++s) {
-                        int cc = slot_col(s);
-                        if (cc >= 0) scr[col * kRow + 64 + cc] = slots[s];
-                    }
+                for (int c = 0; c < BI::KS3; ++c) dh2[mt] = mfma(lds_frag(bwz, BI::t3(c, mt), lane), lam[c], dh2[mt]);
+#pragma unroll
+                for (int i = 0; i < 16; ++i) dh2[mt][i] = h2.v[mt][i] > 0.0f ? dh2[mt][i] : 0.0f;
+            }
+            // (3) dW2 += dh2 h1^T, one 32-row tile of dh2 (0..31) at a time beside h1 (32..95); b2 += dh2
+            if (wp) {
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int mt = 0; mt < HT; ++mt)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) scr[col * kRowR + 32 + 32 * mt + out_row(i, g)] = h1.v[mt][i];
+#pragma unroll
+                for (int mt = 0; mt < HT; ++mt) {
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) scr[col * kRowR + out_row(i, g)] = dh2[mt][i];
                     __builtin_amdgcn_wave_barrier();
 #pragma unroll
                     for (int c = 0; c < 16; ++c) {
-                        const float* r = scr + (2 * c + g) * kRow;
-                        float bx = r[64 + col];
+                        const float* r = scr + (2 * c + g) * kRowR + col;
+                        const float ax = r[0];
 #pragma unroll
-                        for (int mt = 0; mt < HT; ++mt) gW1[mt] = mfma(r[32 * mt + col], bx, gW1[mt]);
+                        for (int nt = 0; nt < HT; ++nt) gW2[mt][nt] = mfma(ax, r[32 + 32 * nt], gW2[mt][nt]);
                     }
                     __builtin_amdgcn_wave_barrier();
+                    gb2[mt] += dh2[mt];
                 }
-                // (6) dx = W1^T dh1: input feature 2 i + g in register i
-                f32x16 dx = f32x16{};
-#pragma unroll
-                for (int c0 = 0; c0 < 16 * HT; c0 += 8) {
-                    const char* bwz = bw + opaque_zero();
-#pragma unroll
-                    for (int c = c0; c < c0 + 8; ++c) dx = mfma(lds_frag(bwz, BI::t1(c), lane), dh1[c >> 4][c & 15], dx);
-                }
-                // action gradient of this step (continuous actions), summed over the tile
-                if (N_ACT == 0 && p.apart) {
-#pragma unroll
-                    for (int j = 0; j < D_AIN; ++j) {
-                        const int fin = D_S + j;
-                        float v = (valid && (fin & 1) == g) ? dx[fin >> 1] : 0.0f;
-                        v = sum32(v);
-                        v += __shfl_xor(v, 32);
-                        if (lane == 0 && tile_ok) p.apart[((size_t)tile * p.H + t) * D_AIN + j] = v;
-                    }
-                }
-                // state adjoint: lam_t = lam_{t+1} + d(f_T)/ds_t^T lam_{t+1}
-#pragma unroll
-                for (int s = 0; s < SS; ++s)
-                    if (2 * s + g < D_S) lam[s] += dx[s];
             }
+            // (4) dh1 = (W2^T dh2) * [h1 > 0]
+            f32x16 dh1[HT];
+#pragma unroll
+            for (int mt = 0; mt < HT; ++mt) dh1[mt] = f32x16{};
+#pragma unroll
+            for (int c0 = 0; c0 < 16 * HT; c0 += 8) {
+                const char* bwz = bw + opaque_zero();
+#pragma unroll
+                for (int c = c0; c < c0 + 8; ++c)
+#pragma unroll
+                    for (int mt = 0; mt < HT; ++mt)
+                        dh1[mt] = mfma(lds_frag(bwz, BI::t2(c, mt), lane), dh2[c >> 4][c & 15], dh1[mt]);
+            }
+#pragma unroll
+            for (int mt = 0; mt < HT; ++mt)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) dh1[mt][i] = h1.v[mt][i] > 0.0f ? dh1[mt][i] : 0.0f;
+            // (5) dW1 (+ b1 through the ones column 15) += dh1 x^T: rows dh1 (0..63), x (64..79)
+            if (wp) {
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int mt = 0; mt < HT; ++mt)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) scr[col * kRowR + 32 * mt + out_row(i, g)] = dh1[mt][i];
+                if (g)
+#pragma unroll
+                    for (int j = D_IN; j < 16; ++j) scr[col * kRowR + 64 + j] = j == 15 ? 1.0f : 0.0f;
+#pragma unroll
+                for (int s = 0; s < NT::IN_SLOTS; ++s) {
+                    int cc = slot_col(s);
+                    if (cc >= 0) scr[col * kRowR + 64 + cc] = slots[s];
+                }
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    const float* r = scr + (4 * c + (lane >> 4)) * kRowR + (lane & 15);
+                    const float bx = r[64];
+#pragma unroll
+                    for (int mt = 0; mt < 4; ++mt) gW1[mt] = mfma16(r[16 * mt], bx, gW1[mt]);
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+            // (6) dx = W1^T dh1: the state adjoint, and with continuous actions the action's
+            const char* t1 = bw + (size_t)BI::t1(0) * 256;
+            // action gradient of this step (continuous actions), summed over the tile
+            if (N_ACT == 0 && p.apart) {
+                const f32x4 da = four(t1, D_S, dh1);
+#pragma unroll
+                for (int j = 0; j < D_AIN; ++j) {
+                    float v = valid ? da[j] : 0.0f;
+                    v = sum32(v);
+                    v += __shfl_xor(v, 32);
+                    if (lane == 0) p.apart[((size_t)tile * p.H + t) * D_AIN + j] = v;
+                }
+            }
+            // state adjoint: lam_t = lam_{t+1} + d(f_T)/ds_t^T lam_{t+1}
+            float dx[SS];
+            join_halves(four(t1, 0, dh1), dx);
+#pragma unroll
+            for (int s = 0; s < SS; ++s)
+                if (2 * s + g < D_S) lam[s] += dx[s];
         }
     }
-    // ---- per-wave partials
-    const int wid = blockIdx.x * wpb + wave;
-    float lsum = sum32(loss_acc) + __shfl_xor(sum32(loss_acc), 32);
-    if (lane == 0) p.lpart[wid] = lsum;
+    // ---- the block's partial: its waves' in wave order, gathered in LDS
+    __syncthreads();
+    float* sum = reinterpret_cast<float*>(smem);
+    float lsum = sum32(loss_acc);
+    lsum += __shfl_xor(lsum, 32);
+    if (lane == 0 && wave < wpb) sum[wave] = lsum;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float v = 0.0f;
+        for (int k = 0; k < wpb; ++k) v += sum[k];
+        p.lpart[blockIdx.x] = v;
+    }
     if (!p.want_params) return;
-    float* out = p.wpart + (size_t)wid * p.n_params;
     // layout: W1 [64][D_IN], b1 [64], W2 [64][64], b2 [64], W3 [D_S][64], b3 [D_S]
-    const int oW1 = 0, ob1 = 64 * D_IN, oW2 = ob1 + 64, ob2 = oW2 + 64 * 64, oW3 = ob2 + 64, ob3 = oW3 + D_S * 64;
+    constexpr int oW1 = 0, ob1 = 64 * D_IN, oW2 = ob1 + 64, ob2 = oW2 + 64 * 64, oW3 = ob2 + 64, ob3 = oW3 + D_S * 64;
+    for (int k = 0; k < wpb; ++k) {
+        __syncthreads();
+        if (wave != k) continue;
+        auto put = [&](int at, float v) { sum[at] = k ? sum[at] + v : v; };
 #pragma unroll
-    for (int mt = 0; mt < HT; ++mt)
+        for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int m = 32 * mt + out_row(i, g);
-            if (col < D_IN) out[oW1 + m * D_IN + col] = gW1[mt][i];
-            if (col == 31) out[ob1 + m] = gW1[mt][i];
+            for (int i = 0; i < 4; ++i) {
+                const int m = 16 * mt + 4 * (lane >> 4) + i, n = lane & 15;
+                if (n < D_IN) put(oW1 + m * D_IN + n, gW1[mt][i]);
+                if (n == 15) put(ob1 + m, gW1[mt][i]);
+            }
 #pragma unroll
-            for (int nt = 0; nt < HT; ++nt) out[oW2 + m * 64 + 32 * nt + col] = gW2[mt][nt][i];
+        for (int mt = 0; mt < HT; ++mt)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int m = 32 * mt + out_row(i, g);
+#pragma unroll
+                for (int nt = 0; nt < HT; ++nt) put(oW2 + m * 64 + 32 * nt + col, gW2[mt][nt][i]);
+                const float v = sum32(gb2[mt][i]);
+                if (col == 0) put(ob2 + m, v);
+            }
+#pragma unroll
+        for (int m = 0; m < D_S; ++m) put(oW3 + m * 64 + lane, gW3[0][m] + gW3[1][m]);
+#pragma unroll
+        for (int s = 0; s < SS; ++s) {
+            const float v = sum32(gb3[s]);
+            if (col == 0 && 2 * s + g < D_S) put(ob3 + 2 * s + g, v);
         }
-#pragma unroll
-    for (int nt = 0; nt < HT; ++nt)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int m = out_row(i, g);
-            if (m < D_S) out[oW3 + m * 64 + 32 * nt + col] = gW3[nt][i];
-        }
-#pragma unroll
-    for (int mt = 0; mt < HT; ++mt)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            float v = sum32(gb2[mt][i]);
-            if (col == 0) out[ob2 + 32 * mt + out_row(i, g)] = v;
-        }
-#pragma unroll
-    for (int s = 0; s < SS; ++s) {
-        float v = sum32(gb3[s]);
-        if (col == 0 && 2 * s + g < D_S) out[ob3 + 2 * s + g] = v;
     }
+    __syncthreads();
+    float* out = p.wpart + (size_t)blockIdx.x * p.n_params;
+    for (int q = threadIdx.x; q < p.n_params; q += blockDim.x) out[q] = sum[q];
 }
 
 // Fixed-order sums of the per-wave partials: parameters, objective, actions.
@@ -648,12 +690,14 @@ bool grad_supported(int shape) {
 }
 
 hipError_t launch_grad(int shape, const GradParams& p, int blocks, size_t lds, hipStream_t s) {
+    // at least four waves stage the networks, whatever number takes tiles
+    const int threads = 64 * (p.waves < 4 ? 4 : p.waves);
     switch (shape) {
 #define X(id, ds, na, da, dw)                                                                                \
     case id:                                                                                                \
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(grad_kernel<ds, na, da, dw>),                 \
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                     \
-        hipLaunchKernelGGL((grad_kernel<ds, na, da, dw>), blocks, 256, lds, s, p);                           \
+        hipLaunchKernelGGL((grad_kernel<ds, na, da, dw>), blocks, threads, lds, s, p);                           \
         break;
         GRAD_SHAPES(X)
 #undef X
@@ -663,19 +707,7 @@ hipError_t launch_grad(int shape, const GradParams& p, int blocks, size_t lds, h
     return hipGetLastError();
 }
 
-int grad_blocks_per_cu(int shape, size_t lds) {
-    int n = 0;
-    switch (shape) {
-#define X(id, ds, na, da, dw)                                                                                  \
-    case id:                                                                                                  \
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, grad_kernel<ds, na, da, dw>, 256, lds) != hipSuccess) \
-            n = 1;                                                                                            \
-        break;
-        GRAD_SHAPES(X)
-#undef X
-    }
-    return n < 1 ? 1 : n;
-}
+size_t grad_scratch_bytes(int waves) { return (size_t)waves * 32 * kRowR * sizeof(float); }
 
 // (shape id, d_s, discrete actions, continuous action width, d_o)
 #define NCE_GRAD_SHAPES(X) X(0, 4, 5, 0, 2) X(2, 4, 0, 4, 2)

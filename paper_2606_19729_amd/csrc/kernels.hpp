@@ -255,18 +255,19 @@ struct FoldBatchItem {
 };
 
 // Adjoint rollouts (two hidden layers of width 64, binary32).
+constexpr int kGradMaxWaves = 8;
 struct GradParams {
     NetBlob fwd, bwd;          // forward pack (actions as inputs) and transposed pack
     const float* s0;           // [B][d_s]
     const void* actions;       // int32 [B][H] or float [B / particles][H][d_a]
     const float* noise;        // [B][H][d_w] or NULL
     const float* targets;      // [B][H][d_s] (distillation)
-    float* ckpt;               // [B][NC][d_s] checkpoints
-    float* segst;              // [B][C + 1][d_s] states of the segment being reversed
-    float* wpart;              // [waves][n_params] parameter-gradient partials
-    float* lpart;              // [waves] objective partials
+    float* states;             // [tiles][H][state slots][64] rollout states s_0 .. s_{H-1}, one lane slot each
+    float* wpart;              // [blocks][n_params] parameter-gradient partials
+    float* lpart;              // [blocks] objective partials
     float* apart;              // [tiles][H][d_a] action-gradient partials or NULL
-    int B, H, C, NC, particles, objective, want_params, n_params;
+    int B, H, particles, objective, want_params, n_params;
+    int waves;                 // waves per block that take tiles (<= kGradMaxWaves)
     double scale;
     uint32_t key0, key1;
     float goal[32];
@@ -414,7 +415,7 @@ int plan_batch_blocks_per_cu(int shape, int dt, int waves_per_block, size_t lds)
 bool grad_supported(int shape);
 hipError_t launch_grad(int shape, const GradParams& p, int blocks, size_t lds, hipStream_t s);
 hipError_t launch_grad_reduce(const GradReduceParams& p, hipStream_t s);
-int grad_blocks_per_cu(int shape, size_t lds);
+size_t grad_scratch_bytes(int waves);  // transpose rows of that many waves
 int propose_batch_blocks_per_cu(int shape, int dt, int waves_per_block, size_t lds);
 
 // Output tiles per pass of the plan kernel's paired evaluation (two

@@ -195,6 +195,53 @@ def test_full_size_distillation_and_return_gradients(V):
         assert ek <= TOL
 
 
+@pytest.mark.parametrize("tiles", [1, 5, 256, 257, 1025, 2049])
+def test_gradients_at_every_spread_of_tiles(V, tiles):
+    """Rollout tiles per block from one wave on one CU to more tiles than the
+    card's waves (a second pass over the grid), with a ragged last tile."""
+    H, B = 3, 32 * tiles - 27
+    m, S0, A, T = distill_inputs(B, H, seed=21, noise_seed=6)
+    print(f"grad case: distillation, {tiles} tiles, B={B}", flush=True)
+    loss, gp, _ = V.rollout_grad(V.Model(m), dev(S0), dev(A, torch.int32), H, V.VOILA_OBJ_DISTILL, targets=dev(T),
+                                 seed=6)
+    torch.cuda.synchronize()
+    l_ref, g_ref, _ = oracle.rollout_grad(m, S0, A, H, oracle.DISTILL, targets=T, seed=6)
+    assert abs(loss.item() - l_ref) <= 1e-5 * abs(l_ref)
+    assert rel(gp.cpu().numpy(), flat_layers(g_ref)) <= TOL
+    mc, rng = cont_model(seed=22), np.random.default_rng(22)
+    S0c = rng.standard_normal((32 * tiles, 4)).astype(np.float32)
+    Ac = rng.uniform(-1, 1, (tiles, H, 4)).astype(np.float32)
+    goal = np.array([1.0, 1.0, 0.0, 0.0], np.float32)
+    J, gpc, gA = V.rollout_grad(V.Model(mc), dev(S0c), dev(Ac), H, V.VOILA_OBJ_RETURN, gamma=0.9, goal=goal,
+                                particles=32, seed=7, want_actions=True)
+    torch.cuda.synchronize()
+    J_ref, gp_ref, gA_ref = oracle.rollout_grad(mc, S0c, Ac, H, oracle.RETURN, gamma=0.9, goal=goal, particles=32,
+                                                seed=7, want_actions=True)
+    assert abs(J.item() - J_ref) <= 1e-5 * abs(J_ref)
+    assert rel(gpc.cpu().numpy(), flat_layers(gp_ref)) <= TOL
+    # a sequence's gradient is a sum over its 32 rollouts alone, and a unit
+    # whose pre-activation lies within binary32 rounding of zero can take
+    # either side of the ReLU: those sequences have no gradient to compare
+    sure = kink_distance(mc, S0c, Ac, 7) > 1e-6
+    assert sure.mean() > 0.97 and rel(gA.cpu().numpy()[sure], gA_ref[sure]) <= TOL
+
+
+def kink_distance(m, S0, A, seed):
+    """Each sequence's smallest |pre-activation| (binary64) over its 32 rollouts and all steps."""
+    K, H = A.shape[:2]
+    s, near = S0.astype(np.float64), np.full(K, np.inf)
+    for t in range(H):
+        a = np.repeat(A[:, t].astype(np.float64), 32, axis=0)
+        z = np.concatenate([s, a, oracle.normals_rows(seed, 32 * K, 0, t, 3, 4)], axis=1)
+        for li, (W, b) in enumerate(m.trans):
+            z = z @ W.astype(np.float64).T + b
+            if li + 1 < len(m.trans):
+                near = np.minimum(near, np.abs(z).reshape(K, -1).min(axis=1))
+                z = np.maximum(z, 0.0)
+        s = s + z
+    return near
+
+
 def test_autograd_functions(V):
     from paper_2606_19729_amd.autograd import DistillLoss, MeanReturn
     mc = cont_model(seed=14)
