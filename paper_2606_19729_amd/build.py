@@ -17,7 +17,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libvoila.so")
 OBJ = os.path.join(HERE, "_build")
-SOURCES = ["k_plan.hip", "k_plan_bf16.hip", "k_observe.hip", "k_search.hip", "k_nce.hip", "k_nce_grad.hip", "k_ddim.hip", "k_update.hip", "grad.hip",
+SOURCES = ["k_plan.hip", "k_plan_bf16.hip", "k_observe.hip", "k_search.hip", "k_nce.hip", "k_nce_grad.hip", "k_nce_pair.hip", "k_nce_pair_products.hip", "k_ddim.hip", "k_update.hip", "grad.hip",
            "resample_large.hip", "abi.hip"]
 ARCH = os.environ.get("VOILA_OFFLOAD_ARCH", "gfx950")
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", "-Xclang", "-target-feature", "-Xclang",
@@ -29,7 +29,7 @@ FLAGS = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", "-Xclang", "-target-
 # two; the binary32 plan kernel, in k_plan.hip, and the contrastive scores
 # kernels are not faster in that form).
 VGPR_FORM = ["-mllvm", "-amdgpu-mfma-vgpr-form"]
-EXTRA = {"k_plan_bf16.hip": VGPR_FORM, "k_observe.hip": VGPR_FORM}
+EXTRA = {"k_plan_bf16.hip": VGPR_FORM, "k_observe.hip": VGPR_FORM, "k_nce_pair.hip": VGPR_FORM}
 
 
 def _jobs():

@@ -187,15 +187,22 @@ std::vector<char> pack_net(const HostNet& n, int dt, int in_slots_per_group, con
 // action are folded into per-row biases), the hidden->hidden layers, then the
 // transposed hidden->hidden layers from the last to the first (the products
 // W_l^T delta_l of the reverse sweep), padded to whole stream chunks.
-std::vector<char> pack_nce_wide(const HostNet& n, int dt, int in_slots_per_group, const SlotMap& map) {
+// With pass_tiles > 0 every layer is stored pass by pass (pass_tiles output
+// tiles, all k-steps of them) and the stream is padded to the rollout kernel's
+// chunks; with 0 layer by layer, k-step by k-step.
+std::vector<char> pack_nce_wide(const HostNet& n, int dt, int in_slots_per_group, const SlotMap& map,
+                                int pass_tiles) {
     const int W = n.width(), HT = W / 32, NHID = n.n_layers - 1, KP = kper(dt);
     const int esz = dt == DT_F32 ? 4 : 2;
     const size_t fb = (size_t)64 * KP * esz;
     const int IN_KS = in_slots_per_group / KP, HID_KS = 16 * HT / KP;
     const size_t nf0 = (size_t)IN_KS * HT, nfh = (size_t)HID_KS * HT;
     const size_t nfr = nf0 + 2 * (size_t)(NHID - 1) * nfh;
-    const size_t fpc = VOILA_STREAM_CHB / fb;
+    const size_t fpc = (pass_tiles ? VOILA_PLAN_STREAM_CHB : VOILA_STREAM_CHB) / fb;
     std::vector<char> blob((nfr + fpc - 1) / fpc * fpc * fb, 0);
+    auto at = [&](int ks, int c, int t) {  // fragment (c, t) of a layer of ks k-steps
+        return pass_tiles ? (size_t)(t / pass_tiles * ks + c) * pass_tiles + t % pass_tiles : (size_t)c * HT + t;
+    };
     auto put = [&](size_t frag, int lane, int j, float v) {
         char* p = blob.data() + ((frag * 64 + lane) * KP + j) * esz;
         if (dt == DT_F32) {
@@ -211,14 +218,14 @@ std::vector<char> pack_nce_wide(const HostNet& n, int dt, int in_slots_per_group
             for (int lane = 0; lane < 64; ++lane)
                 for (int j = 0; j < KP; ++j) {
                     int col = map(c * KP + j, lane / 32);
-                    put((size_t)c * HT + t, lane, j, col >= 0 ? n.w(0, 32 * t + lane % 32, col) : 0.0f);
+                    put(at(IN_KS, c, t), lane, j, col >= 0 ? n.w(0, 32 * t + lane % 32, col) : 0.0f);
                 }
     for (int l = 1; l <= NHID - 1; ++l)
         for (int c = 0; c < HID_KS; ++c)
             for (int t = 0; t < HT; ++t)
                 for (int lane = 0; lane < 64; ++lane)
                     for (int j = 0; j < KP; ++j)
-                        put(nf0 + (size_t)(l - 1) * nfh + (size_t)c * HT + t, lane, j,
+                        put(nf0 + (size_t)(l - 1) * nfh + at(HID_KS, c, t), lane, j,
                             n.w(l, 32 * t + lane % 32, hidden_in(c * KP + j, lane / 32)));
     for (int k = 0; k < NHID - 1; ++k) {
         const int l = NHID - 1 - k;  // W_{l+1}^T maps the adjoint of h_{l+1} to h_l
@@ -226,7 +233,7 @@ std::vector<char> pack_nce_wide(const HostNet& n, int dt, int in_slots_per_group
             for (int t = 0; t < HT; ++t)
                 for (int lane = 0; lane < 64; ++lane)
                     for (int j = 0; j < KP; ++j)
-                        put(nf0 + (size_t)(NHID - 1 + k) * nfh + (size_t)c * HT + t, lane, j,
+                        put(nf0 + (size_t)(NHID - 1 + k) * nfh + at(HID_KS, c, t), lane, j,
                             n.w(l, hidden_in(c * KP + j, lane / 32), 32 * t + lane % 32));
     }
     return blob;
@@ -326,7 +333,7 @@ struct voila_model_s {
     const float* lik_w3 = nullptr;   // [width] output-layer weights of the likelihood network
     int nce_grad_bpc = 1, n_lik_params = 0;
     // the same derivative for likelihood networks evaluated layer by layer
-    bool has_nce_wide = false;
+    bool has_nce_wide = false, has_nce_pair = false;  // pair: the bfloat16 form, two units per wave
     const char* nce_wide_stream = nullptr;  // first layer, hidden layers, transposed hidden layers
     const float* nce_wide_bh = nullptr;     // [n_hidden - 1][width]
     const float* nce_wide_wout = nullptr;   // [width] (bfloat16 values for bfloat16 models)
@@ -522,7 +529,8 @@ voila_status_t voila_model_create(const voila_model_desc_t* desc, int32_t device
     m->has_nce_wide = L.present() && !m->lik_split && nce_wide_supported(shape);
     if (m->has_nce_wide) {
         SlotMap mo{m->d_o, 0, 0, 0, 0, m->d_s + aw};
-        blobs.push_back(pack_nce_wide(L, dt, nce_in_slots(shape, dt), mo));
+        blobs.push_back(pack_nce_wide(L, dt, nce_in_slots(shape, dt), mo,
+                                      nce_pair_supported(shape, dt) ? nce_pair_pass_tiles() : 0));
         if (m->n_lik_params == 0)
             for (int l = 0; l < L.n_layers; ++l) m->n_lik_params += L.dims[l + 1] * L.dims[l] + L.dims[l + 1];
     } else {
@@ -641,9 +649,10 @@ voila_status_t voila_model_create(const voila_model_desc_t* desc, int32_t device
     m->pw_bpc = pw_lik_blocks_per_cu(shape, dt);
     m->nce_bpc = nce_scores_blocks_per_cu(shape, dt);
     if (m->has_nce_grad) m->nce_grad_bpc = nce_grad_blocks_per_cu(shape, nce_grad_lds_bytes(m));
-    if (m->has_nce_wide) {
-        m->nce_wide_bpc = nce_wide_bwd_blocks_per_cu(dt);
-        m->nce_wgrad_bpc = nce_wide_wgrad_blocks_per_cu(dt);
+    m->has_nce_pair = m->has_nce_wide && nce_pair_supported(shape, dt);
+    if (m->has_nce_wide && !m->has_nce_pair) {
+        m->nce_wide_bpc = nce_wide_bwd_blocks_per_cu();
+        m->nce_wgrad_bpc = nce_wide_wgrad_blocks_per_cu();
     }
     *out = m;
     return VOILA_OK;
@@ -1504,16 +1513,58 @@ struct NceGradWs {
     // layered networks: activation arrays of one chunk of units, per-workgroup partials
     void* act;
     long uc;
+    // bfloat16 form: the mini-batch's operands, partials and blocks of the three layers
+    char* batch;
+    float* layer_part[3];
+    int layer_blocks[3];
     size_t bytes;
 };
 // Units (32 pairs each) held by one chunk of the layered derivative's arrays
 // at most, and the array bytes per unit.
-long nce_wide_unit_cap(const voila_model_s* m) { return m->dt == DT_F32 ? (1L << 14) : (1L << 15); }
+constexpr long kNceWideUnitCap = 1L << 14;
 size_t nce_wide_unit_bytes(const voila_model_s* m) {
-    return (2 * (size_t)m->n_hidden - 1) * m->width * 32 * (m->dt == DT_F32 ? 4 : 2);
+    return (2 * (size_t)m->n_hidden - 1) * m->width * 32 * 4;
 }
 // uc = 0: as many units per chunk as the workspace of ws_bytes holds (the
 // default workspace holds min(all units, the cap)).
+// The bfloat16 form takes pairs of units: stored are 49 KB per unit, in chunks
+// of at most 49,152 units (2.4 GB; a chunk ends in a partly filled grid and in
+// 54 MB of partial sums added up, about 40 us beside 1 ms of a full chunk).
+constexpr long kNcePairUnitCap = 49152;
+NceGradWs carve_nce_pair(NceGradWs w, char* base, size_t off, const voila_model_s* m, int B, size_t ws_bytes) {
+    const int jpairs = ((B + 31) / 32 + 1) / 2;
+    const long units = 2L * B * jpairs;
+    auto take = [&](size_t bytes) {
+        char* p = base + off;
+        off = align_up(off + bytes, 256);
+        return p;
+    };
+    w.batch = take(nce_pair_batch_bytes(B, jpairs));
+    w.blocks = (int)std::min<long>(m->cus, (units / 2 + 3) / 4);
+    w.wpart = reinterpret_cast<float*>(take((size_t)w.blocks * (m->width + 1) * 4));
+    // blocks of the products: one per CU, fewer when a block would have under
+    // 16 units (its 256 KB of partial sums then cost more than its products);
+    // the first layer's products are a quarter of the others', its operands
+    // as many bytes
+    const long nb = std::max<long>(8, std::min<long>(m->cus, units / 16));
+    w.layer_blocks[2] = (int)(nb / 4);
+    w.layer_blocks[0] = (int)((nb - nb / 4) / 2);
+    w.layer_blocks[1] = (int)(nb - nb / 4) - w.layer_blocks[0];
+    const size_t W = m->width, d_in = (size_t)m->d_s + m->action_width() + m->d_o;
+    for (int l = 0; l < 3; ++l)
+        w.layer_part[l] = reinterpret_cast<float*>(take((size_t)w.layer_blocks[l] * ((l == 2 ? d_in : W) * W + W) * 4));
+    long uc = std::min(units, kNcePairUnitCap);
+    const size_t per = nce_pair_unit_bytes();
+    if (ws_bytes > off) {
+        const long fit = (long)((ws_bytes - off) / per) - 2;  // two units past the end are written to as well
+        uc = std::min(uc, std::max(fit, 0L));
+    }
+    w.uc = std::max(2L, uc / 2 * 2);
+    w.act = base + off;
+    off = align_up(off + (size_t)(w.uc + 2) * per, 256);
+    w.bytes = off;
+    return w;
+}
 NceGradWs carve_nce_grad(char* base, voila_model_t m, int B, size_t ws_bytes = 0) {
     NceGradWs w{};
     w.nce = base;
@@ -1521,6 +1572,7 @@ NceGradWs carve_nce_grad(char* base, voila_model_t m, int B, size_t ws_bytes = 0
     size_t off = align_up(w.nce_bytes, 256);
     w.G = reinterpret_cast<float*>(base + off);
     off = align_up(off + (size_t)B * B * 4, 256);
+    if (m->has_nce_pair) return carve_nce_pair(w, base, off, m, B, ws_bytes);
     const long units = (long)B * ((B + 31) / 32);
     if (m->has_nce_wide) {
         w.blocks = m->cus * m->nce_wgrad_bpc;
@@ -1532,7 +1584,7 @@ NceGradWs carve_nce_grad(char* base, voila_model_t m, int B, size_t ws_bytes = 0
     w.wpart = reinterpret_cast<float*>(base + off);
     off = align_up(off + (size_t)w.blocks * m->n_lik_params * 4, 256);
     if (m->has_nce_wide) {
-        long uc = units < nce_wide_unit_cap(m) ? units : nce_wide_unit_cap(m);
+        long uc = std::min(units, kNceWideUnitCap);
         if (ws_bytes > off) {
             const long fit = (long)((ws_bytes - off) / nce_wide_unit_bytes(m));
             uc = fit < uc ? fit : uc;
@@ -1571,11 +1623,57 @@ voila_status_t voila_info_nce_grad(voila_model_t m, const float* d_states, const
     if (!guard.ok) return fail(VOILA_ERR_DEVICE, "hipSetDevice failed");
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     NceWs nw = carve_nce(reinterpret_cast<char*>(w.nce), m, B);
+    if (m->has_nce_pair) {
+        NcePairParams p{};
+        p.stream = m->nce_wide_stream;
+        p.bh = m->nce_wide_bh;
+        p.w_out = m->nce_wide_wout;
+        p.b0 = nw.b0;
+        p.grad = w.G;
+        p.states = d_states;
+        p.actions = d_actions;
+        p.B = B;
+        p.jpairs = ((B + 31) / 32 + 1) / 2;
+        p.n_actions = m->n_actions;
+        p.d_a = m->d_a;
+        p.d_s = m->d_s;
+        p.uc = w.uc;
+        p.part = w.wpart;
+        for (int l = 0; l < 3; ++l) {
+            p.wpart[l] = w.layer_part[l];
+            p.wb[l] = w.layer_blocks[l];
+        }
+        nce_pair_carve(p, reinterpret_cast<char*>(w.act), w.batch);
+        VOILA_CHECK_HIP(launch_nce_pair_prep(p, d_obs, s));
+        const long pairs = (long)B * p.jpairs;
+        for (long u0 = 0; u0 < pairs; u0 += w.uc / 2) {
+            p.u0 = u0;
+            p.u1 = std::min(u0 + w.uc / 2, pairs);
+            p.accumulate = u0 > 0 ? 1 : 0;
+            // the first chunk writes every block's partial, empty ones included
+            VOILA_CHECK_HIP(launch_nce_pair_bwd(p, w.blocks, s));
+            VOILA_CHECK_HIP(launch_nce_pair_wgrad(p, s));
+        }
+        const int W = m->width, d_in = m->d_s + m->action_width() + m->d_o;
+        const float* parts[4] = {p.wpart[2], p.wpart[1], p.wpart[0], p.part};
+        const int n[4] = {W * d_in + W, W * W + W, W * W + W, W + 1};
+        const int rows[4] = {p.wb[2], p.wb[1], p.wb[0], w.blocks};
+        float* dst = d_param_grad_out;
+        for (int l = 0; l < 4; ++l) {
+            GradReduceParams r{};
+            r.wpart = parts[l];
+            r.grad_params = dst;
+            r.n_params = n[l];
+            r.n_waves = rows[l];
+            VOILA_CHECK_HIP(launch_grad_reduce(r, s));
+            dst += n[l];
+        }
+        return VOILA_OK;
+    }
     if (m->has_nce_wide) {
         // chunks of units: forward and reverse sweep of every pair, then the
         // split-K products into per-workgroup partial sums
         const long units = (long)B * ((B + 31) / 32);
-        const int upc = m->dt == DT_F32 ? 1 : 2;  // units per staged chunk of the product kernel
         for (long u0 = 0; u0 < units; u0 += w.uc) {
             const long u1 = u0 + w.uc < units ? u0 + w.uc : units;
             NceWideParams a{};
@@ -1592,14 +1690,13 @@ voila_status_t voila_info_nce_grad(voila_model_t m, const float* d_states, const
             a.B = B;
             const long want = (u1 - u0 + 3) / 4;
             const long cap = (long)m->cus * m->nce_wide_bpc;
-            VOILA_CHECK_HIP(launch_nce_wide_bwd(m->shape, m->dt, a, (int)(want < cap ? want : cap), s));
+            VOILA_CHECK_HIP(launch_nce_wide_bwd(m->shape, a, (int)(want < cap ? want : cap), s));
             NceWgradParams b{};
             b.act = w.act;
             b.uc = w.uc;
             b.u0 = u0;
             b.n_units = u1 - u0;
-            const long per = (b.n_units + w.blocks - 1) / w.blocks;
-            b.per_split = (per + upc - 1) / upc * upc;
+            b.per_split = (b.n_units + w.blocks - 1) / w.blocks;
             b.grad = w.G;
             b.w_out = m->nce_wide_wout;
             b.states = d_states;
@@ -1614,7 +1711,7 @@ voila_status_t voila_info_nce_grad(voila_model_t m, const float* d_states, const
             b.part = w.wpart;
             b.n_params = m->n_lik_params;
             b.accumulate = u0 > 0 ? 1 : 0;
-            VOILA_CHECK_HIP(launch_nce_wide_wgrad(m->shape, m->dt, b, w.blocks, s));
+            VOILA_CHECK_HIP(launch_nce_wide_wgrad(m->shape, b, w.blocks, s));
         }
         GradReduceParams r{};
         r.wpart = w.wpart;

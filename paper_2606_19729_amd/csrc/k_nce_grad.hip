@@ -1,6 +1,7 @@
 // k_nce_grad.hip -- derivative of the contrastive (InfoNCE) objective with
-// respect to the parameters of a likelihood network evaluated layer by layer
-// (hidden width 256), in two stages per chunk of pairs:
+// respect to the parameters of a binary32 likelihood network evaluated layer by
+// layer (hidden width 256; the bfloat16 form is in nce_pair.hpp), in two stages
+// per chunk of pairs:
 //   1. nce_wide_bwd_kernel: every pair (i, j) runs the network forward on
 //      [s'_i, a_i, o_j] and the reverse sweep with weight G_ij (Eq. 6), and
 //      stores the hidden activations h_1..h_L and the hidden adjoints
@@ -24,7 +25,6 @@ template <class N> struct BwdStreamShape {
 
 template <int DT> struct Elem;
 template <> struct Elem<DT_F32> { typedef float type; };
-template <> struct Elem<DT_BF16> { typedef __bf16 type; };
 
 // Binary32 values as B operands without the ReLU (adjoints may be negative).
 template <int HT>
@@ -32,23 +32,9 @@ __device__ __forceinline__ void set_plain(Act<DT_F32, HT>& a, const f32x16 (&acc
 #pragma unroll
     for (int t = 0; t < HT; ++t) a.v[t] = acc[t];
 }
-template <int HT>
-__device__ __forceinline__ void set_plain(Act<DT_BF16, HT>& a, const f32x16 (&acc)[HT]) {
-#pragma unroll
-    for (int t = 0; t < HT; ++t)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            bf16x8 r;
-#pragma unroll
-            for (int q = 0; q < 8; ++q) r[q] = (__bf16)acc[t][8 * h + q];
-            a.v[2 * t + h] = r;
-        }
-}
 // Element (t, i) of an operand set (the value the matrix cores consume).
 template <int HT>
 __device__ __forceinline__ float act_at(const Act<DT_F32, HT>& a, int t, int i) { return a.v[t][i]; }
-template <int HT>
-__device__ __forceinline__ __bf16 act_at(const Act<DT_BF16, HT>& a, int t, int i) { return a.v[2 * t + (i >> 3)][i & 7]; }
 
 template <int DT, int D_O, int WIDTH, int NHID>
 __global__ __launch_bounds__(256) void nce_wide_bwd_kernel(NceWideParams p) {
@@ -61,7 +47,7 @@ __global__ __launch_bounds__(256) void nce_wide_bwd_kernel(NceWideParams p) {
 #ifndef VOILA_NCE_BWD_DEPTH
 #define VOILA_NCE_BWD_DEPTH 4
 #endif
-    constexpr int DEPTH = DT == DT_F32 ? VOILA_NCE_BWD_DEPTH : kPfDepth;
+    constexpr int DEPTH = VOILA_NCE_BWD_DEPTH;
     static_assert(HT % 2 == 0, "two tiles of ReLU bits per mask word");
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int lane = threadIdx.x & 63, g = lane >> 5, col = lane & 31;
@@ -189,14 +175,8 @@ template <int DT> struct WgCfg;
 template <> struct WgCfg<DT_F32> {
     static constexpr int KC = 32, PAD = 1, VEC = 4;  // pairs per staged chunk, row padding, elements per load
 };
-template <> struct WgCfg<DT_BF16> {
-    static constexpr int KC = 64, PAD = 8, VEC = 8;
-};
-
 template <int DT> struct WgVec;
 template <> struct WgVec<DT_F32> { typedef f32x4 type; };
-template <> struct WgVec<DT_BF16> { typedef bf16x8 type; };
-
 // VEC consecutive elements of a feature-major row (zero past the chunk's
 // last pair).
 template <int DT>
@@ -213,12 +193,8 @@ __device__ __forceinline__ typename WgVec<DT>::type load_vec(const typename Elem
 // Writes VEC operand elements into an LDS row.
 template <int DT>
 __device__ __forceinline__ void store_vec(typename Elem<DT>::type* dst, const typename WgVec<DT>::type& v) {
-    if constexpr (DT == DT_F32) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) dst[q] = v[q];  // rows are padded to an odd stride: no vector store
-    } else {
-        *reinterpret_cast<bf16x8*>(dst) = v;
-    }
+    for (int q = 0; q < 4; ++q) dst[q] = v[q];  // rows are padded to an odd stride: no vector store
 }
 
 template <int DT> struct WgFrag;
@@ -229,15 +205,6 @@ template <> struct WgFrag<DT_F32> {
     }
     static constexpr int KSTEPS = WgCfg<DT_F32>::KC / 2;
 };
-template <> struct WgFrag<DT_BF16> {
-    // pairs 16 s + 8 (lane / 32) .. + 7 of row r
-    __device__ static __forceinline__ bf16x8 load(const __bf16* t, int row, int s, int lane) {
-        return *reinterpret_cast<const bf16x8*>(t + row * (WgCfg<DT_BF16>::KC + WgCfg<DT_BF16>::PAD) + 16 * s +
-                                                8 * (lane >> 5));
-    }
-    static constexpr int KSTEPS = WgCfg<DT_BF16>::KC / 16;
-};
-
 // One weight derivative over this workgroup's units [v0, v1) of the chunk:
 // C[m][n] = sum_p A[m][p] B[n][p] with A the layer's output adjoints (formed
 // from the last hidden layer, G and w_out when FORMED) and B its inputs (the
@@ -464,64 +431,40 @@ __global__ __launch_bounds__(256) void nce_wide_wgrad_kernel(NceWgradParams p) {
 // launchers (the realistic shape: width 256, three hidden layers, d_o = 32)
 // ---------------------------------------------------------------------------
 namespace {
-template <int DT> constexpr size_t bwd_lds() {
-    typedef Net<DT, 256, 3, in_slots(DT, 32, 0, 0), 8> NT;
+constexpr size_t bwd_lds() {
+    typedef Net<DT_F32, 256, 3, in_slots(DT_F32, 32, 0, 0), 8> NT;
     return (size_t)StreamSrc<BwdStreamShape<NT>>::LDS_BYTES;
 }
-template <int DT> constexpr size_t wgrad_lds() {
-    return (size_t)2 * 256 * (WgCfg<DT>::KC + WgCfg<DT>::PAD) * (DT == DT_F32 ? 4 : 2);
-}
+constexpr size_t wgrad_lds() { return (size_t)2 * 256 * (WgCfg<DT_F32>::KC + WgCfg<DT_F32>::PAD) * 4; }
 }  // namespace
 
 bool nce_wide_supported(int shape) { return shape == 1; }
 
-size_t nce_wide_bwd_lds(int dt) {
+size_t nce_wide_bwd_lds() {
     // stream buffers, then hidden biases, output weights and one bias row per wave
-    const size_t s = dt == DT_F32 ? bwd_lds<DT_F32>() : bwd_lds<DT_BF16>();
-    return s + (size_t)(2 + 1 + kWavesPerBlock) * 256 * 4;
+    return bwd_lds() + (size_t)(2 + 1 + kWavesPerBlock) * 256 * 4;
 }
 
-hipError_t launch_nce_wide_bwd(int shape, int dt, const NceWideParams& p0, int blocks, hipStream_t s) {
+hipError_t launch_nce_wide_bwd(int shape, const NceWideParams& p0, int blocks, hipStream_t s) {
     if (shape != 1) return hipErrorInvalidValue;
     NceWideParams p = p0;
-    const size_t lds = nce_wide_bwd_lds(dt);
-    p.lds_bias = (uint32_t)(dt == DT_F32 ? bwd_lds<DT_F32>() : bwd_lds<DT_BF16>());
-    if (dt == DT_F32) {
-        (void)hipFuncSetAttribute((const void*)nce_wide_bwd_kernel<DT_F32, 32, 256, 3>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        hipLaunchKernelGGL((nce_wide_bwd_kernel<DT_F32, 32, 256, 3>), blocks, 256, lds, s, p);
-    } else {
-        (void)hipFuncSetAttribute((const void*)nce_wide_bwd_kernel<DT_BF16, 32, 256, 3>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        hipLaunchKernelGGL((nce_wide_bwd_kernel<DT_BF16, 32, 256, 3>), blocks, 256, lds, s, p);
-    }
+    const size_t lds = nce_wide_bwd_lds();
+    p.lds_bias = (uint32_t)bwd_lds();
+    (void)hipFuncSetAttribute((const void*)nce_wide_bwd_kernel<DT_F32, 32, 256, 3>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL((nce_wide_bwd_kernel<DT_F32, 32, 256, 3>), blocks, 256, lds, s, p);
     return hipGetLastError();
 }
 
-hipError_t launch_nce_wide_wgrad(int shape, int dt, const NceWgradParams& p, int blocks, hipStream_t s) {
+hipError_t launch_nce_wide_wgrad(int shape, const NceWgradParams& p, int blocks, hipStream_t s) {
     if (shape != 1) return hipErrorInvalidValue;
-    if (dt == DT_F32) {
-        const size_t lds = wgrad_lds<DT_F32>();
-        (void)hipFuncSetAttribute((const void*)nce_wide_wgrad_kernel<DT_F32, 256, 3, 64>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        hipLaunchKernelGGL((nce_wide_wgrad_kernel<DT_F32, 256, 3, 64>), blocks, 256, lds, s, p);
-    } else {
-        const size_t lds = wgrad_lds<DT_BF16>();
-        (void)hipFuncSetAttribute((const void*)nce_wide_wgrad_kernel<DT_BF16, 256, 3, 64>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        hipLaunchKernelGGL((nce_wide_wgrad_kernel<DT_BF16, 256, 3, 64>), blocks, 256, lds, s, p);
-    }
+    (void)hipFuncSetAttribute((const void*)nce_wide_wgrad_kernel<DT_F32, 256, 3, 64>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)wgrad_lds());
+    hipLaunchKernelGGL((nce_wide_wgrad_kernel<DT_F32, 256, 3, 64>), blocks, 256, wgrad_lds(), s, p);
     return hipGetLastError();
 }
 
-int nce_wide_bwd_blocks_per_cu(int dt) {
-    return dt == DT_F32 ? occupancy(nce_wide_bwd_kernel<DT_F32, 32, 256, 3>, nce_wide_bwd_lds(DT_F32))
-                        : occupancy(nce_wide_bwd_kernel<DT_BF16, 32, 256, 3>, nce_wide_bwd_lds(DT_BF16));
-}
-
-int nce_wide_wgrad_blocks_per_cu(int dt) {
-    return dt == DT_F32 ? occupancy(nce_wide_wgrad_kernel<DT_F32, 256, 3, 64>, wgrad_lds<DT_F32>())
-                        : occupancy(nce_wide_wgrad_kernel<DT_BF16, 256, 3, 64>, wgrad_lds<DT_BF16>());
-}
+int nce_wide_bwd_blocks_per_cu() { return occupancy(nce_wide_bwd_kernel<DT_F32, 32, 256, 3>, nce_wide_bwd_lds()); }
+int nce_wide_wgrad_blocks_per_cu() { return occupancy(nce_wide_wgrad_kernel<DT_F32, 256, 3, 64>, wgrad_lds()); }
 
 }  // namespace voila

@@ -436,13 +436,13 @@ int observe_blocks_per_cu(int shape, int dt);
 // Whether a shape's kernels stage the packed network in LDS.
 bool weights_in_lds(int shape);
 
-// Derivative of the contrastive objective for likelihood networks evaluated
-// layer by layer: stage 1 (forward and reverse sweep of every pair of a
+// Derivative of the contrastive objective for binary32 likelihood networks
+// evaluated layer by layer: stage 1 (forward and reverse sweep of every pair of a
 // chunk, activations and adjoints stored) and stage 2 (split-K products).
 struct NceWideParams {
     const char* stream;    // fragments: first layer (observation inputs), hidden layers, transposed hidden layers
     const float* bh;       // [NHID - 1][width] hidden biases
-    const float* w_out;    // [width] output-layer weights (bfloat16 values for bfloat16 models)
+    const float* w_out;    // [width] output-layer weights
     const float* b0;       // [B][width] first-layer bias rows with s'_i and a_i folded in
     const float* obs;      // [B][d_o]
     const float* grad;     // [B][B] d loss / d l_ij
@@ -468,11 +468,44 @@ struct NceWgradParams {
     int accumulate;        // 0: the first chunk writes the partials, 1: later chunks add
 };
 bool nce_wide_supported(int shape);
-size_t nce_wide_bwd_lds(int dt);
-hipError_t launch_nce_wide_bwd(int shape, int dt, const NceWideParams& p, int blocks, hipStream_t s);
-hipError_t launch_nce_wide_wgrad(int shape, int dt, const NceWgradParams& p, int blocks, hipStream_t s);
-int nce_wide_bwd_blocks_per_cu(int dt);
-int nce_wide_wgrad_blocks_per_cu(int dt);
+size_t nce_wide_bwd_lds();
+hipError_t launch_nce_wide_bwd(int shape, const NceWideParams& p, int blocks, hipStream_t s);
+hipError_t launch_nce_wide_wgrad(int shape, const NceWgradParams& p, int blocks, hipStream_t s);
+int nce_wide_bwd_blocks_per_cu();
+int nce_wide_wgrad_blocks_per_cu();
+
+// The same derivative for the bfloat16 network, two units of 32 pairs per wave
+// (k_nce_pair.hip).  Pair-unit u: row u / jpairs, units 2 (u % jpairs) and the next.
+struct NcePairParams {
+    const char* stream;    // fragments in pass order: first layer (observations), hidden, transposed hidden layers
+    const float* bh;       // [2][width] hidden biases
+    const float* w_out;    // [width] output-layer weights (bfloat16 values)
+    const float* b0;       // [B][width] first-layer bias rows with s'_i and a_i folded in
+    const float* grad;     // [B][B] d loss / d l_ij
+    char* obs_n;           // [2 jpairs][2][64][8] observations as first-layer operands
+    char* obs_t;           // [2 jpairs][2][64][8] observations as operands of the products over pairs
+    char* row_ops;         // [B][64] [s'_i, a_i, 1] as bfloat16 pairs, by lane column
+    char* act;             // [3][uc + 2][16 KB] h_2, delta_2, delta_1, pairs along the registers
+    char* sgn;             // [uc + 2][1 KB] sign pattern of h_3
+    float* gt;             // [uc + 2][32] G of the unit's pairs (zero past B)
+    const float* states;   // [B][d_s]
+    const void* actions;   // int32 [B] or float [B][d_a]
+    long uc;               // unit capacity of the arrays (even)
+    long u0, u1;           // pair-units of the chunk
+    int B, jpairs, n_actions, d_a, d_s;
+    float* part;           // [bwd blocks][width + 1] output-layer partials
+    float* wpart[3];       // partials of layers 3, 2 ([wb][width^2 + width]) and 1 ([wb][width d_in + width])
+    int wb[3];             // blocks of layers 3, 2, 1
+    int accumulate;        // 0: the first chunk writes the partials, 1: later chunks add
+};
+bool nce_pair_supported(int shape, int dt);
+int nce_pair_pass_tiles();               // output tiles per pass of the fragment stream
+size_t nce_pair_unit_bytes();            // stored per unit
+size_t nce_pair_batch_bytes(int B, int jpairs);  // operands of the mini-batch
+void nce_pair_carve(NcePairParams& p, char* act, char* batch);
+hipError_t launch_nce_pair_prep(const NcePairParams& p, const float* obs, hipStream_t s);
+hipError_t launch_nce_pair_bwd(const NcePairParams& p, int blocks, hipStream_t s);
+hipError_t launch_nce_pair_wgrad(const NcePairParams& p, hipStream_t s);
 
 constexpr int kWavesPerBlock = 4;
 

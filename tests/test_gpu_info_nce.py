@@ -392,3 +392,30 @@ def test_realistic_param_grad_bench_size_properties(V, compute):
     d = run_dev(V, m, S, A, O)
     assert loss == pytest.approx(float(d["loss"][0]), rel=1e-12)
     assert np.array_equal(run_grad_ws(V, m, S, A, O)[1], g)
+
+
+@pytest.mark.parametrize("B", [1, 31, 33, 64, 65, 130])
+def test_realistic_param_grad_bf16_at_ragged_batches(V, B):
+    # one unit, a padded second unit, an odd number of units per row, several
+    # pair-units per row: against the bfloat16 emulation at the bound of
+    # test_realistic_param_grad_bf16_against_emulation, and a workspace that
+    # holds two units per chunk (the partial sums accumulated over up to 325
+    # chunks) agrees to the rounding of binary32 sums
+    w = workloads.realistic(seed=91, N=512, K=1, H=1)
+    S, A, O = workloads.nce_batch(w, B, seed=25)
+    m = V.Model(w.model, compute="bf16")
+    print(f"info_nce grad realistic bf16 B={B}", flush=True)
+    loss, g = run_grad_ws(V, m, S, A, O)
+    if B == 1:
+        assert loss == 0.0 and np.all(g == 0.0)
+        return
+    _, g_em = oracle.info_nce_param_grad(w.model, S, A, O, bf16=True)
+    scale = float(np.max(np.abs(g_em)))
+    err = float(np.max(np.abs(g - g_em))) / scale
+    full = int(V.lib.voila_info_nce_grad_workspace_size(m.handle, B))
+    unit = 3 * 256 * 32 * 2 + 1024 + 128
+    units = 2 * B * ((((B + 31) // 32) + 1) // 2)
+    _, g2 = run_grad_ws(V, m, S, A, O, ws_bytes=full - (units - 2) * unit)
+    print(f"  grad err vs emulation {err:.2e}; vs {units // 2} chunks {np.max(np.abs(g - g2)) / scale:.2e}", flush=True)
+    assert err <= BF16_PARAM_GRAD_BOUND
+    assert np.max(np.abs(g - g2)) <= 1e-5 * scale
