@@ -1140,14 +1140,24 @@ __device__ __forceinline__ void run_net_flat(Src& src, const NetPtrs& P, const f
 // sample tiles, so each weight fragment read from L2 serves ST tiles.  The
 // activations of sample tile st live at lds + st * ACT; the output layer's
 // per-wave partials reuse that space.  bin(c, st) is the first-layer B
-// operand of sample tile st at k-step c.  The outputs go to sink(st, t, i,
-// v): value i of output tile t of sample tile st; with OWN false every wave
-// receives every sample tile's, with OWN true wave w < ST only its own
-// sample tile's (st = w) and the other waves none.  D k-steps of weight
-// fragments are in flight.
-template <class N, int ST, int NW, int D, bool OWN, class BIN, class SINK>
-__device__ __forceinline__ void run_net_split_core(const NetPtrs& P, const float* b0, BIN&& bin, SINK&& sink,
-                                                   int lane, int g, int wave, char* lds) {
+// operand of sample tile st at k-step c, ready() is called once the first
+// weights and biases are on their way and before the first bin.  The outputs
+// go to sink(st, t, i, v): value i of output tile t of sample tile st; with OWN
+// false every wave receives every sample tile's, with OWN true wave w < ST
+// only its own sample tile's (st = w) and the other waves none.
+// What bounds it is the latency of the weight fragments, so the k-steps of all
+// layers are one sequence with D - 1 of them in flight: the next layer's first
+// fragments (and its biases, once the accumulators are stored) load across the
+// layer boundary's barriers, activations are read a k-step ahead, and the
+// compiler orders loads and products freely within a k-step (groups of loads
+// before products: 106 instead of 92 us for one 5 x 1024 evaluation of 64
+// samples on an otherwise idle chip, 55 at the matrix cores' rate; deeper
+// rings gained nothing in that order, and 12 % in this).  5 x 1024 teacher,
+// 20,000 samples x 50 steps 13.0 -> 10.6 ms; 4 x 1024 target-finding rollouts,
+// 2 M steps, 14.9 -> 12.3 ms.
+template <class N, int ST, int NW, int D, bool OWN, class READY, class BIN, class SINK>
+__device__ __forceinline__ void run_net_split_core(const NetPtrs& P, const float* b0, READY&& ready, BIN&& bin,
+                                                   SINK&& sink, int lane, int g, int wave, char* lds) {
     static_assert(N::HT % NW == 0 && N::HID_KS % NW == 0 && N::CT == N::HT, "split needs a layered network");
     static_assert(!OWN || ST <= NW, "every sample tile needs an owner wave");
     constexpr int TPW = N::HT / NW, KQ = N::HID_KS / NW;
@@ -1155,36 +1165,79 @@ __device__ __forceinline__ void run_net_split_core(const NetPtrs& P, const float
     static_assert(ST * NW * 16 * 64 * 4 <= ST * ACT, "partials must fit the activation space");
     typedef typename Frag<N::DT>::type FT;
     typedef FragIdx<N> FI;
+    // k-steps of the hidden-producing layers 0 .. NHID - 1 in sequence
+    constexpr int KT = N::IN_KS + (N::NHID - 1) * N::HID_KS;
     const int t0 = wave * TPW;
-    auto kstep = [&](const char* base, int c) { return base + (size_t)c * N::HT * N::FRAG_BYTES + opaque_zero(); };
     // one base register per sample tile's activations, the k-steps as
     // immediate offsets (a folded constant base past 64 KB would need one
     // address register per k-step, which the compiler hoists and spills)
     char* act[ST];
 #pragma unroll
     for (int st = 0; st < ST; ++st) act[st] = lds + st * ACT + opaque_zero();
+    FT ring[D][TPW];
+    // fragments of k-step n of the sequence (the layers' fragments are
+    // consecutive, k-step by k-step), past its end the wave's first ones of the
+    // output layer
+    // (opaque bases: addresses of every k-step would otherwise be formed ahead
+    // of the caller's step loop and spilled)
+    const char* const wbase = P.f0 + (size_t)FI::first(0, t0) * N::FRAG_BYTES + opaque_zero();
+    const char* const obase = P.f0 + (size_t)(FI::out(0) + wave * KQ) * N::FRAG_BYTES + opaque_zero();
+    static_assert(FI::hidden(1, 0, 0) == N::IN_KS * N::HT, "layers follow each other");
+    auto fetch = [&](auto ni) {
+        constexpr int n = decltype(ni)::value;
+        if constexpr (n < KT) {
+            const char* base = wbase + (size_t)n * N::HT * N::FRAG_BYTES + opaque_zero();
+            static_for<TPW>([&](auto ti) {
+                ring[n % D][decltype(ti)::value] = Frag<N::DT>::load(base, decltype(ti)::value, lane);
+            });
+        } else {
+            static_for<TPW>([&](auto ti) {
+                constexpr int o = (n - KT) * TPW + decltype(ti)::value;  // (k-step, tile) o / NO, o % NO
+                if constexpr (o < KQ * N::NO)
+                    ring[n % D][decltype(ti)::value] = Frag<N::DT>::load(
+                        obase + (size_t)(o % N::NO * N::HID_KS + o / N::NO) * N::FRAG_BYTES + opaque_zero(), 0, lane);
+            });
+        }
+    };
     f32x16 acc[ST][TPW];
+    auto biases = [&](const float* b) {
 #pragma unroll
-    for (int st = 0; st < ST; ++st) init_bias<TPW>(acc[st], b0 + 32 * t0 + opaque_zero(), g);
-    {
-        const char* base = P.f0 + (size_t)FI::first(0, t0) * N::FRAG_BYTES + opaque_zero();
-        mfma_layer_multi<N::IN_KS, TPW, ST, D, FT>(
-            acc, [&](int c, int t) { return Frag<N::DT>::load(kstep(base, c), t, lane); }, bin);
-    }
-#pragma unroll
-    for (int st = 0; st < ST; ++st) split_store<N, TPW>(act[st], acc[st], t0, lane);
-    __syncthreads();
-    static_for<N::NHID - 1>([&](auto li) {
-        constexpr int l = decltype(li)::value + 1;
-#pragma unroll
-        for (int st = 0; st < ST; ++st) init_bias<TPW>(acc[st], P.bh + (l - 1) * N::WIDTH + 32 * t0 + opaque_zero(), g);
-        const char* base = P.f0 + (size_t)FI::hidden(l, 0, t0) * N::FRAG_BYTES + opaque_zero();
-        mfma_layer_multi<N::HID_KS, TPW, ST, D, FT>(
-            acc, [&](int c, int t) { return Frag<N::DT>::load(kstep(base, c), t, lane); },
-            [&](int c, int st) { return split_act<N>(act[st], c, lane); });
-        __syncthreads();
+        for (int st = 0; st < ST; ++st) init_bias<TPW>(acc[st], b + 32 * t0 + opaque_zero(), g);
+    };
+    static_for<D - 1>([&](auto ni) { fetch(ni); });
+    biases(b0);
+    ready();
+    static_for<N::NHID>([&](auto li) {
+        constexpr int l = decltype(li)::value, KS = l == 0 ? N::IN_KS : N::HID_KS;
+        constexpr int n0 = l == 0 ? 0 : N::IN_KS + (l - 1) * N::HID_KS;
+        // the activations' operands are read from LDS a k-step ahead too
+        FT in[2][ST];
+        auto operands = [&](auto ci) {
+            constexpr int c = decltype(ci)::value;
+            static_for<ST>([&](auto si) {
+                constexpr int st = decltype(si)::value;
+                if constexpr (l == 0) in[c % 2][st] = bin(c, st);
+                else in[c % 2][st] = split_act<N>(act[st], c, lane);
+            });
+        };
+        operands(std::integral_constant<int, 0>{});
+        static_for<KS>([&](auto ci) {
+            constexpr int c = decltype(ci)::value, n = n0 + c;
+            fetch(std::integral_constant<int, n + D - 1>{});
+            if constexpr (c + 1 < KS) operands(std::integral_constant<int, c + 1>{});
+            static_for<ST>([&](auto si) {
+                constexpr int st = decltype(si)::value;
+                static_for<TPW>([&](auto ti) {
+                    constexpr int t = decltype(ti)::value;
+                    acc[st][t] = mfma(ring[n % D][t], in[c % 2][st], acc[st][t]);
+                });
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        if constexpr (l > 0) __syncthreads();  // every wave has read the activations these overwrite
 #pragma unroll
         for (int st = 0; st < ST; ++st) split_store<N, TPW>(act[st], acc[st], t0, lane);
+        if constexpr (l + 1 < N::NHID) biases(P.bh + l * N::WIDTH);
         __syncthreads();
     });
     // the output layer: each wave multiplies its k-steps for every output
@@ -1199,14 +1252,23 @@ __device__ __forceinline__ void run_net_split_core(const NetPtrs& P, const float
             for (int t = 0; t < N::NO; ++t) part[st][t] = f32x16{};
     }
     {
+        // fragment o of the wave's output k-steps: (k-step, tile) o / NO, o % NO;
+        // the first D - 1 groups of TPW are in the ring
+        constexpr int NF = KQ * N::NO;
         const int k0 = wave * KQ;
-        const char* base = P.f0 + (size_t)(FI::out(0) + k0) * N::FRAG_BYTES + opaque_zero();
-        mfma_layer_multi<KQ, N::NO, ST, D, FT>(
-            part,
-            [&](int c, int t) {
-                return Frag<N::DT>::load(base + (size_t)(t * N::HID_KS + c) * N::FRAG_BYTES + opaque_zero(), 0, lane);
-            },
-            [&](int c, int st) { return split_act<N>(act[st], k0 + c, lane); });
+        static_for<cdiv(NF, TPW)>([&](auto gi) {
+            constexpr int q = decltype(gi)::value;
+            fetch(std::integral_constant<int, KT + q + D - 1>{});
+            static_for<TPW>([&](auto ti) {
+                constexpr int o = q * TPW + decltype(ti)::value;
+                if constexpr (o < NF)
+                    static_for<ST>([&](auto si) {
+                        constexpr int st = decltype(si)::value;
+                        part[st][o % N::NO] = mfma(ring[(KT + q) % D][decltype(ti)::value],
+                                                   split_act<N>(act[st], k0 + o / N::NO, lane), part[st][o % N::NO]);
+                    });
+            });
+        });
     }
     __syncthreads();  // every wave has read the activations the partials overwrite
     float* pl = reinterpret_cast<float*>(lds);
@@ -1244,7 +1306,7 @@ __device__ __forceinline__ void run_net_split_multi(const NetPtrs& P, const floa
                                                     f32x16 (&out)[ST * N::NO], int lane, int g, int wave,
                                                     char* lds) {
     run_net_split_core<N, ST, NW, D, false>(
-        P, b0, [&](int c, int st) { return Slots<N::DT, N::IN_SLOTS>::b(slots[st], c); },
+        P, b0, [] {}, [&](int c, int st) { return Slots<N::DT, N::IN_SLOTS>::b(slots[st], c); },
         [&](int st, int t, int i, float v) { out[st * N::NO + t][i] = v; }, lane, g, wave, lds);
 }
 
@@ -1262,8 +1324,8 @@ __device__ __forceinline__ void split_stage_inputs(char* lds_in, const float (&s
 }
 
 // The split evaluation with the first-layer operands of sample tile st at
-// lds_in + st * SplitIn<N>::BYTES (written, before a barrier, by its owner
-// wave st); wave w < ST receives its own sample tile's output tiles as
+// lds_in + st * SplitIn<N>::BYTES (written before the call by its owner wave
+// st; the barrier is in here); wave w < ST receives its own sample tile's output tiles as
 // out[t][i] (plain scalars: no vector register tuple is rebuilt per value).
 template <class N, int ST, int NW, int D>
 __device__ __forceinline__ void run_net_split_owned(const NetPtrs& P, const float* b0, const char* lds_in,
@@ -1274,7 +1336,7 @@ __device__ __forceinline__ void run_net_split_owned(const NetPtrs& P, const floa
     for (int st = 0; st < ST; ++st)
         in[st] = reinterpret_cast<const FT*>(lds_in + st * SplitIn<N>::BYTES + opaque_zero());
     run_net_split_core<N, ST, NW, D, true>(
-        P, b0, [&](int c, int st) { return in[st][c * 64 + lane]; },
+        P, b0, [] { __syncthreads(); }, [&](int c, int st) { return in[st][c * 64 + lane]; },
         [&](int, int t, int i, float v) { out[t][i] = v; }, lane, g, wave, lds);
 }
 

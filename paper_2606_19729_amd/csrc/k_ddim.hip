@@ -120,7 +120,7 @@ __global__ __launch_bounds__(256) void ddim_kernel(DdimParams p) {
 #define VOILA_DDIM_SPLIT_TILES 2
 #endif
 #ifndef VOILA_DDIM_SPLIT_DEPTH
-#define VOILA_DDIM_SPLIT_DEPTH 2
+#define VOILA_DDIM_SPLIT_DEPTH 4
 #endif
 constexpr int kDdimSplitWaves = VOILA_DDIM_SPLIT_WAVES, kDdimSplitTiles = VOILA_DDIM_SPLIT_TILES,
               kDdimSplitDepth = VOILA_DDIM_SPLIT_DEPTH;

@@ -211,7 +211,7 @@ __global__ __launch_bounds__(256) void observe_kernel(ObserveParams p) {
 // read from L2 serving both tiles.  Wave q forms tile q's inputs, stages
 // them in LDS and writes the tile's observations (observations wider than
 // 32 come in two output tiles).
-constexpr int kObsSplitWaves = 8, kObsSplitTiles = 2, kObsSplitDepth = 2;
+constexpr int kObsSplitWaves = 8, kObsSplitTiles = 2, kObsSplitDepth = 3;
 
 template <int DT, int WIDTH, int NHID>
 constexpr bool obs_split() {
@@ -247,7 +247,6 @@ __global__ __launch_bounds__(64 * kObsSplitWaves) void observe_split_kernel(Obse
             split_stage_inputs<NT>(in_lds + wave * SplitIn<NT>::BYTES, slots, lane);
         }
         const float* b0 = p.b0 + (size_t)(p.b0_stride ? grp : 0) * p.b0_stride;
-        __syncthreads();  // the owners' inputs are in LDS
         float o[NO][16];
         run_net_split_owned<NT, ST, kObsSplitWaves, kObsSplitDepth>(P, b0, in_lds, o, lane, g, wave, smem);
         if (owner) observe_store<D_O, NO, float[16]>(p, w, o, true, g);

@@ -28,7 +28,7 @@ namespace voila {
 #define VOILA_PLAN_SPLIT_TILES 2
 #endif
 #ifndef VOILA_PLAN_SPLIT_DEPTH
-#define VOILA_PLAN_SPLIT_DEPTH 2
+#define VOILA_PLAN_SPLIT_DEPTH 3
 #endif
 constexpr int kPlanSplitWaves = VOILA_PLAN_SPLIT_WAVES, kPlanSplitTiles = VOILA_PLAN_SPLIT_TILES,
               kPlanSplitDepth = VOILA_PLAN_SPLIT_DEPTH;
@@ -150,7 +150,6 @@ __global__ __launch_bounds__(64 * kPlanSplitWaves) void plan_split_kernel(PlanPa
                 }
                 b0 += (size_t)a * p.net.b0_stride;
             }
-            __syncthreads();  // the owners' inputs are in LDS
             float out[NO][16];
             run_net_split_owned<NT, ST, kPlanSplitWaves, kPlanSplitDepth>(P, b0, in_lds, out, lane, g, wave, smem);
             if (owner) {

@@ -231,7 +231,7 @@ __global__ __launch_bounds__(512) void propose_batch_kernel(BatchProposeParams b
 // waves advances two 32-particle tiles, every layer split over the waves
 // (run_net_split_owned); wave q forms tile q's inputs [s, w] (noise as in
 // propose_tile) and writes its proposals s + f_T(s, a, w).
-constexpr int kPropSplitWaves = 8, kPropSplitDepth = 2;
+constexpr int kPropSplitWaves = 8, kPropSplitDepth = 3;
 
 template <int DT, int D_S, int D_W, int WIDTH, int NHID>
 __global__ __launch_bounds__(64 * kPropSplitWaves) void propose_split_kernel(ProposeParams p) {
@@ -273,7 +273,6 @@ __global__ __launch_bounds__(64 * kPropSplitWaves) void propose_split_kernel(Pro
             }
             split_stage_inputs<NT>(in_lds + wave * SplitIn<NT>::BYTES, slots, lane);
         }
-        __syncthreads();  // the owners' inputs are in LDS
         float d[NO][16];
         run_net_split_owned<NT, ST, kPropSplitWaves, kPropSplitDepth>(P, p.b0_trans, in_lds, d, lane, g, wave, smem);
         if (valid)
