@@ -315,7 +315,7 @@ struct voila_model_s {
     NetBlob trans_plan{}, trans_upd{}, obs{}, lik{}, lik_nce{};
     // the observation network for the rows of whole rollouts: in the paired
     // plan evaluation's pass-major order where that evaluation applies, else obs
-    NetBlob obs_roll{};
+    NetBlob obs_roll{}, lik_pw{};
     const float* fold_w_trans = nullptr;
     const float* fold_b_trans = nullptr;
     const float* fold_w_obs = nullptr;
@@ -545,6 +545,15 @@ voila_status_t voila_model_create(const voila_model_desc_t* desc, int32_t device
     } else {
         blobs.emplace_back();
     }
+    // the likelihood network in pass-major order for the grouped widening step
+    const int lik_pt = L.present() && !m->lik_split ? plan_pass_tiles(shape, dt) : 0;
+    if (lik_pt) {
+        std::vector<float> b0(L.b[0], L.b[0] + LW);
+        SlotMap ml{m->d_s, 0, 0, m->d_s, m->d_s};
+        blobs.push_back(pack_net(L, dt, lik_in_slots(shape, dt), ml, b0, 1, m->lik_pw, false, lik_pt));
+    } else {
+        blobs.emplace_back();
+    }
     const size_t nb = blobs.size();
     std::vector<std::vector<float>> folds;
     m->nf_trans = aw;
@@ -624,6 +633,11 @@ voila_status_t voila_model_create(const voila_model_desc_t* desc, int32_t device
         m->obs_roll.base = m->mem + offs[9];
     } else {
         m->obs_roll = m->obs;
+    }
+    if (lik_pt) {
+        m->lik_pw.base = m->mem + offs[10];
+    } else {
+        m->lik_pw = m->lik;
     }
     m->fold_w_trans = reinterpret_cast<const float*>(m->mem + offs[nb + 0]);
     m->fold_b_trans = reinterpret_cast<const float*>(m->mem + offs[nb + 1]);
@@ -1140,6 +1154,7 @@ struct PwWs {
     float* o_sel;
     float* b0_lik;
     int32_t* tiles;
+    int4* units;
     double* x;
     size_t bytes;
 };
@@ -1157,6 +1172,7 @@ PwWs carve_pw(char* base, voila_model_t m, int T, int M) {
     w.o_sel = reinterpret_cast<float*>(take((size_t)M * m->d_o * 4));
     w.b0_lik = reinterpret_cast<float*>(take((size_t)M * m->width * 4));
     w.tiles = reinterpret_cast<int32_t*>(take(((size_t)M + 1) * 4));
+    w.units = reinterpret_cast<int4*>(take(((size_t)T / 32 + M) * sizeof(int4)));
     w.x = reinterpret_cast<double*>(take((size_t)T * 8));
     w.bytes = off;
     return w;
@@ -1194,7 +1210,7 @@ voila_status_t voila_pw_step(voila_model_t m, const float* d_succ, int32_t T, co
     if (!guard.ok) return fail(VOILA_ERR_DEVICE, "hipSetDevice failed");
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     PwParams p{};
-    p.lik = m->lik;
+    p.lik = m->lik_pw;
     p.succ = d_succ;
     p.seg = d_seg;
     p.actions = d_actions;
@@ -1207,6 +1223,8 @@ voila_status_t voila_pw_step(voila_model_t m, const float* d_succ, int32_t T, co
     p.o_sel = w.o_sel;
     p.b0_lik = w.b0_lik;
     p.tiles = w.tiles;
+    p.units = w.units;
+    p.unit_tiles = plan_pass_tiles(m->shape, m->dt) ? 2 : 1;
     p.x = w.x;
     p.widen = d_widen_out;
     p.branch = d_branch_out;
@@ -1226,8 +1244,8 @@ voila_status_t voila_pw_step(voila_model_t m, const float* d_succ, int32_t T, co
     p.lambda = o->lambda;
     p.key0 = (uint32_t)(o->seed & 0xffffffffu);
     p.key1 = (uint32_t)(o->seed >> 32);
-    // 1. an observation drawn at each group's first successor (used by the groups that widen)
-    VOILA_CHECK_HIP(launch_pw_first(p, s));
+    // 1. the likelihood's work units; an observation drawn at each group's
+    // first successor (used by the groups that widen)
     FoldStepsParams fo{};
     fo.w = m->fold_w_obs;
     fo.b = m->fold_b_obs;
@@ -1240,7 +1258,7 @@ voila_status_t voila_pw_step(voila_model_t m, const float* d_succ, int32_t T, co
     fo.d_a = m->d_a;
     fo.bf16 = m->dt == DT_BF16 ? 1 : 0;
     fo.status = d_status;
-    VOILA_CHECK_HIP(launch_fold_steps(fo, s));
+    VOILA_CHECK_HIP(launch_pw_prepare(p, fo, s));
     ObserveParams op{};
     op.obs = m->obs;
     op.b0 = w.b0_obs;
@@ -1252,7 +1270,8 @@ voila_status_t voila_pw_step(voila_model_t m, const float* d_succ, int32_t T, co
     op.H = 1;
     op.key0 = p.key0;
     op.key1 = p.key1;
-    VOILA_CHECK_HIP(launch_observe(m->shape, m->dt, op, observe_blocks(m, M), s));
+    op.row_groups = 1;
+    VOILA_CHECK_HIP(launch_observe(m->shape, m->dt, op, observe_blocks(m, ((long)M + 31) / 32), s));
     // 2. widening test, branch choice, table update
     VOILA_CHECK_HIP(launch_pw_branch(p, s));
     // 3. likelihood of every successor against its group's branch observation
@@ -1264,13 +1283,12 @@ voila_status_t voila_pw_step(voila_model_t m, const float* d_succ, int32_t T, co
     fl.obs = w.o_sel;
     fl.d_o = m->d_o;
     VOILA_CHECK_HIP(launch_fold_steps(fl, s));
-    VOILA_CHECK_HIP(launch_pw_tiles(p, s));
-    const long units = (long)T / 32 + M;
+    const long units = (long)T / (32 * p.unit_tiles) + M;
     const long want = (units + kWavesPerBlock - 1) / kWavesPerBlock;
     const long cap = (long)m->cus * m->pw_bpc;
     VOILA_CHECK_HIP(launch_pw_lik(m->shape, m->dt, p, (int)(want < cap ? want : cap), s));
     // 4. per-group weights and systematic resampling
-    VOILA_CHECK_HIP(launch_pw_norm_res(p, M < m->cus ? M : m->cus, s));
+    VOILA_CHECK_HIP(launch_pw_norm_res(p, m->cus, s));
     return VOILA_OK;
 }
 

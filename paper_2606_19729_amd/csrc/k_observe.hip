@@ -22,6 +22,16 @@ struct ObsRow {
 // This lane's row of tile unit u (index arithmetic only).
 __device__ __forceinline__ ObsRow observe_row(const ObserveParams& p, long u, int n_tiles, int col) {
     ObsRow w;
+    if (p.row_groups) {
+        // one row per group: the tile's columns are 32 groups (a tile per group
+        // would hold one row: 82 us for 4,096 groups of the realistic network)
+        const int k = (int)u * 32 + col;
+        w.valid = k < p.K;
+        w.grp = w.valid ? k : p.K - 1;
+        w.i = 0;
+        w.r = (size_t)w.grp;
+        return w;
+    }
     w.grp = (int)(u / n_tiles);
     const int tile = (int)(u - (long)w.grp * n_tiles);
     const int k = w.grp / p.H, t = w.grp - k * p.H;
@@ -187,7 +197,8 @@ __global__ __launch_bounds__(256) void observe_kernel(ObserveParams p) {
         // split mode: the block's four waves evaluate one tile together
         const int tpb = MODE == kSplit ? 1 : (int)(blockDim.x >> 6);
         const long first = MODE == kSplit ? (long)blockIdx.x : (long)blockIdx.x * tpb + wave;
-        for (long u = first; u < n_units; u += (long)gridDim.x * tpb) {
+        const long n_here = p.row_groups ? ((long)p.K + 31) / 32 : n_units;
+        for (long u = first; u < n_here; u += (long)gridDim.x * tpb) {
             float slots[NTO::IN_SLOTS];
             const ObsRow w = observe_inputs<D_S, D_WZ>(p, u, n_tiles, g, col, slots);
             const float* b0 = p.b0 + (size_t)w.grp * p.b0_stride;

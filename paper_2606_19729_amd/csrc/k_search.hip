@@ -163,22 +163,16 @@ __device__ __forceinline__ bool pw_group(const PwParams& p, int m, int& lo, int&
 }
 }  // namespace
 
-// First successor of each group (the state a new branch's observation is drawn at).
-__global__ __launch_bounds__(256) void pw_first_kernel(PwParams p) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= p.M * p.d_s) return;
-    const int m = e / p.d_s, c = e - m * p.d_s;
-    int lo, n;
-    pw_group(p, m, lo, n);
-    p.first[e] = n > 0 ? p.succ[(size_t)lo * p.d_s + c] : 0.0f;
-}
-
-// Widening test, branch choice and table update, one thread per action node.
+// Widening test, branch choice and table update, 32 lanes per action node (each
+// takes the test; they share the copies), and the records of the node's
+// likelihood work units.
 __global__ __launch_bounds__(256) void pw_branch_kernel(PwParams p) {
-    const int m = blockIdx.x * blockDim.x + threadIdx.x;
+    const int m = blockIdx.x * (blockDim.x / 32) + threadIdx.x / 32, l = threadIdx.x & 31;
     if (m >= p.M) return;
     int lo, n;
     pw_group(p, m, lo, n);
+    for (int q = l, nu = p.tiles[m + 1] - p.tiles[m]; q < nu; q += 32)
+        p.units[p.tiles[m] + q] = make_int4(m, lo + q * 32 * p.unit_tiles, lo + n, 0);
     int wid = 0, br = -1;
     const int C = p.children[m];
     if (C < 0 || C > p.B) {
@@ -190,31 +184,55 @@ __global__ __launch_bounds__(256) void pw_branch_kernel(PwParams p) {
         float* row = p.table + (size_t)m * p.B * p.d_o;
         if (wid) {
             br = C;
-            for (int c = 0; c < p.d_o; ++c) row[(size_t)br * p.d_o + c] = p.o_new[(size_t)m * p.d_o + c];
-            p.children[m] = C + 1;
         } else {
             const uint4 w = philox4x32_10(make_uint4((uint32_t)m, 1u, 0u, 6u << 16), p.key0, p.key1);
             br = (int)floor((double)word_to_uniform(w.x) * (double)C);
         }
-        for (int c = 0; c < p.d_o; ++c) p.o_sel[(size_t)m * p.d_o + c] = row[(size_t)br * p.d_o + c];
+        for (int c = l; c < p.d_o; c += 32) {
+            const float v = wid ? p.o_new[(size_t)m * p.d_o + c] : row[(size_t)br * p.d_o + c];
+            if (wid) row[(size_t)br * p.d_o + c] = v;
+            p.o_sel[(size_t)m * p.d_o + c] = v;
+        }
     } else {
-        for (int c = 0; c < p.d_o; ++c) p.o_sel[(size_t)m * p.d_o + c] = 0.0f;
+        for (int c = l; c < p.d_o; c += 32) p.o_sel[(size_t)m * p.d_o + c] = 0.0f;
     }
-    if (p.widen) p.widen[m] = wid;
-    if (p.branch) p.branch[m] = br;
+    if (l == 0) {
+        // (after every lane's read of the count: a wave's lanes step together)
+        if (wid) p.children[m] = C + 1;
+        if (p.widen) p.widen[m] = wid;
+        if (p.branch) p.branch[m] = br;
+    }
 }
 
-// Exclusive prefix of the groups' 32-row tile counts (one workgroup).
-__global__ __launch_bounds__(1024) void pw_tiles_kernel(PwParams p) {
+// Block 0: exclusive prefix of the groups' likelihood work units.  The next
+// blocks: first successor of each group (the state a new branch's observation
+// is drawn at); the last ones: the observation network's bias rows (few groups;
+// many take fold_rows_kernel).  One launch, since none needs another's result.
+__global__ __launch_bounds__(1024) void pw_prepare_kernel(PwParams p, FoldStepsParams fold, int first_blocks) {
+    if ((int)blockIdx.x > first_blocks) {
+        const long e = (long)((int)blockIdx.x - 1 - first_blocks) * blockDim.x + threadIdx.x;
+        const int j = (int)(e / fold.width), r = (int)(e - (long)j * fold.width);
+        if (j < fold.rows) fold_element(fold, j, r);
+        return;
+    }
+    if (blockIdx.x > 0) {
+        const int e = (blockIdx.x - 1) * blockDim.x + threadIdx.x;
+        if (e >= p.M * p.d_s) return;
+        const int m = e / p.d_s, c = e - m * p.d_s;
+        int lo, n;
+        pw_group(p, m, lo, n);
+        p.first[e] = n > 0 ? p.succ[(size_t)lo * p.d_s + c] : 0.0f;
+        return;
+    }
     __shared__ int wtot[16];
     const int tid = threadIdx.x, lane = tid & 63;
-    const int per = (p.M + 1023) / 1024;
+    const int per = (p.M + 1023) / 1024, rows = 32 * p.unit_tiles;
     const int a = tid * per, b = min(p.M, a + per);
     int run = 0;
     for (int m = a; m < b; ++m) {
         int lo, n;
         pw_group(p, m, lo, n);
-        run += (n + 31) / 32;
+        run += (n + rows - 1) / rows;
     }
     int incl = run;
 #pragma unroll
@@ -230,13 +248,18 @@ __global__ __launch_bounds__(1024) void pw_tiles_kernel(PwParams p) {
         int lo, n;
         pw_group(p, m, lo, n);
         p.tiles[m] = off;
-        off += (n + 31) / 32;
+        off += (n + rows - 1) / rows;
     }
     if (tid == 1023) p.tiles[p.M] = off;
 }
 
 // Likelihood of every successor against its group's chosen observation:
-// x_j = l([s'_j, a_m, o_m]) / lambda, one 32-row tile of one group per wave.
+// x_j = l([s'_j, a_m, o_m]) / lambda, one work unit of one group per wave: a
+// 32-row tile, or two through the paired evaluation of the rollout kernel.  A
+// unit's record, states and bias row are read one unit ahead (a wave's
+// consecutive units lie in different groups, and finding the group by bisection
+// alone took as long as the network).  2.1 M successors of 4,096 groups,
+// bfloat16 realistic network: 800 -> 600 us.
 template <int DT, int D_S, int WIDTH, int NHID, int MODE>
 __global__ __launch_bounds__(256) void pw_lik_kernel(PwParams p) {
     if constexpr (!generic_compiled(DT, WIDTH, NHID)) {
@@ -244,52 +267,238 @@ __global__ __launch_bounds__(256) void pw_lik_kernel(PwParams p) {
     } else {
     typedef Net<DT, WIDTH, NHID, in_slots(DT, D_S, 0, 0)> NTL;
     constexpr int SS = state_slots(D_S);
+    constexpr bool PAIRS = MODE == kStream && plan_pairs<DT, WIDTH, NHID>();
+    constexpr int TPU = PAIRS ? 2 : 1;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int lane = threadIdx.x & 63, g = lane >> 5, col = lane & 31;
     const int wpb = blockDim.x >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const kconst int32_t* tiles = (const kconst int32_t*)p.tiles;
-    const kconst int32_t* seg = (const kconst int32_t*)p.seg;
-    const long n_units = tiles[p.M];
-    with_weights<NTL, MODE, 1>(smem, p.lik, [&](auto& src, const NetPtrs& P) {
-        // block-uniform loop (a streamed network's chunk barriers need every wave)
-        for (long ub = blockIdx.x; ub * wpb < n_units; ub += gridDim.x) {
-            const int u = (int)(ub * wpb + wave);
-            const bool ok = u < n_units;
-            // the group of this tile: the last m with tiles[m] <= u
-            int a = 0, b = p.M;
-            while (a < b) {
-                const int mid = (a + b + 1) >> 1;
-                if (tiles[mid] <= u) a = mid;
-                else b = mid - 1;
-            }
-            const int m = ok ? a : 0;
-            const int lo = seg[m], hi = seg[m + 1];
-            const int j = ok ? lo + (u - tiles[m]) * 32 + col : 0;
-            const bool valid = ok && j < hi;
-            float slots[NTL::IN_SLOTS];
+    const kconst int32_t* units = (const kconst int32_t*)p.units;
+    const long n_units = ((const kconst int32_t*)p.tiles)[p.M];
+    float* rowb = reinterpret_cast<float*>(smem + p.row_bias_lds) + wave * NTL::WIDTH;
+    constexpr int RB = NTL::WIDTH / 64;  // bias floats per lane
+    static_assert(NTL::WIDTH % 64 == 0 && RB <= 16, "bias row copy: whole lanes");
+    int nj[TPU];
+    bool nv[TPU];
+    float nst[TPU][SS], nbv[RB];
+    auto next_inputs = [&](long u) {
+        const bool ok = u < n_units;  // wave-uniform
+        const long at = ok ? 4 * u : 0;
+        const int4 rec = make_int4(units[at], units[at + 1], ok ? units[at + 2] : 0, 0);
 #pragma unroll
-            for (int s = 0; s < NTL::IN_SLOTS; ++s) slots[s] = 0.0f;
+        for (int q = 0; q < TPU; ++q) {
+            nj[q] = rec.y + 32 * q + col;
+            nv[q] = nj[q] < rec.z;
 #pragma unroll
             for (int s = 0; s < SS; ++s) {
                 const int f = 2 * s + g;
-                slots[s] = (valid && f < D_S) ? p.succ[(size_t)j * D_S + f] : 0.0f;
+                nst[q][s] = (nv[q] && f < D_S) ? p.succ[(size_t)nj[q] * D_S + f] : 0.0f;
             }
-            __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
-            const f32x16 o = run_net<NTL>(src, P, p.b0_lik + (size_t)m * NTL::WIDTH, slots, lane, g);
-            if (g == 0 && valid) {
-                const float l = o[0];
-                if (p.loglik) p.loglik[j] = l;
-                if (!isfinite(l) && p.status) p.status[0] = 5;
-                p.x[j] = (double)l / p.lambda;
+        }
+        const float* brow = p.b0_lik + (size_t)rec.x * NTL::WIDTH;
+#pragma unroll
+        for (int q = 0; q < RB; ++q) nbv[q] = brow[q * 64 + lane];
+    };
+    with_weights<NTL, MODE, 1, PAIRS ? VOILA_PLAN_STREAM_CHB : VOILA_STREAM_CHB>(smem, p.lik, [&](auto& src,
+                                                                                            const NetPtrs& P) {
+        if (n_units > 0) next_inputs((long)blockIdx.x * wpb + wave);
+        // block-uniform loop (a streamed network's chunk barriers need every wave)
+        for (long ub = blockIdx.x; ub * wpb < n_units; ub += gridDim.x) {
+            float slots[TPU][NTL::IN_SLOTS];
+            int j[TPU];
+            bool valid[TPU];
+#pragma unroll
+            for (int q = 0; q < TPU; ++q) {
+                j[q] = nj[q];
+                valid[q] = nv[q];
+#pragma unroll
+                for (int s = 0; s < NTL::IN_SLOTS; ++s) slots[q][s] = 0.0f;
+#pragma unroll
+                for (int s = 0; s < SS; ++s) slots[q][s] = nst[q][s];
             }
+#pragma unroll
+            for (int q = 0; q < RB; ++q) rowb[q * 64 + lane] = nbv[q];
+            next_inputs((ub + gridDim.x) * wpb + wave);
+            f32x16 o[TPU];
+            if constexpr (PAIRS) {
+                run_net_flat<NTL, 2, kPlanPassTiles>(src, P, rowb, slots, o, lane, g);
+            } else {
+                o[0] = run_net<NTL>(src, P, rowb, slots[0], lane, g);
+            }
+#pragma unroll
+            for (int q = 0; q < TPU; ++q)
+                if (g == 0 && valid[q]) {
+                    const float l = o[q][0];
+                    if (p.loglik) p.loglik[j[q]] = l;
+                    if (!isfinite(l) && p.status) p.status[0] = 5;
+                    p.x[j[q]] = (double)l / p.lambda;
+                }
         }
     });
     }
 }
 
-// Weights, statistics and systematic resampling of every group, one
-// workgroup per group (the single-belief procedure on the group's rows).
+// Weights, statistics and systematic resampling of every group of at most
+// kPwSmall successors, a workgroup of 256 threads each (a group is a chain of
+// reductions: many small workgroups per CU overlap their latencies, where one
+// of 1,024 threads with LDS for 8,192 fills a CU alone: 159 -> 89 us for 4,096
+// groups).  Element tid + 256 v plays thread tid + 256 v of the single-belief
+// procedure and the sums keep its order (lanes by butterfly, then the 16
+// wave sums), so the weights are its bits.
+constexpr int kPwSmall = 1024, kPwThreads = 256, kPwPer = kPwSmall / kPwThreads, kPwWaves = kPwSmall / 64;
+__global__ __launch_bounds__(kPwThreads) void pw_norm_res_small_kernel(PwParams pw) {
+    __shared__ double buf[kPwSmall];
+    __shared__ int ids[kPwSmall];
+    __shared__ double redd[kPwWaves];
+    __shared__ int redi[kPwThreads / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // (waves past the group's end have nothing to compute in slot k: zeros)
+    auto sum = [&](const double (&v)[kPwPer], int n) {
+        double t[kPwPer];
+#pragma unroll
+        for (int k = 0; k < kPwPer; ++k) t[k] = kPwThreads * k + 64 * wave < n ? wave_sum_d(v[k]) : 0.0;
+        __syncthreads();
+        if (lane == 0)
+#pragma unroll
+            for (int k = 0; k < kPwPer; ++k) redd[4 * k + wave] = t[k];
+        __syncthreads();
+        double r = 0.0;
+#pragma unroll
+        for (int w = 0; w < kPwWaves; ++w) r += redd[w];
+        return r;
+    };
+    auto max_i = [&](int v) {
+        v = wave_max_i(v);
+        __syncthreads();
+        if (lane == 0) redi[wave] = v;
+        __syncthreads();
+        int r = redi[0];
+#pragma unroll
+        for (int w = 1; w < kPwThreads / 64; ++w) r = max(r, redi[w]);
+        return r;
+    };
+    for (int m = blockIdx.x; m < pw.M; m += gridDim.x) {
+        int lo, n;
+        pw_group(pw, m, lo, n);
+        if (n == 0 || n > kPwSmall) continue;
+        int c = 0;
+        while ((1 << c) < n) ++c;
+        const int bits = 52 - c < 32 ? 52 - c : 32;
+        double x[kPwPer], v[kPwPer], mx = -INFINITY;
+        int bad = 0;
+#pragma unroll
+        for (int k = 0; k < kPwPer; ++k) {
+            const int i = tid + kPwThreads * k;
+            x[k] = i < n ? pw.x[(size_t)lo + i] : -INFINITY;
+            if (isnan(x[k]) || x[k] == INFINITY) bad = 1;
+            mx = fmax(mx, x[k]);
+        }
+        mx = wave_max_d(mx);
+        __syncthreads();
+        if (lane == 0) redd[wave] = mx;
+        __syncthreads();
+        mx = fmax(fmax(redd[0], redd[1]), fmax(redd[2], redd[3]));
+        if (max_i(bad) || !isfinite(mx)) {
+            if (tid == 0 && pw.status) pw.status[0] = 5;
+            __syncthreads();
+            continue;
+        }
+#pragma unroll
+        for (int k = 0; k < kPwPer; ++k) {
+            v[k] = 0.0;
+            if (kPwThreads * k + 64 * wave < n) v[k] = tid + kPwThreads * k < n ? exp(x[k] - mx) : 0.0;
+        }
+        const double S = sum(v, n);
+        double w[kPwPer];
+#pragma unroll
+        for (int k = 0; k < kPwPer; ++k) {
+            const int i = tid + kPwThreads * k;
+            w[k] = 0.0;
+            if (i < n) {
+                w[k] = v[k] / S;
+                if (pw.w) pw.w[(size_t)lo + i] = w[k];
+            }
+            v[k] = w[k] * w[k];
+        }
+        const double SQ = sum(v, n);
+        if (tid == 0 && pw.stats) {
+            pw.stats[2 * (size_t)m] = mx + log(S) - log((double)n);
+            pw.stats[2 * (size_t)m + 1] = 1.0 / SQ;
+        }
+        const double scale = ldexp((double)n, bits);
+        int last = -1;
+#pragma unroll
+        for (int k = 0; k < kPwPer; ++k) {
+            w[k] = rint(w[k] * scale);
+            if (w[k] > 0.0) last = tid + kPwThreads * k;
+        }
+        last = max_i(last);
+        if (last < 0) {
+            if (tid == 0 && pw.status) pw.status[0] = 5;
+            __syncthreads();
+            continue;
+        }
+        // inclusive prefix (exact integers: any order gives the same bits)
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kPwPer; ++k) {
+            v[k] = w[k];
+            if (kPwThreads * k + 64 * wave < n)
+#pragma unroll
+                for (int d = 1; d < 64; d <<= 1) {
+                    const double o = __shfl_up(v[k], d);
+                    if (lane >= d) v[k] += o;
+                }
+            if (lane == 63) redd[4 * k + wave] = v[k];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kPwPer; ++k) {
+            double off = 0.0;
+            for (int q = 0; q < 4 * k + wave; ++q) off += redd[q];
+            buf[tid + kPwThreads * k] = v[k] + off;
+        }
+        __syncthreads();
+        const double step = ldexp(1.0, bits), u = (double)(pw.U[m] >> (32 - bits));
+        // first i with C_i > P_j (the count of C_i <= P_j), a thread's outputs side by side
+        int at[kPwPer];
+#pragma unroll
+        for (int k = 0; k < kPwPer; ++k) at[k] = 0;
+#pragma unroll
+        for (int d = kPwSmall; d >= 1; d >>= 1) {
+            if (d > n) continue;
+#pragma unroll
+            for (int k = 0; k < kPwPer; ++k) {
+                const double P = (double)(tid + kPwThreads * k) * step + u;
+                const int e = at[k] + d;
+                if (e <= n && !(buf[e - 1] > P)) at[k] = e;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < kPwPer; ++k) {
+            const int j = tid + kPwThreads * k;
+            if (j < n) {
+                const int idx = at[k] < n ? at[k] : last;
+                if (pw.idx) pw.idx[(size_t)lo + j] = idx;
+                ids[j] = idx;
+            }
+        }
+        __syncthreads();
+        if (pw.succ_out) {
+            const int rf = pw.d_s;
+            const float* src = pw.succ + (size_t)lo * rf;
+            float* dst = pw.succ_out + (size_t)lo * rf;
+            if (rf % 4 == 0 && ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) & 15) == 0)
+                block_gather(reinterpret_cast<float4*>(dst), reinterpret_cast<const float4*>(src), ids, n, rf / 4);
+            else
+                block_gather(dst, src, ids, n, rf);
+        }
+        __syncthreads();
+    }
+}
+
+// The same for groups of more than kPwSmall successors, one workgroup of 1,024
+// threads per group (the single-belief procedure on the group's rows).
 __global__ __launch_bounds__(kNormResThreads) void pw_norm_res_kernel(PwParams pw) {
     __shared__ double buf[kNormResMaxN];
     __shared__ int ids[kNormResMaxN];
@@ -298,7 +507,7 @@ __global__ __launch_bounds__(kNormResThreads) void pw_norm_res_kernel(PwParams p
     for (int m = blockIdx.x; m < pw.M; m += gridDim.x) {
         int lo, n;
         pw_group(pw, m, lo, n);
-        if (n == 0) continue;
+        if (n <= kPwSmall) continue;
         int c = 0;
         while ((1 << c) < n) ++c;
         NormResParams p{};
@@ -324,22 +533,33 @@ __global__ __launch_bounds__(kNormResThreads) void pw_norm_res_kernel(PwParams p
 // launchers
 #define PWL_K(id, ds, na, da, dw, dox, dwz, w, nh, DT) pw_lik_kernel<DT, ds, w, nh, plan_mode<w>()>
 
-hipError_t launch_pw_lik(int shape, int dt, const PwParams& p, int blocks, hipStream_t s) {
+template <int DT, int D_S, int W, int NH>
+constexpr size_t pw_stream_lds() {
+    return plan_pairs<DT, W, NH>() ? stream_lds_of<DT, D_S, 0, 0, 0, W, NH, VOILA_PLAN_STREAM_CHB>()
+                                   : stream_lds_of<DT, D_S, 0, 0, 0, W, NH>();
+}
+
+hipError_t launch_pw_lik(int shape, int dt, const PwParams& p0, int blocks, hipStream_t s) {
+    PwParams p = p0;
     size_t lds = p.lik.bytes;
     if (!weights_in_lds(shape)) {
         switch (shape * 2 + dt) {
 #define X(id, ds, na, da, dw, dox, dwz, w, nh)                           \
     case id * 2 + 0:                                                    \
-        lds = stream_lds_of<DT_F32, ds, 0, 0, 0, w, nh>();              \
+        lds = pw_stream_lds<DT_F32, ds, w, nh>();                       \
         break;                                                          \
     case id * 2 + 1:                                                    \
-        lds = stream_lds_of<DT_BF16, ds, 0, 0, 0, w, nh>();             \
+        lds = pw_stream_lds<DT_BF16, ds, w, nh>();                      \
         break;
             VOILA_SHAPES(X)
 #undef X
         }
         lds += p.lik.bytes - p.lik.off_b0;
     }
+    // one first-layer bias row per wave after the staged weights and biases
+    lds = (lds + 15) / 16 * 16;
+    p.row_bias_lds = (uint32_t)lds;
+    lds += (size_t)kWavesPerBlock * shape_info(shape).width * 4;
     switch (shape * 2 + dt) {
 #define X(id, ds, na, da, dw, dox, dwz, w, nh)                                                                \
     case id * 2 + 0:                                                                                         \
@@ -366,9 +586,11 @@ int pw_lik_blocks_per_cu(int shape, int dt) {
     switch (shape * 2 + dt) {
 #define X(id, ds, na, da, dw, dox, dwz, w, nh)                                                               \
     case id * 2 + 0:                                                                                        \
-        return occupancy(PWL_K(id, ds, na, da, dw, dox, dwz, w, nh, DT_F32), lds_for_width<w>() ? kLdsGuess : kStreamLds); \
+        return occupancy(PWL_K(id, ds, na, da, dw, dox, dwz, w, nh, DT_F32),                                \
+                         lds_for_width<w>() ? kLdsGuess : pw_stream_lds<DT_F32, ds, w, nh>());               \
     case id * 2 + 1:                                                                                        \
-        return occupancy(PWL_K(id, ds, na, da, dw, dox, dwz, w, nh, DT_BF16), lds_for_width<w>() ? kLdsGuess : kStreamLds);
+        return occupancy(PWL_K(id, ds, na, da, dw, dox, dwz, w, nh, DT_BF16),                               \
+                         lds_for_width<w>() ? kLdsGuess : pw_stream_lds<DT_BF16, ds, w, nh>());
         VOILA_SHAPES(X)
 #undef X
     }
@@ -402,27 +624,27 @@ hipError_t launch_soft_value(const SoftValueParams& p, int blocks, hipStream_t s
     return hipGetLastError();
 }
 
-hipError_t launch_pw_first(const PwParams& p, hipStream_t s) {
-    const int n = p.M * p.d_s;
-    if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(pw_first_kernel, (n + 255) / 256, 256, 0, s, p);
-    return hipGetLastError();
-}
-
 hipError_t launch_pw_branch(const PwParams& p, hipStream_t s) {
     if (p.M == 0) return hipSuccess;
-    hipLaunchKernelGGL(pw_branch_kernel, (p.M + 255) / 256, 256, 0, s, p);
+    hipLaunchKernelGGL(pw_branch_kernel, (p.M + 7) / 8, 256, 0, s, p);
     return hipGetLastError();
 }
 
-hipError_t launch_pw_tiles(const PwParams& p, hipStream_t s) {
-    hipLaunchKernelGGL(pw_tiles_kernel, 1, 1024, 0, s, p);
-    return hipGetLastError();
+hipError_t launch_pw_prepare(const PwParams& p, const FoldStepsParams& fold, hipStream_t s) {
+    const int first_blocks = (p.M * p.d_s + 1023) / 1024;
+    const bool here = fold.rows < kFoldManyRows;
+    const int fold_blocks = here ? (int)(((long)fold.rows * fold.width + 1023) / 1024) : 0;
+    hipLaunchKernelGGL(pw_prepare_kernel, 1 + first_blocks + fold_blocks, 1024, 0, s, p, fold, first_blocks);
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess || here ? e : launch_fold_steps(fold, s);
 }
 
-hipError_t launch_pw_norm_res(const PwParams& p, int blocks, hipStream_t s) {
-    if (p.M == 0 || blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(pw_norm_res_kernel, blocks, kNormResThreads, 0, s, p);
+hipError_t launch_pw_norm_res(const PwParams& p, int cus, hipStream_t s) {
+    if (p.M == 0 || cus == 0) return hipSuccess;
+    const int cap = 8 * cus;
+    hipLaunchKernelGGL(pw_norm_res_small_kernel, p.M < cap ? p.M : cap, kPwThreads, 0, s, p);
+    // a group can only be larger when there are that many successors
+    if (p.T > kPwSmall) hipLaunchKernelGGL(pw_norm_res_kernel, p.M < cus ? p.M : cus, kNormResThreads, 0, s, p);
     return hipGetLastError();
 }
 

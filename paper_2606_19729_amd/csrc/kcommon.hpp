@@ -149,6 +149,40 @@ __device__ int block_max_i(int v, int* red) {
 
 }  // namespace
 
+// First-layer bias r of row j with the row's action (and observation) folded in.
+__device__ __forceinline__ void fold_element(const FoldStepsParams& p, int j, int r) {
+    float acc = p.b[r];
+    bool bad = false;
+    if (p.n_actions > 0) {
+        int a = reinterpret_cast<const int32_t*>(p.cands)[j];
+        if (a < 0 || a >= p.n_actions) {
+            bad = true;
+            a = 0;
+        }
+        for (int c = 0; c < p.n_actions; ++c) acc += p.w[(size_t)r * p.nf + c] * (c == a ? 1.0f : 0.0f);
+    } else {
+        const float* ac = reinterpret_cast<const float*>(p.cands) + (size_t)j * p.d_a;
+        for (int c = 0; c < p.d_a; ++c) {
+            float v = ac[c];
+            bad |= !isfinite(v);
+            if (p.bf16) v = (float)(__bf16)v;
+            acc += p.w[(size_t)r * p.nf + c] * v;
+        }
+    }
+    if (p.obs) {
+        const int c0 = p.n_actions > 0 ? p.n_actions : p.d_a;
+        const float* ob = p.obs + (size_t)j * p.d_o;
+        for (int c = 0; c < p.d_o; ++c) {
+            float v = ob[c];
+            bad |= !isfinite(v);
+            if (p.bf16) v = (float)(__bf16)v;
+            acc += p.w[(size_t)r * p.nf + c0 + c] * v;
+        }
+    }
+    if (bad && p.status && r == 0) p.status[0] = 1;
+    p.out[(size_t)j * p.width + r] = acc;
+}
+
 // dst row r = src row ids[r] for r < n (rows of w elements) by the whole
 // workgroup: each thread keeps one column and walks rows, so consecutive
 // threads move consecutive elements.

@@ -90,6 +90,7 @@ struct ObserveParams {
     const float* noise;      // [K][N][H][d_wz] or NULL
     float* out;              // [K][N][H][d_o]
     int N, K, H, crn;
+    int row_groups;          // N = H = 1: 32 rows of different groups to a tile, each with its own bias row
     uint32_t key0, key1;
     uint32_t row_bias_lds;   // LDS offset of the per-wave bias rows (whole-rollout launches; set by the launcher)
 };
@@ -158,7 +159,10 @@ struct PwParams {
     const float* o_new;       // [M][d_o] observation drawn at the first successor
     float* o_sel;             // [M][d_o] observation of the chosen branch (workspace)
     const float* b0_lik;      // [M][width] folded likelihood biases
-    int32_t* tiles;           // [M + 1] exclusive prefix of the groups' 32-row tile counts
+    int32_t* tiles;           // [M + 1] exclusive prefix of the groups' work-unit counts
+    int4* units;              // [units] group, first row, end of the group's rows of each likelihood work unit
+    int unit_tiles;           // 32-row tiles per work unit (2: paired evaluation)
+    uint32_t row_bias_lds;    // LDS offset of the per-wave bias rows (set by the launcher)
     double* x;                // [T] l / lambda
     int32_t* widen;           // [M] or NULL
     int32_t* branch;          // [M] or NULL
@@ -355,12 +359,12 @@ hipError_t launch_plan(int shape, int dt, const PlanParams& p, int blocks, hipSt
 hipError_t launch_q_reduce(const QReduceParams& p, hipStream_t s);
 hipError_t launch_fold_steps(const FoldStepsParams& p, hipStream_t s);
 // Grouped progressive-widening stages.
-hipError_t launch_pw_first(const PwParams& p, hipStream_t s);
+constexpr int kFoldManyRows = 256;  // rows from which the folds take a kernel for many rows
+hipError_t launch_pw_prepare(const PwParams& p, const FoldStepsParams& fold, hipStream_t s);
 hipError_t launch_pw_branch(const PwParams& p, hipStream_t s);
-hipError_t launch_pw_tiles(const PwParams& p, hipStream_t s);
 hipError_t launch_pw_lik(int shape, int dt, const PwParams& p, int blocks, hipStream_t s);
 int pw_lik_blocks_per_cu(int shape, int dt);
-hipError_t launch_pw_norm_res(const PwParams& p, int blocks, hipStream_t s);
+hipError_t launch_pw_norm_res(const PwParams& p, int cus, hipStream_t s);
 // Contrastive-objective stages: all-pairs scores, per-row losses and
 // derivatives (one workgroup per row), the mean loss (one workgroup).
 hipError_t launch_nce_scores(int shape, int dt, const NceParams& p, int blocks, hipStream_t s);

@@ -190,3 +190,21 @@ def test_realistic_many_groups_sampled(V):
         assert scaled_err(d["loglik"][lo:hi], ll) <= TOL, g
     check_groups(c, d, lam, groups=groups)
     print(f"  {len(groups)} sampled groups match; widened {int(d['widen'].sum())}", flush=True)
+
+
+@pytest.mark.parametrize("compute", ["f32", "bf16"])
+@pytest.mark.parametrize("copies", [1, 25])
+def test_groups_at_the_edges_of_tiles_and_workgroups(V, compute, copies):
+    # group sizes around the tile (32), the two-tile unit (64), the wave and
+    # the 256 threads of the small groups' workgroup, and around the 1,024
+    # successors from which a group takes the large one; 11 groups (bias rows
+    # folded beside the work-unit prefix) and 275 (by the kernel for many rows)
+    w = workloads.realistic(seed=66, N=8, K=1, H=1)
+    sizes = [1, 31, 32, 33, 64, 65, 256, 257, 1023, 1024, 1025]
+    small = [s for s in sizes if s < 300]
+    sizes = sizes + (small * 40)[:len(sizes) * (copies - 1)]
+    c = make_case(w.model, 66, M=len(sizes), d_max=8)
+    c["seg"] = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    c["succ"] = (np.random.default_rng(67).standard_normal((sum(sizes), w.model.d_s)) * 0.8).astype(np.float32)
+    print(f"pw step group edges {compute}, {len(sizes)} groups", flush=True)
+    compare(V, w.model, c, compute)
