@@ -821,6 +821,20 @@ FoldStepsParams fold_one(voila_model_t m, const float* w, const float* b, int nf
 }
 }  // namespace
 
+namespace {
+// Whether an update's first stage runs on half tiles: networks of width 65 to
+// 256 (the 32-row tiles split over four waves).  In binary32 at every size (N =
+// 64: 88 -> 38 us for the whole update, 4,096: 103 -> 53, 8,192: 120 -> 94,
+// 65,536: 480 -> 446).  In bfloat16, where reading the weights for half as many
+// particles costs more than the products, while the chip holds all of them at
+// two blocks per CU (300: 31 -> 24, 4,096: 44 -> 33, 8,192: 62 -> 58; beyond,
+// 13,000: 69 -> 71 and 65,536: 116 -> 150).
+bool half_tiles(voila_model_t m, int N) {
+    if (pass_tiles_per_block(m->shape) != 1 || m->lik_split) return false;
+    return m->dt == DT_F32 || (N + 15) / 16 <= 2 * m->cus;
+}
+}  // namespace
+
 size_t voila_update_workspace_size(voila_model_t m, int32_t N) {
     if (!m || N < 1) return 0;
     return carve_update(nullptr, m->width, N, m->d_s).bytes;
@@ -843,11 +857,15 @@ voila_status_t voila_update(voila_model_t m, const float* d_states, const double
     DeviceGuard guard(m->device);
     if (!guard.ok) return fail(VOILA_ERR_DEVICE, "hipSetDevice failed");
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    VOILA_CHECK_HIP(launch_fold_steps(
-        fold_one(m, m->fold_w_trans, m->fold_b_trans, m->nf_trans, d_action, nullptr, w.b0_trans, d_status), s));
-    VOILA_CHECK_HIP(launch_fold_steps(
-        fold_one(m, m->fold_w_lik, m->fold_b_lik, m->nf_lik, d_action, d_obs, w.b0_lik, d_status, m->lik_width),
-        s));
+    const FoldStepsParams ft =
+        fold_one(m, m->fold_w_trans, m->fold_b_trans, m->nf_trans, d_action, nullptr, w.b0_trans, d_status);
+    const FoldStepsParams fl =
+        fold_one(m, m->fold_w_lik, m->fold_b_lik, m->nf_lik, d_action, d_obs, w.b0_lik, d_status, m->lik_width);
+    const bool half = half_tiles(m, N);
+    if (!half) {
+        VOILA_CHECK_HIP(launch_fold_steps(ft, s));
+        VOILA_CHECK_HIP(launch_fold_steps(fl, s));
+    }
     ProposeParams p{};
     p.trans = m->trans_upd;
     p.lik = m->lik;
@@ -870,6 +888,9 @@ voila_status_t voila_update(voila_model_t m, const float* d_states, const double
         VOILA_CHECK_HIP(launch_propose_split(m->shape, m->dt, p, want < cap ? want : cap, s));
         const int lcap = m->cus * m->lik_bpc;
         VOILA_CHECK_HIP(launch_lik_rows(m->shape, m->dt, p, n_tiles < lcap ? n_tiles : lcap, s));
+    } else if (half) {
+        const int want = (N + 15) / 16, cap = 2 * m->cus;
+        VOILA_CHECK_HIP(launch_propose_half(m->shape, m->dt, ProposeHalfParams{p, ft, fl}, want < cap ? want : cap, s));
     } else {
         const int tpb = pass_tiles_per_block(m->shape);
         const int want = (n_tiles + tpb - 1) / tpb;

@@ -189,8 +189,10 @@ __device__ __forceinline__ void propose_tile(const NetPtrs& PT, const NetPtrs& P
 
 template <int DT, int D_S, int D_W, int WIDTH, int NHID, int MODE>
 __global__ __launch_bounds__(256) void propose_kernel(ProposeParams p) {
-    if constexpr (!generic_compiled(DT, WIDTH, NHID)) {
-        return;  // refused at model creation (binary32 wider than 256) or run by the split rollout kernel
+    if constexpr (!generic_compiled(DT, WIDTH, NHID) || (MODE == kSplit && DT == DT_F32)) {
+        // refused at model creation (binary32 wider than 256) or run by the
+        // split rollout kernel; binary32 up to 256 runs on half tiles
+        return;
     } else {
     constexpr bool WLDS = MODE == kResident;
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -211,6 +213,308 @@ __global__ __launch_bounds__(256) void propose_kernel(ProposeParams p) {
     } else {
         for (int tile = blockIdx.x * wpb + (threadIdx.x >> 6); tile < n_tiles; tile += gridDim.x * wpb)
             propose_tile<DT, D_S, D_W, WIDTH, NHID>(PT, PL, p, tile, true, lane, g, col);
+    }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// update stage 1 on half tiles
+// ---------------------------------------------------------------------------
+// A belief of 4,096 particles is 128 tiles of 32: half the CUs of the chip, one
+// wave per SIMD.  Here a block advances 16 particles with one wave per 32 rows
+// of a hidden layer (two 16x16 products per k-step; for width 256 eight waves,
+// two per SIMD), on the weight fragments as the 32-row tiles are packed: lane
+// (m, g4) of a product over two packed k-steps reads rows 2 m and 2 m + 1 (one
+// load for both) of k-step g4 / 2, half g4 % 2.  Each product sums its k values
+// in ascending order and the output layer's quarters are added in wave order,
+// so the results are the tiles' bit for bit.  The weights come as one sequence
+// over the layers of both networks, kHalfDepth k-step pairs ahead and across
+// the layer barriers; the first layer's action and observation are folded by
+// the block itself (256 + 256 rows by 512 threads) while the first fragments
+// arrive, instead of by two launches before it.  Bound by the chain of k-steps
+// of the six hidden products and the layer barriers (matrix cores 40 % busy):
+// 4,096 particles in binary32 33.8 us, 76 + 10 on 32-row tiles.
+template <int DT> struct HalfOps;
+template <> struct HalfOps<DT_F32> {
+    static constexpr int GROUP = 4;  // k-step pairs per 16-byte B operand read
+    typedef f32x2 Weights;           // rows 2 m and 2 m + 1
+    typedef float Fragment;
+    static constexpr int DEPTH = 16;
+    __device__ static __forceinline__ float row(const Weights& w, int h) { return w[h]; }
+    __device__ static __forceinline__ float b(const u32x4& v, int s) { return __builtin_bit_cast(f32x4, v)[s % 4]; }
+    __device__ static __forceinline__ f32x4 mul(float a, float b, f32x4 c) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    }
+    // LDS offset of slot s of half g of particle n
+    __device__ static __forceinline__ int slot(int s, int g, int n) {
+        return (((s / 8) * 4 + (s % 2) * 2 + g) * 16 + n) * 16 + (s / 2) % 4 * 4;
+    }
+    __device__ static __forceinline__ void put(char* p, float v) { *reinterpret_cast<float*>(p) = v; }
+    // ReLU of the wave's rows, stored where the next layer reads its B operands
+    __device__ static __forceinline__ void store(char* act, const f32x4 (&acc)[2], int tile, int n, int g4) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+                *reinterpret_cast<f32x2*>(act + (((2 * tile + g4 / 2) * 4 + 2 * h + a) * 16 + n) * 16 + 8 * (g4 % 2)) =
+                    (f32x2){relu_f32(acc[h][2 * a]), relu_f32(acc[h][2 * a + 1])};
+    }
+};
+template <> struct HalfOps<DT_BF16> {
+    static constexpr int GROUP = 1;
+    struct Weights {
+        bf16x8 r[2];
+    };
+    typedef bf16x8 Fragment;
+    static constexpr int DEPTH = 8;
+    __device__ static __forceinline__ bf16x8 row(const Weights& w, int h) { return w.r[h]; }
+    __device__ static __forceinline__ bf16x8 b(const u32x4& v, int) { return __builtin_bit_cast(bf16x8, v); }
+    __device__ static __forceinline__ f32x4 mul(bf16x8 a, bf16x8 b, f32x4 c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+    }
+    __device__ static __forceinline__ int slot(int s, int g, int n) {
+        return (((s / 16) * 4 + (s / 8 % 2) * 2 + g) * 16 + n) * 16 + s % 8 * 2;
+    }
+    __device__ static __forceinline__ void put(char* p, float v) { *reinterpret_cast<__bf16*>(p) = (__bf16)v; }
+    __device__ static __forceinline__ void store(char* act, const f32x4 (&acc)[2], int tile, int n, int g4) {
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+            *reinterpret_cast<uint2*>(act + ((tile * 4 + 2 * (g4 / 2) + a) * 16 + n) * 16 + 8 * (g4 % 2)) =
+                make_uint2(relu_bf16x2(acc[0][2 * a], acc[1][2 * a]), relu_bf16x2(acc[0][2 * a + 1], acc[1][2 * a + 1]));
+    }
+};
+
+template <class N> struct HalfNet {
+    static constexpr int IN_S = cdiv(N::IN_KS, 2), HID_S = N::HID_KS / 2;  // k-step pairs per layer
+    static constexpr int SEQ = IN_S + (N::NHID - 1) * HID_S;               // of the hidden layers
+    static constexpr int OUT_S = HID_S / 4;                                // of an output quarter
+    static constexpr int IN_BYTES = cdiv(IN_S, HalfOps<N::DT>::GROUP) * 1024;
+    static constexpr int ACT = cdiv(HID_S, HalfOps<N::DT>::GROUP) * 1024;
+    static_assert(N::CT == N::HT && N::HT % 4 == 0 && N::NO == 1, "layered networks of 4k tiles");
+};
+constexpr int kHalfPart = 4 * 32 * 16 * 4;  // the output quarters [quarter][feature][particle]
+
+// The weights of k-step pair n of the networks' sequence (N, then NN if there is one).
+template <class N, class NN, int n>
+__device__ __forceinline__ typename HalfOps<N::DT>::Weights half_weights(const char* f0, const char* next, uint32_t off) {
+    typedef typename HalfOps<N::DT>::Weights W;
+    constexpr int FB = N::FRAG_BYTES * N::HT;
+    if constexpr (n >= HalfNet<N>::SEQ) {
+        return half_weights<NN, NN, n - HalfNet<N>::SEQ>(next, next, off);
+    } else {
+        constexpr int s = n < HalfNet<N>::IN_S ? 2 * n : N::IN_KS + 2 * (n - HalfNet<N>::IN_S);
+        return *reinterpret_cast<const W*>(f0 + (size_t)s * FB + off);
+    }
+}
+
+// One network on the block's 16 particles: inputs at `in`, first-layer bias
+// `b0` (row order, LDS); the output quarters are left in `part` behind a
+// barrier, for quarter_sum.  `ring` holds pairs R0 .. of the sequence.
+template <class N, class NN, int R0, int D>
+__device__ __forceinline__ void half_net(typename HalfOps<N::DT>::Weights (&ring)[D], const NetPtrs& P,
+                                         const char* next, uint32_t off, const float* b0, const char* in, char* act,
+                                         float* part, int d_out, int lane, int wave) {
+    typedef HalfOps<N::DT> Ops;
+    typedef HalfNet<N> HN;
+    constexpr int FB = N::FRAG_BYTES;
+    const int m = lane & 15, g4 = lane >> 4;
+    const int quarter = wave & 3;
+    const char* fo = P.f0 + (size_t)(FragIdx<N>::out(0) + quarter * (N::HID_KS / 4)) * FB;
+    f32x4 acc[2];
+    auto bias = [&](const float* b) {
+        const f32x4 lo = *reinterpret_cast<const f32x4*>(b + 32 * wave + 8 * g4);
+        const f32x4 hi = *reinterpret_cast<const f32x4*>(b + 32 * wave + 8 * g4 + 4);
+        acc[0] = (f32x4){lo[0], lo[2], hi[0], hi[2]};
+        acc[1] = (f32x4){lo[1], lo[3], hi[1], hi[3]};
+    };
+    typename Ops::Fragment of[HN::OUT_S];
+    const int oh = wave >> 2;  // the output rows' half of this wave (waves 0 .. 3 take both if there are no others)
+    auto out_weights = [&](int h) {
+        const char* p = fo + opaque_zero();
+        const int off = (g4 >> 1) * FB + (g4 & 1) * (FB / 2) + (16 * h + m) * (FB / 64);
+#pragma unroll
+        for (int s = 0; s < HN::OUT_S; ++s)
+            of[s] = *reinterpret_cast<const typename Ops::Fragment*>(p + 2 * s * FB + off);
+    };
+    bias(b0);
+    static_for<N::NHID>([&](auto li) {
+        constexpr int l = decltype(li)::value;
+        constexpr int KS = l == 0 ? HN::IN_S : HN::HID_S, n0 = l == 0 ? 0 : HN::IN_S + (l - 1) * HN::HID_S;
+        constexpr int NG = cdiv(KS, Ops::GROUP);
+        const char* src = l == 0 ? in : act + (l - 1) % 2 * HN::ACT;
+        auto operand = [&](int q) { return *reinterpret_cast<const u32x4*>(src + (q * 64 + lane) * 16); };
+        u32x4 b[2];
+        b[0] = operand(0);
+        f32x4 nb[2];
+        if constexpr (l + 1 < N::NHID) {
+            const float* bh = P.bh + l * N::WIDTH + 32 * wave + opaque_zero();
+            nb[0] = *reinterpret_cast<const f32x4*>(bh + 8 * g4);
+            nb[1] = *reinterpret_cast<const f32x4*>(bh + 8 * g4 + 4);
+        }
+        static_for<KS>([&](auto si) {
+            constexpr int s = decltype(si)::value, q = s / Ops::GROUP;
+            if constexpr (s % Ops::GROUP == 0 && q + 1 < NG) b[(q + 1) % 2] = operand(q + 1);
+            typename Ops::Weights w = ring[(R0 + n0 + s) % D];
+            // the second half of an odd last k-step pair holds other weights
+            if constexpr (l == 0 && 2 * s + 1 == N::IN_KS)
+                if (g4 >= 2) w = typename Ops::Weights{};
+#pragma unroll
+            for (int h = 0; h < 2; ++h) acc[h] = Ops::mul(Ops::row(w, h), Ops::b(b[q % 2], s), acc[h]);
+            if constexpr (n0 + s + D < HN::SEQ || !std::is_same<N, NN>::value)
+                ring[(R0 + n0 + s) % D] = half_weights<N, NN, n0 + s + D>(P.f0, next, off);
+            if constexpr (l + 1 == N::NHID && s == KS / 2) out_weights(oh);
+        });
+        Ops::store(act + l % 2 * HN::ACT, acc, wave, m, g4);
+        if constexpr (l + 1 < N::NHID) {
+            acc[0] = (f32x4){nb[0][0], nb[0][2], nb[1][0], nb[1][2]};
+            acc[1] = (f32x4){nb[0][1], nb[0][3], nb[1][1], nb[1][3]};
+        }
+        __syncthreads();
+    });
+    const char* src = act + (N::NHID - 1) % 2 * HN::ACT + quarter * (HN::ACT / 4);
+    for (int h = oh; 16 * h < 2 * cdiv(d_out, 2); h += N::HT / 4) {
+        if (h != oh) out_weights(h);
+        f32x4 o = {};
+        if (quarter == 0) o = *reinterpret_cast<const f32x4*>(P.bo + 16 * h + 4 * g4);
+#pragma unroll
+        for (int s = 0; s < HN::OUT_S; ++s)
+            o = Ops::mul(of[s], Ops::b(*reinterpret_cast<const u32x4*>(src + (s / Ops::GROUP * 64 + lane) * 16), s), o);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            part[(quarter * 32 + 2 * (8 * h + 4 * (g4 / 2) + i) + g4 % 2) * 16 + m] = o[i];
+    }
+    __syncthreads();
+}
+
+__device__ __forceinline__ float quarter_sum(const float* part, int f, int n) {
+    const float* p = part + f * 16 + n;
+    return ((p[0] + p[512]) + p[1024]) + p[1536];
+}
+
+template <int DT, int D_S, int D_W, int WIDTH, int NHID>
+struct HalfPropose {
+    typedef Net<DT, WIDTH, NHID, in_slots(DT, D_S, 0, D_W)> NTT;
+    typedef Net<DT, WIDTH, NHID, in_slots(DT, D_S, 0, 0)> NTL;
+    static constexpr int IN_T = HalfNet<NTT>::IN_BYTES, IN_L = HalfNet<NTL>::IN_BYTES;
+    static constexpr int COLS = 2 * kHalfCols * 4;  // folded values: action | action, observation
+    static constexpr int LDS = IN_T + IN_L + 2 * HalfNet<NTT>::ACT + kHalfPart + 2 * WIDTH * 4 + COLS;
+};
+
+template <int DT, int D_S, int D_W, int WIDTH, int NHID>
+__global__ __launch_bounds__(2 * WIDTH, 2) void propose_half_kernel(ProposeHalfParams hp) {
+    if constexpr (pass_mode<WIDTH>() != kSplit) {
+        return;  // the other networks run in propose_kernel or propose_split_kernel
+    } else {
+    typedef HalfPropose<DT, D_S, D_W, WIDTH, NHID> H;
+    typedef typename H::NTT NTT;
+    typedef typename H::NTL NTL;
+    typedef HalfOps<DT> Ops;
+    constexpr int T = 2 * WIDTH, SS = state_slots(D_S), D = Ops::DEPTH;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    char* const in_t = smem;
+    char* const in_l = in_t + H::IN_T;
+    char* const act = in_l + H::IN_L;
+    float* const part = reinterpret_cast<float*>(act + 2 * HalfNet<NTT>::ACT);
+    float* const b0 = part + kHalfPart / 4;  // [trans, lik][WIDTH]
+    float* const cols = b0 + 2 * WIDTH;      // [trans, lik][kHalfCols]
+    const ProposeParams& p = hp.p;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const NetPtrs PT = net_ptrs(p.trans.base, p.trans), PL = net_ptrs(p.lik.base, p.lik);
+    constexpr int FB = NTT::FRAG_BYTES;
+    const uint32_t off0 = (((lane >> 5) & 1) * NTT::HT + wave) * FB + ((lane >> 4) & 1) * (FB / 2) + 2 * (lane & 15) * (FB / 64);
+    typename Ops::Weights ring[D];
+    // addresses opaque to the compiler, or it computes every k-step's ahead of the loop
+    NetPtrs QT = PT, QL = PL;
+    uint32_t off;
+    auto fill = [&] {
+        QT.f0 = PT.f0 + opaque_zero();
+        QL.f0 = PL.f0 + opaque_zero();
+        off = off0;
+        asm volatile("" : "+v"(off));
+        static_for<D>([&](auto ni) {
+            constexpr int n = decltype(ni)::value;
+            ring[n] = half_weights<NTT, NTL, n>(QT.f0, QL.f0, off);
+        });
+    };
+    fill();
+    for (int e = tid; e < (H::IN_T + H::IN_L) / 4; e += T) reinterpret_cast<float*>(smem)[e] = 0.0f;
+    // folded values, checked and rounded once
+    if (tid < 2 * kHalfCols) {
+        const FoldStepsParams& f = tid < kHalfCols ? hp.fold_trans : hp.fold_lik;
+        const int c = tid % kHalfCols, na = f.n_actions > 0 ? f.n_actions : f.d_a;
+        float v = 0.0f;
+        bool bad = false;
+        if (c < na && f.n_actions > 0) {
+            int a = reinterpret_cast<const int32_t*>(f.cands)[0];
+            bad = a < 0 || a >= f.n_actions;
+            v = c == (bad ? 0 : a) ? 1.0f : 0.0f;
+        } else if (c < na + f.d_o) {
+            v = c < na ? reinterpret_cast<const float*>(f.cands)[c] : f.obs[c - na];
+            bad = !isfinite(v);
+            if (f.bf16) v = (float)(__bf16)v;
+        }
+        if (bad && f.status) f.status[0] = 1;
+        cols[tid] = v;
+    }
+    __syncthreads();
+    {
+        // thread r of each half folds row r
+        const int r = tid % WIDTH;
+        const FoldStepsParams& f = tid < WIDTH ? hp.fold_trans : hp.fold_lik;
+        const float* v = cols + (tid < WIDTH ? 0 : kHalfCols);
+        const float* w = f.w + (size_t)r * f.nf;
+        const int nc = (f.n_actions > 0 ? f.n_actions : f.d_a) + f.d_o;
+        float a = f.b[r];
+#pragma unroll 4
+        for (int c = 0; c < nc; ++c) a += w[c] * v[c];
+        b0[tid] = a;
+    }
+    const int n_half = (p.N + 15) / 16;
+    for (int u = blockIdx.x; u < n_half; u += gridDim.x) {
+        if (u != (int)blockIdx.x) fill();
+        // inputs: states of (particle, feature), noise of (particle, block of four, half)
+        float st[cdiv(32 * SS, T)];
+#pragma unroll
+        for (int k = 0; k < cdiv(32 * SS, T); ++k) {
+            const int e = tid + k * T, f = e % (2 * SS), n = e / (2 * SS), i = u * 16 + n;
+            st[k] = (n < 16 && i < p.N && f < D_S) ? p.states[(size_t)i * D_S + f] : 0.0f;
+            if (n < 16) Ops::put(in_t + Ops::slot(f / 2, f % 2, n), st[k]);
+        }
+        for (int e = tid; e < 16 * noise_slots(D_W); e += T) {
+            const int n = e % 16, g = e / 16 % 2, blk = e / 32, i = u * 16 + n, f = 4 * blk + 2 * g;
+            float z0, z1;
+            if (p.noise) {
+                z0 = (i < p.N && f < D_W) ? p.noise[(size_t)i * D_W + f] : 0.0f;
+                z1 = (i < p.N && f + 1 < D_W) ? p.noise[(size_t)i * D_W + f + 1] : 0.0f;
+            } else {
+                const uint4 w = philox4x32_10(make_uint4((uint32_t)i, 0u, 0u, (5u << 16) | (uint32_t)blk), p.key0, p.key1);
+                box_muller(g ? w.z : w.x, g ? w.w : w.y, z0, z1);
+            }
+            Ops::put(in_t + Ops::slot(SS + 2 * blk, g, n), z0);
+            Ops::put(in_t + Ops::slot(SS + 2 * blk + 1, g, n), z1);
+        }
+        __syncthreads();
+        half_net<NTT, NTL, 0, D>(ring, QT, QL.f0, off, b0, in_t, act, part, D_S, lane, wave);
+#pragma unroll
+        for (int k = 0; k < cdiv(32 * SS, T); ++k) {
+            const int e = tid + k * T, f = e % (2 * SS), n = e / (2 * SS), i = u * 16 + n;
+            if (n >= 16) continue;
+            const float s1 = st[k] + quarter_sum(part, f, n);
+            Ops::put(in_l + Ops::slot(f / 2, f % 2, n), s1);
+            if (i < p.N && f < D_S) p.prop[(size_t)i * D_S + f] = s1;
+        }
+        __syncthreads();
+        half_net<NTL, NTL, HalfNet<NTT>::SEQ % D, D>(ring, QL, QL.f0, off, b0 + WIDTH, in_l, act, part, 1, lane, wave);
+        if (tid < 16 && u * 16 + tid < p.N) {
+            const int i = u * 16 + tid;
+            const float l = quarter_sum(part, 0, tid);
+            if (p.loglik) p.loglik[i] = l;
+            if (!isfinite(l) && p.status) p.status[0] = 5;
+            double x = (double)l / p.lambda;
+            if (p.prior_w) x += log(p.prior_w[i]);
+            p.x[i] = x;
+        }
     }
     }
 }
@@ -419,6 +723,36 @@ hipError_t launch_propose(int shape, int dt, const ProposeParams& p, int blocks,
         break;                                                                                             \
     case id * 2 + 1:                                                                                       \
         hipLaunchKernelGGL((PROP_K(id, ds, na, da, dw, dox, dwz, w, nh, DT_BF16)), blocks, 256, lds, s, p); \
+        break;
+        VOILA_SHAPES(X)
+#undef X
+        default:
+            return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+#define PROPH_K(id, ds, na, da, dw, dox, dwz, w, nh, DT) propose_half_kernel<DT, ds, dw, w, nh>
+
+template <int DT, int D_S, int D_W, int W, int NH>
+constexpr size_t propose_half_lds() {
+    if constexpr (pass_mode<W>() != kSplit)
+        return 0;
+    else
+        return HalfPropose<DT, D_S, D_W, W, NH>::LDS;
+}
+
+hipError_t launch_propose_half(int shape, int dt, const ProposeHalfParams& p, int blocks, hipStream_t s) {
+    if (!pass_split(shape) || p.fold_trans.nf > kHalfCols || p.fold_lik.nf > kHalfCols) return hipErrorInvalidValue;
+    switch (shape * 2 + dt) {
+#define X(id, ds, na, da, dw, dox, dwz, w, nh)                                                                    \
+    case id * 2 + 0:                                                                                             \
+        hipLaunchKernelGGL((PROPH_K(id, ds, na, da, dw, dox, dwz, w, nh, DT_F32)), blocks, 2 * w,                 \
+                           (propose_half_lds<DT_F32, ds, dw, w, nh>()), s, p);                                    \
+        break;                                                                                                   \
+    case id * 2 + 1:                                                                                             \
+        hipLaunchKernelGGL((PROPH_K(id, ds, na, da, dw, dox, dwz, w, nh, DT_BF16)), blocks, 2 * w,                \
+                           (propose_half_lds<DT_BF16, ds, dw, w, nh>()), s, p);                                   \
         break;
         VOILA_SHAPES(X)
 #undef X

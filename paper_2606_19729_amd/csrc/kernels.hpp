@@ -106,6 +106,14 @@ struct FoldStepsParams {
     int32_t* status;     // or NULL
 };
 
+// The update's first stage on half tiles, with the folds of its first-layer
+// biases (at most kHalfCols columns each) done by its blocks.
+constexpr int kHalfCols = 64;
+struct ProposeHalfParams {
+    ProposeParams p;
+    FoldStepsParams fold_trans, fold_lik;
+};
+
 // Soft value of M nodes' candidate preferences (one workgroup per node).
 struct SoftValueParams {
     const float* Q;          // [M][K] preferences (plan's Q), or NULL when Qd is given
@@ -390,6 +398,7 @@ int ddim_blocks_per_cu(int shape, int dt);
 constexpr int kDdimMaxSteps = 4096;
 constexpr int kNceMaxBatch = 32768;  // B <= this (the score matrix holds B^2 binary32 values)
 constexpr int kPwMaxGroup = 8192;  // successors per group (one workgroup normalises and resamples a group)
+hipError_t launch_propose_half(int shape, int dt, const ProposeHalfParams& p, int blocks, hipStream_t s);
 hipError_t launch_propose(int shape, int dt, const ProposeParams& p, int blocks, hipStream_t s);
 // Update stage 1 of the models of VOILA_LIK_SHAPES: proposals through the split
 // transition kernel (two 32-particle tiles per block), then the likelihood of

@@ -297,6 +297,30 @@ def test_update_realistic():
     check_update(w)
 
 
+@pytest.mark.parametrize("compute", ["f32", "bf16"])
+@pytest.mark.parametrize("N", [1, 15, 16, 17, 33, 4097, 8192])
+def test_update_half_tiles(N, compute):
+    # blocks of 16 particles (their remainders, one and two blocks per CU)
+    # against the oracle (binary32), and the first N particles of a belief of
+    # 8,225: more half tiles than blocks (binary32), the 32-row tiles (bfloat16)
+    w = workloads.realistic(K=1, H=1, N=8225, seed=71)
+    o = oracle.draw_observation(w).astype(np.float32)
+    small = workloads.Workload(**{**w.__dict__, "states": w.states[:N], "true_index": 0})
+    noise = workloads.explicit_update_noise(w) if N % 2 else None
+    prior = np.random.default_rng(N).dirichlet(np.ones(N)) if N % 3 == 0 else None
+    m = V.Model(w.model, compute=compute)
+    say(f"update on half tiles N={N} {compute}")
+    args = dict(lam=w.lam, seed=w.update_seed, U=w.resample_u)
+    a = V.update(m, dev(small.states), w.update_action, o, noise=None if noise is None else dev(noise[:N]),
+                 prior_w=None if prior is None else dev(prior, torch.float64), **args)
+    b = V.update(m, dev(w.states), w.update_action, o, noise=None if noise is None else dev(noise), **args)
+    torch.cuda.synchronize()
+    for k in ["prop", "loglik"]:
+        assert np.array_equal(host(a[k]), host(b[k])[:N]), k
+    if compute == "f32":
+        check_update(small, noise=None if noise is None else noise[:N], prior=prior)
+
+
 def test_update_nonfinite_likelihood_sets_status():
     w = workloads.small(N=50)
     m_desc = w.model
