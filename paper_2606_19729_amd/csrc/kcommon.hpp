@@ -199,7 +199,10 @@ __device__ __forceinline__ void block_gather(T* dst, const T* src, const int* id
     }
 }
 
-__device__ void norm_res_body(const NormResParams& p, double* buf, double* redd, int* redi, int* ids) {
+// `slices` workgroups may share the work: each normalises all N values, the
+// first stores the weights, and each resamples and gathers its own positions.
+__device__ void norm_res_body(const NormResParams& p, double* buf, double* redd, int* redi, int* ids, int slice = 0,
+                              int slices = 1) {
     const int tid = threadIdx.x, N = p.N;
 
     if (!p.w_in) {
@@ -236,11 +239,11 @@ __device__ void norm_res_body(const NormResParams& p, double* buf, double* redd,
         for (int i = tid; i < N; i += kNormResThreads) {
             double w = buf[i] / S;
             buf[i] = w;
-            if (p.w_out) p.w_out[i] = w;
+            if (p.w_out && slice == 0) p.w_out[i] = w;
             sq += w * w;
         }
         const double SQ = block_sum_d(sq, redd);
-        if (tid == 0 && p.stats) {
+        if (tid == 0 && p.stats && slice == 0) {
             p.stats[0] = mx + log(S) - (p.uniform_prior ? log((double)N) : 0.0);
             p.stats[1] = 1.0 / SQ;
         }
@@ -300,8 +303,9 @@ __device__ void norm_res_body(const NormResParams& p, double* buf, double* redd,
     // systematic positions P_j = j 2^b + u; idx_j = first i with C_i > P_j
     const double step = ldexp(1.0, p.bits);
     const double u = (double)(p.U >> (32 - p.bits));
-    for (int j = tid; j < N; j += kNormResThreads) {
-        const double P = (double)j * step + u;
+    const int share = (N + slices - 1) / slices, j0 = slice * share, nj = max(0, min(N - j0, share));
+    for (int j = tid; j < nj; j += kNormResThreads) {
+        const double P = (double)(j0 + j) * step + u;
         int a = 0, b = N;
         while (a < b) {
             int mid = (a + b) >> 1;
@@ -309,16 +313,17 @@ __device__ void norm_res_body(const NormResParams& p, double* buf, double* redd,
             else a = mid + 1;
         }
         const int idx = a < N ? a : last;
-        if (p.idx_out) p.idx_out[j] = idx;
+        if (p.idx_out) p.idx_out[j0 + j] = idx;
         ids[j] = idx;
     }
     if (p.src && p.dst) {
         __syncthreads();
         const int rf = p.row_floats;
         if (rf % 4 == 0 && ((reinterpret_cast<uintptr_t>(p.src) | reinterpret_cast<uintptr_t>(p.dst)) & 15) == 0)
-            block_gather(reinterpret_cast<float4*>(p.dst), reinterpret_cast<const float4*>(p.src), ids, N, rf / 4);
+            block_gather(reinterpret_cast<float4*>(p.dst) + (size_t)j0 * (rf / 4),
+                         reinterpret_cast<const float4*>(p.src), ids, nj, rf / 4);
         else
-            block_gather(p.dst, p.src, ids, N, rf);
+            block_gather(p.dst + (size_t)j0 * rf, p.src, ids, nj, rf);
     }
 }
 

@@ -237,6 +237,28 @@ def test_resample_gathers_rows_and_flags_zero_mass():
     assert int(st.item()) == V.VOILA_ERR_NUMERIC
 
 
+@pytest.mark.parametrize("N", [255, 256, 257, 513, 8191])
+@pytest.mark.parametrize("rf", [1, 3, 16])
+def test_reweight_resample_shares_of_workgroups(N, rf):
+    # around the 256 positions of a workgroup; then with the indices written
+    # over the log-likelihoods, which one workgroup has to read before it writes
+    rng = np.random.default_rng(N + rf)
+    ll = rng.standard_normal(N).astype(np.float32) * 3
+    prior = rng.dirichlet(np.ones(N))
+    src = rng.standard_normal((N, rf)).astype(np.float32)
+    say(f"  reweight and resample N={N} rows of {rf}")
+    w_ref, st_ref = oracle.normalize(ll.astype(np.float64), 0.7, prior)
+    for over in [False, True]:
+        l = dev(ll)
+        out = V.reweight_resample(l, 0x51234567, lam=0.7, prior_w=dev(prior, torch.float64), src=dev(src), want_w=True,
+                                  idx=l.view(torch.int32) if over else None)
+        torch.cuda.synchronize()
+        assert max_rel(host(out["w"]), w_ref) <= 1e-12 and max_rel(host(out["stats"]), st_ref) <= 1e-12
+        idx = out["idx"].cpu().numpy()
+        assert np.array_equal(idx, oracle.resample(host(out["w"]), 0x51234567))
+        assert np.array_equal(out["dst"].cpu().numpy(), src[idx])
+
+
 # ----------------------------------------------------------------------------- observe / update
 def test_observe_matches_oracle():
     for w in [workloads.small(N=77), workloads.realistic(N=90, K=1, H=1)]:
