@@ -862,10 +862,7 @@ voila_status_t voila_update(voila_model_t m, const float* d_states, const double
     const FoldStepsParams fl =
         fold_one(m, m->fold_w_lik, m->fold_b_lik, m->nf_lik, d_action, d_obs, w.b0_lik, d_status, m->lik_width);
     const bool half = half_tiles(m, N);
-    if (!half) {
-        VOILA_CHECK_HIP(launch_fold_steps(ft, s));
-        VOILA_CHECK_HIP(launch_fold_steps(fl, s));
-    }
+    if (!half) VOILA_CHECK_HIP(launch_fold_pair(ft, fl, s));
     ProposeParams p{};
     p.trans = m->trans_upd;
     p.lik = m->lik;

@@ -19,6 +19,13 @@ __global__ __launch_bounds__(256) void fold_steps_kernel(FoldStepsParams p) {
     for (int j = blockIdx.y; j < p.rows; j += gridDim.y) fold_element(p, j, r);
 }
 
+// One row of two networks in one launch (an update's transition and likelihood).
+__global__ __launch_bounds__(256) void fold_pair_kernel(FoldStepsParams a, FoldStepsParams b) {
+    const int r = blockIdx.x * blockDim.x + threadIdx.x;
+    const FoldStepsParams& p = blockIdx.y ? b : a;
+    if (r < p.width) fold_element(p, 0, r);
+}
+
 // The same for many rows: a block stages its 256 rows of the columns in LDS,
 // transposed (read once, coalesced, instead of once per row with a stride of nf
 // floats), and the values of eight rows at a time, checked and rounded once
@@ -963,6 +970,12 @@ int norm_res_slices(const NormResParams& p) {
         for (const auto& i : in)
             if (!apart(o.at, o.bytes, i.at, i.bytes)) return 1;
     return (p.N + kNormResShare - 1) / kNormResShare;
+}
+
+hipError_t launch_fold_pair(const FoldStepsParams& a, const FoldStepsParams& b, hipStream_t s) {
+    const int width = a.width > b.width ? a.width : b.width;
+    hipLaunchKernelGGL(fold_pair_kernel, dim3((width + 255) / 256, 2), 256, 0, s, a, b);
+    return hipGetLastError();
 }
 
 hipError_t launch_norm_res(const NormResParams& p, hipStream_t s) {

@@ -366,6 +366,7 @@ constexpr int kNormResThreads = 1024;
 hipError_t launch_plan(int shape, int dt, const PlanParams& p, int blocks, hipStream_t s);
 hipError_t launch_q_reduce(const QReduceParams& p, hipStream_t s);
 hipError_t launch_fold_steps(const FoldStepsParams& p, hipStream_t s);
+hipError_t launch_fold_pair(const FoldStepsParams& a, const FoldStepsParams& b, hipStream_t s);
 // Grouped progressive-widening stages.
 constexpr int kFoldManyRows = 256;  // rows from which the folds take a kernel for many rows
 hipError_t launch_pw_prepare(const PwParams& p, const FoldStepsParams& fold, hipStream_t s);
