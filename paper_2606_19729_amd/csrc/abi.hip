@@ -687,7 +687,8 @@ voila_status_t voila_model_destroy(voila_model_t m) {
 // ---------------------------------------------------------------------------
 static size_t plan_ws(int N, int K) {
     const size_t n_tiles = ((size_t)N + 31) / 32;
-    return align_up((size_t)K * n_tiles * sizeof(float), 256);
+    const size_t tiles = (size_t)K * n_tiles;
+    return align_up(std::max(tiles, 32 * std::min<size_t>(tiles, kPlanHalfTiles)) * sizeof(float), 256);
 }
 
 size_t voila_plan_workspace_size(voila_model_t model, int32_t N, int32_t K, int32_t H) {
@@ -711,10 +712,12 @@ voila_status_t voila_plan(voila_model_t m, const float* d_states, const double* 
     if (o->reward_at != 0 && o->reward_at != 1) return fail(VOILA_ERR_INVALID_ARG, "reward_at must be 0 or 1");
     if (K == 0) return VOILA_OK;
     if (!d_states || !d_q_out || (!d_cands && H > 0)) return fail(VOILA_ERR_INVALID_ARG, "NULL device buffer");
-    if (!ws || ws_bytes < plan_ws(N, K)) return fail(VOILA_ERR_WORKSPACE, "plan workspace too small");
+    const int n_tiles = (N + 31) / 32;
+    const long tiles = (long)K * n_tiles;
+    if (!ws || ws_bytes < align_up((size_t)tiles * sizeof(float), 256))
+        return fail(VOILA_ERR_WORKSPACE, "plan workspace too small");
     DeviceGuard guard(m->device);
     if (!guard.ok) return fail(VOILA_ERR_DEVICE, "hipSetDevice failed");
-    const int n_tiles = (N + 31) / 32;
     PlanParams p{};
     p.net = m->trans_plan;
     p.states = d_states;
@@ -735,6 +738,22 @@ voila_status_t voila_plan(voila_model_t m, const float* d_states, const double* 
     p.crn = o->crn ? 1 : 0;
     p.reward_at = o->reward_at;
     for (int j = 0; j < 64; ++j) p.goal[j] = j < m->d_s ? o->h_goal[j] : 0.0f;
+    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    QReduceParams q{};
+    q.partials = p.partials;
+    q.q = d_q_out;
+    q.K = K;
+    q.n_tiles = n_tiles;
+    q.scale = d_belief_w ? 1.0f : (float)(1.0 / (double)N);
+    // Half tiles up to three 32-particle tiles per CU, where the tile kernel has
+    // less than a wave per SIMD (20 steps, tiles of 32: 128 30 against 83 us, 512
+    // 53 / 82, 1,024 98 / 83); the tile kernel also serves workspaces that hold
+    // the tiles' partial sums only.
+    if (plan_half_shape(m->shape, m->dt) && tiles <= std::min(kPlanHalfTiles, 3 * m->cus) &&
+        ws_bytes >= 32 * (size_t)tiles * sizeof(float)) {
+        VOILA_CHECK_HIP(launch_plan_half(m->shape, p, q, s));
+        return VOILA_OK;
+    }
     // units: (candidate, tile), or (candidate, group of tiles) for the paired
     // and the split evaluations
     const int tpu = plan_tiles_per_unit(m->shape, m->dt), upb = plan_units_per_block(m->shape, m->dt);
@@ -742,14 +761,7 @@ voila_status_t voila_plan(voila_model_t m, const float* d_states, const double* 
     const long want = (units + upb - 1) / upb;
     const long cap = (long)m->cus * m->plan_bpc;
     const int blocks = (int)(want < cap ? want : cap);
-    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     VOILA_CHECK_HIP(launch_plan(m->shape, m->dt, p, blocks, s));
-    QReduceParams q{};
-    q.partials = p.partials;
-    q.q = d_q_out;
-    q.K = K;
-    q.n_tiles = n_tiles;
-    q.scale = d_belief_w ? 1.0f : (float)(1.0 / (double)N);
     VOILA_CHECK_HIP(launch_q_reduce(q, s));
     return VOILA_OK;
 }

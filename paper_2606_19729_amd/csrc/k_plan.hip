@@ -179,6 +179,159 @@ __global__ __launch_bounds__(64 * kPlanSplitWaves) void plan_split_kernel(PlanPa
     }
 }
 
+// ---------------------------------------------------------------------------
+// small plans: one half tile per block
+// ---------------------------------------------------------------------------
+// A plan of few tiles is the latency of its steps: in plan_kernel one wave runs
+// a tile's 104 products of 64 cycles one after the other (32 candidates x 128
+// particles: 128 waves on 32 CUs, 4.2 us per step).  Here a block advances 16
+// particles of one candidate: each of its four waves produces 16 rows of a
+// hidden layer (16x16 products over two packed k-steps each, its weights in
+// registers for the whole rollout), every wave sums the four outputs of its
+// particles itself (lane (n, g4) feature g4 of particle n, one chain over the
+// hidden units, so nothing waits for a third barrier) and holds the states.
+// Noise, actions and first-layer bias rows are prepared kHalfSteps steps at a
+// time, one (particle, step) per thread.  All sums run in plan_kernel's order,
+// so the returns are the same bits; the contributions are left per particle
+// for q_reduce_half_kernel.
+constexpr int kHalfSteps = 16;
+
+template <int DT, int D_S, int D_A, int D_W, int WIDTH, int NHID>
+constexpr bool plan_half() {
+    return DT == DT_F32 && WIDTH == 64 && NHID == 2 && state_slots(D_S) == 2 && noise_slots(D_W) == 2 &&
+           (D_A == 0 || action_slots(D_A) == 2);
+}
+
+template <int DT, int D_S, int N_ACT, int D_A, int D_W, int WIDTH, int NHID>
+__global__ __launch_bounds__(256, 2) void plan_half_kernel(PlanParams p, float* contribs) {
+    if constexpr (!plan_half<DT, D_S, D_A, D_W, WIDTH, NHID>()) {
+        return;  // not chosen for the other networks
+    } else {
+    typedef Net<DT, WIDTH, NHID, in_slots(DT, D_S, D_A, D_W)> NT;
+    typedef FragIdx<NT> FI;
+    constexpr int IN_S = NT::IN_KS / 2, HID_S = NT::HID_KS / 2;  // k-step pairs
+    __shared__ __attribute__((aligned(16))) float act[2][WIDTH * 16];  // [k / 16][k % 4][particle][k / 4 % 4]
+    __shared__ float nz[kHalfSteps][64], av[kHalfSteps][4];
+    __shared__ __attribute__((aligned(16))) float bias[kHalfSteps][WIDTH];
+    const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g4 = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), tile = wave >> 1, rows = 16 * (wave & 1);
+    const NetPtrs P = net_ptrs(p.net.base, p.net);
+    const float* const W = reinterpret_cast<const float*>(P.f0);
+    const int f_lane = (g4 & 1) * 32 + rows + n, c_lane = g4 >> 1;
+    float w0[IN_S], w1[HID_S], wo[WIDTH];
+#pragma unroll
+    for (int s = 0; s < IN_S; ++s) w0[s] = W[FI::first(2 * s + c_lane, tile) * 64 + f_lane];
+#pragma unroll
+    for (int s = 0; s < HID_S; ++s) w1[s] = W[FI::hidden(1, 2 * s + c_lane, tile) * 64 + f_lane];
+#pragma unroll
+    for (int q = 0; q < WIDTH; ++q) wo[q] = W[FI::out(q / 2) * 64 + q % 2 * 32 + out_row(g4 / 2, g4 % 2)];
+    const f32x4 b1 = *reinterpret_cast<const f32x4*>(P.bh + 32 * tile + rows + 4 * g4);
+    const float bo = P.bo[out_row(g4 / 2, g4 % 2)];
+    const float goal = g4 < D_S ? p.goal[g4] : 0.0f;
+    // -|s - goal|^2, features f and f + 2 first, then both pairs (reward_to's order)
+    auto reward = [&](float x) {
+        const float e = x - goal, o = __uint_as_float(swap_halves(__float_as_uint(e)));
+        const float first = g4 < 2 ? e : o, second = g4 < 2 ? o : e;
+        const float part = __builtin_fmaf(second, second, first * first);
+        return -(part + __shfl_xor(part, 16));
+    };
+    auto store = [&](float* dst, const f32x4& a) {
+        float* at = dst + ((wave * 4 + g4 % 2) * 16 + n) * 4 + 2 * (g4 / 2);
+        *reinterpret_cast<f32x2*>(at) = (f32x2){relu_f32(a[0]), relu_f32(a[2])};
+        *reinterpret_cast<f32x2*>(at + 128) = (f32x2){relu_f32(a[1]), relu_f32(a[3])};
+    };
+    const int n_half = 2 * p.n_tiles;
+    const int u = blockIdx.x;
+    const int k = u / n_half, half = u - k * n_half, i = half * 16 + n;
+    const bool valid = i < p.N;
+    float st = valid && g4 < D_S ? p.states[(size_t)i * D_S + g4] : 0.0f;
+    float G = 0.0f;
+    double disc = 1.0;
+    for (int t0 = 0; t0 < p.H; t0 += kHalfSteps) {
+        const int tn = min(kHalfSteps, p.H - t0);
+        // every wave is past the second barrier of the previous step, after
+        // which it reads none of these
+        if (const int j = tid / 16, m = tid % 16, t = t0 + j; j < tn) {
+            const int im = half * 16 + m;
+            float z[4];
+            if (p.noise) {
+                const float* src = p.noise + (((size_t)k * p.N + (im < p.N ? im : 0)) * p.H + t) * D_W;
+#pragma unroll
+                for (int f = 0; f < 4; ++f) z[f] = f < D_W ? src[f] : 0.0f;
+            } else {
+                const uint4 w = philox4x32_10(make_uint4((uint32_t)im, p.crn ? 0u : (uint32_t)k, (uint32_t)t, 3u << 16),
+                                              p.key0, p.key1);
+                box_muller(w.x, w.y, z[0], z[1]);
+                box_muller(w.z, w.w, z[2], z[3]);
+            }
+            // slot s of lane group g is feature 2 g + s, k = 2 s + g
+#pragma unroll
+            for (int f = 0; f < 4; ++f) nz[j][(2 * (f % 2) + f / 2) * 16 + m] = z[f];
+            const float* b0 = P.b0;
+            if (N_ACT > 0) {
+                int a = reinterpret_cast<const int32_t*>(p.cands)[(size_t)k * p.H + t];
+                if (a < 0 || a >= N_ACT) {
+                    if (p.status && m == 0) p.status[0] = 1;
+                    a = 0;
+                }
+                b0 += (size_t)a * p.net.b0_stride;
+            }
+            *reinterpret_cast<f32x4*>(&bias[j][4 * m]) = *reinterpret_cast<const f32x4*>(b0 + 4 * m);
+            if (D_A > 0 && m < 4)
+                av[j][m] = m < D_A ? reinterpret_cast<const float*>(p.cands)[((size_t)k * p.H + t) * D_A + m] : 0.0f;
+        }
+        __syncthreads();
+        f32x4 acc;
+        float z, a = 0.0f;
+        auto inputs = [&](int j) {
+            acc = *reinterpret_cast<const f32x4*>(&bias[j][32 * tile + rows + 4 * g4]);
+            z = nz[j][lane];
+            if (D_A > 0) a = av[j][g4];
+        };
+        inputs(0);
+        for (int j = 0; j < tn; ++j) {
+            float r = 0.0f;
+            if (p.reward_at) r = reward(st);
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w0[0], st, acc, 0, 0, 0);
+            if (D_A > 0) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w0[1], a, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w0[IN_S - 1], z, acc, 0, 0, 0);
+            store(act[0], acc);
+            __syncthreads();
+            f32x4 h = b1;
+#pragma unroll
+            for (int q = 0; q < HID_S / 4; ++q) {
+                const f32x4 b = *reinterpret_cast<const f32x4*>(&act[0][(q * 64 + lane) * 4]);
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+                    h = __builtin_amdgcn_mfma_f32_16x16x4f32(w1[4 * q + s], b[s], h, 0, 0, 0);
+            }
+            store(act[1], h);
+            __syncthreads();
+            if (j + 1 < tn) inputs(j + 1);
+            float o = bo;
+#pragma unroll
+            for (int q = 0; q < WIDTH / 16; ++q) {
+                f32x4 v[4];
+#pragma unroll
+                for (int g = 0; g < 4; ++g) v[g] = *reinterpret_cast<const f32x4*>(&act[1][((q * 4 + g) * 16 + n) * 4]);
+#pragma unroll
+                for (int s = 0; s < 16; ++s) o = __builtin_fmaf(wo[16 * q + s], v[s % 4][s / 4], o);
+            }
+            st += o;
+            if (p.traj && valid && wave == 0 && g4 < D_S)
+                p.traj[(((size_t)k * p.N + i) * p.H + t0 + j) * D_S + g4] = st;
+            if (!p.reward_at) r = reward(st);
+            G = __builtin_fmaf((float)disc, r, G);
+            disc *= p.gamma;
+        }
+    }
+    if (wave == 0 && g4 == 0) {
+        if (p.returns && valid) p.returns[(size_t)k * p.N + i] = G;
+        contribs[(size_t)u * 16 + n] = valid ? (p.belief_w ? (float)p.belief_w[i] * G : G) : 0.0f;
+    }
+    }
+}
+
 // Many planning instances of one network shape in one persistent launch.
 // The work list holds block items (instance, first tile unit, number of
 // units): a block takes items from a queue (atomic counter, list sorted by
@@ -237,6 +390,24 @@ __global__ __launch_bounds__(256) void q_reduce_kernel(QReduceParams p) {
     if (k >= p.K) return;
     float s = 0.0f;
     for (int j = lane; j < p.n_tiles; j += 64) s += p.partials[(size_t)k * p.n_tiles + j];
+    s += __shfl_xor(s, 32);
+    s = sum32(s);
+    if (lane == 0) p.q[k] = s * p.scale;
+}
+
+// q_reduce_kernel's sums from the particles' contributions [K][32 n_tiles]: a
+// block per candidate forms the tiles' partial sums first.
+__global__ __launch_bounds__(256) void q_reduce_half_kernel(QReduceParams p) {
+    __shared__ float part[kPlanHalfTiles];
+    const int lane = threadIdx.x & 63, k = blockIdx.x;
+    for (int j = threadIdx.x >> 5; j < p.n_tiles; j += 8) {
+        const float v = sum32(p.partials[((size_t)k * p.n_tiles + j) * 32 + (threadIdx.x & 31)]);
+        if ((threadIdx.x & 31) == 0) part[j] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    float s = 0.0f;
+    for (int j = lane; j < p.n_tiles; j += 64) s += part[j];
     s += __shfl_xor(s, 32);
     s = sum32(s);
     if (lane == 0) p.q[k] = s * p.scale;
@@ -431,6 +602,39 @@ int plan_batch_blocks_per_cu(int shape, int dt, int wpb, size_t lds) {
 hipError_t launch_q_reduce_batch(const QReduceParams* d_qs, int n_inst, int max_k, hipStream_t s) {
     if (n_inst == 0 || max_k == 0) return hipSuccess;
     hipLaunchKernelGGL(q_reduce_batch_kernel, dim3((max_k + 3) / 4, n_inst), 256, 0, s, d_qs);
+    return hipGetLastError();
+}
+
+#define PLANH_K(id, ds, na, da, dw, dox, dwz, w, nh) plan_half_kernel<DT_F32, ds, na, da, dw, w, nh>
+
+bool plan_half_shape(int shape, int dt) {
+    if (dt != DT_F32) return false;
+    switch (shape) {
+#define X(id, ds, na, da, dw, dox, dwz, w, nh) \
+    case id:                                   \
+        return plan_half<DT_F32, ds, (na > 0 ? 0 : da), dw, w, nh>();
+        VOILA_SHAPES(X)
+#undef X
+    }
+    return false;
+}
+
+hipError_t launch_plan_half(int shape, const PlanParams& p, const QReduceParams& q, hipStream_t s) {
+    const int blocks = 2 * p.K * p.n_tiles;
+    if (p.n_tiles > kPlanHalfTiles) return hipErrorInvalidValue;
+    float* contribs = const_cast<float*>(q.partials);
+    switch (shape) {
+#define X(id, ds, na, da, dw, dox, dwz, w, nh)                                                                          \
+    case id:                                                                                                           \
+        hipLaunchKernelGGL((PLANH_K(id, ds, na, (na > 0 ? 0 : da), dw, dox, dwz, w, nh)), blocks, 256, 0, s, p, contribs); \
+        break;
+        VOILA_SHAPES(X)
+#undef X
+        default:
+            return hipErrorInvalidValue;
+    }
+    if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    hipLaunchKernelGGL(q_reduce_half_kernel, p.K, 256, 0, s, q);
     return hipGetLastError();
 }
 

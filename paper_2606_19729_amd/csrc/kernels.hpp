@@ -365,6 +365,10 @@ constexpr int kNormResThreads = 1024;
 // Kernel launchers (return the launch status).
 hipError_t launch_plan(int shape, int dt, const PlanParams& p, int blocks, hipStream_t s);
 hipError_t launch_q_reduce(const QReduceParams& p, hipStream_t s);
+// Small plans on half tiles: contributions [K][32 n_tiles] at q.partials, then Q.
+constexpr int kPlanHalfTiles = 1024;  // most tiles of such a plan
+bool plan_half_shape(int shape, int dt);
+hipError_t launch_plan_half(int shape, const PlanParams& p, const QReduceParams& q, hipStream_t s);
 hipError_t launch_fold_steps(const FoldStepsParams& p, hipStream_t s);
 hipError_t launch_fold_pair(const FoldStepsParams& a, const FoldStepsParams& b, hipStream_t s);
 // Grouped progressive-widening stages.

@@ -237,6 +237,37 @@ def test_resample_gathers_rows_and_flags_zero_mass():
     assert int(st.item()) == V.VOILA_ERR_NUMERIC
 
 
+@pytest.mark.parametrize("net", ["small", "continuous"])
+@pytest.mark.parametrize("K,N,H", [(1, 1, 1), (3, 15, 15), (2, 33, 16), (5, 16, 17), (8, 100, 33), (768, 32, 4),
+                                   (769, 32, 4), (16, 1537, 2)])
+def test_small_plans_on_half_tiles(net, K, N, H):
+    # around the 16 particles of a block, the 16 prepared steps and the largest
+    # plans on half tiles, against the oracle, and against the tile kernel (the
+    # one that serves a workspace of the tiles' partial sums) bit for bit
+    w = getattr(workloads, net)(seed=K + N, K=K, N=N, H=H)
+    m = V.Model(w.model)
+    rng = np.random.default_rng(N)
+    S, C = dev(w.states), torch.as_tensor(w.cands, device="cuda")
+    noise = rng.standard_normal((K, N, H, w.model.d_w)).astype(np.float32)
+    bw = rng.dirichlet(np.ones(N))
+    tiles = K * ((N + 31) // 32)
+    say(f"  plan on half tiles {net} K={K} N={N} H={H}")
+    for opts in [dict(), dict(crn=True, reward_at=1), dict(noise=noise, belief_w=bw)]:
+        o = dict(opts)
+        if "noise" in o:
+            o.update(noise=dev(noise), belief_w=dev(bw, torch.float64))
+        a = V.plan(m, S, C, w.gamma, w.goal, seed=w.plan_seed, return_G=True, return_traj=True, **o)
+        small_ws = torch.empty((tiles * 4 + 255) // 256 * 256, dtype=torch.uint8, device="cuda")
+        b = V.plan(m, S, C, w.gamma, w.goal, seed=w.plan_seed, return_G=True, return_traj=True, workspace=small_ws, **o)
+        torch.cuda.synchronize()
+        for x, y in zip(a, b):
+            assert torch.equal(x, y)
+    ref = oracle.plan(w.model, w.states, w.cands, w.gamma, w.goal, seed=w.plan_seed)
+    q = V.plan(m, S, C, w.gamma, w.goal, seed=w.plan_seed)
+    torch.cuda.synchronize()
+    assert scaled_err(host(q), ref) <= TOL
+
+
 @pytest.mark.parametrize("N", [255, 256, 257, 513, 8191])
 @pytest.mark.parametrize("rf", [1, 3, 16])
 def test_reweight_resample_shares_of_workgroups(N, rf):
