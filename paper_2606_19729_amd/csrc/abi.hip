@@ -761,7 +761,7 @@ voila_status_t voila_plan(voila_model_t m, const float* d_states, const double* 
     const long want = (units + upb - 1) / upb;
     const long cap = (long)m->cus * m->plan_bpc;
     const int blocks = (int)(want < cap ? want : cap);
-    VOILA_CHECK_HIP(launch_plan(m->shape, m->dt, p, blocks, s));
+    VOILA_CHECK_HIP(launch_plan(m->shape, m->dt, p, blocks, cap, m->cus, s));
     VOILA_CHECK_HIP(launch_q_reduce(q, s));
     return VOILA_OK;
 }
@@ -893,8 +893,7 @@ voila_status_t voila_update(voila_model_t m, const float* d_states, const double
     p.key1 = (uint32_t)(o->seed >> 32);
     const int n_tiles = (N + 31) / 32;
     if (m->lik_split) {
-        const int want = (n_tiles + kPropSplitTiles - 1) / kPropSplitTiles, cap = m->cus * m->prop_bpc;
-        VOILA_CHECK_HIP(launch_propose_split(m->shape, m->dt, p, want < cap ? want : cap, s));
+        VOILA_CHECK_HIP(launch_propose_split(m->shape, m->dt, p, m->cus * m->prop_bpc, m->cus, s));
         const int lcap = m->cus * m->lik_bpc;
         VOILA_CHECK_HIP(launch_lik_rows(m->shape, m->dt, p, n_tiles < lcap ? n_tiles : lcap, s));
     } else if (half) {
@@ -1543,7 +1542,7 @@ voila_status_t voila_ddim_sample(voila_denoiser_t m, const float* d_states, cons
     const long tpb = ddim_tiles_per_block(m->shape);
     const long want = (tiles + tpb - 1) / tpb;
     const long cap = (long)m->cus * m->bpc;
-    VOILA_CHECK_HIP(launch_ddim(m->shape, m->dt, p, (int)(want < cap ? want : cap), s));
+    VOILA_CHECK_HIP(launch_ddim(m->shape, m->dt, p, (int)(want < cap ? want : cap), (int)cap, m->cus, s));
     return VOILA_OK;
 }
 

@@ -124,21 +124,21 @@ __global__ __launch_bounds__(256) void ddim_kernel(DdimParams p) {
 #endif
 constexpr int kDdimSplitWaves = VOILA_DDIM_SPLIT_WAVES, kDdimSplitTiles = VOILA_DDIM_SPLIT_TILES,
               kDdimSplitDepth = VOILA_DDIM_SPLIT_DEPTH;
-template <int DT, int D_X, int D_C, int WIDTH, int NHID>
+template <int DT, int D_X, int D_C, int WIDTH, int NHID, int ST>
 __global__ __launch_bounds__(64 * kDdimSplitWaves) void ddim_split_kernel(DdimParams p) {
     if constexpr (!net_compiled(DT, WIDTH) || WIDTH <= 64) {
         return;  // small networks run one tile per wave in ddim_kernel
     } else {
-    constexpr int ST = kDdimSplitTiles, NO = cdiv(D_X, 32);
+    constexpr int NO = cdiv(D_X, 32), D = ST > 1 ? kDdimSplitDepth : kSingleTileDepth;
     typedef Net<DT, WIDTH, NHID, in_slots(DT, D_X, 0, D_C), WIDTH / 32, NO> NT;
     constexpr int SS = state_slots(D_X), SW = noise_slots(D_C);
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int lane = threadIdx.x & 63, g = lane >> 5, col = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int n_groups = (p.N + 32 * ST - 1) / (32 * ST);
+    const int n_groups = (p.N + 32 * ST - 1) / (32 * ST);  // counted from tile 0
     const kconst float* coef = (const kconst float*)p.coef;
     const NetPtrs P = net_ptrs(p.net.base, p.net);
-    for (int grp = blockIdx.x; grp < n_groups; grp += gridDim.x) {
+    for (int grp = p.tile0 / ST + blockIdx.x; grp < n_groups; grp += gridDim.x) {
         float x[ST][SS], cond[ST][SW];
         bool valid[ST];
         int row[ST];
@@ -170,7 +170,7 @@ __global__ __launch_bounds__(64 * kDdimSplitWaves) void ddim_split_kernel(DdimPa
                 for (int s = 0; s < SW; ++s) slots[st][SS + s] = cond[st][s];
             }
             f32x16 v[ST * NO];
-            run_net_split_multi<NT, ST, kDdimSplitWaves, kDdimSplitDepth>(P, p.b0 + (size_t)t * WIDTH, slots, v, lane, g, wave, smem);
+            run_net_split_multi<NT, ST, kDdimSplitWaves, D>(P, p.b0 + (size_t)t * WIDTH, slots, v, lane, g, wave, smem);
             const float Am1 = coef[2 * t], B = coef[2 * t + 1];
             // state slot s holds feature 2 s + g: output tile s / 16, register s % 16
 #pragma unroll
@@ -193,7 +193,8 @@ __global__ __launch_bounds__(64 * kDdimSplitWaves) void ddim_split_kernel(DdimPa
 // launchers
 template <int W> constexpr int ddim_mode() { return W <= 64 ? kResident : kSplit; }
 #define DDIM_K(id, dx, dc, w, nh, DT) ddim_kernel<DT, dx, dc, w, nh, ddim_mode<w>()>
-#define DDIM_SK(id, dx, dc, w, nh, DT) ddim_split_kernel<DT, dx, dc, w, nh>
+#define DDIM_SK(id, dx, dc, w, nh, DT) ddim_split_kernel<DT, dx, dc, w, nh, kDdimSplitTiles>
+#define DDIM_S1(id, dx, dc, w, nh, DT) ddim_split_kernel<DT, dx, dc, w, nh, 1>
 
 int ddim_shape(int d_x, int d_c, int width, int n_hidden) {
 #define X(id, dx, dc, w, nh) \
@@ -223,12 +224,12 @@ bool ddim_split(int shape) {
     return false;
 }
 
-template <int DT, int D_X, int D_C, int W, int NH>
+template <int DT, int D_X, int D_C, int W, int NH, int ST = kDdimSplitTiles>
 constexpr size_t ddim_split_lds() {
     if constexpr (!net_compiled(DT, W)) {
         return 0;
     } else {
-        return (size_t)kDdimSplitTiles * SplitLds<Net<DT, W, NH, in_slots(DT, D_X, 0, D_C), W / 32, cdiv(D_X, 32)>>::ACT;
+        return (size_t)ST * SplitLds<Net<DT, W, NH, in_slots(DT, D_X, 0, D_C), W / 32, cdiv(D_X, 32)>>::ACT;
     }
 }
 int ddim_tiles_per_block(int shape) { return ddim_split(shape) ? kDdimSplitTiles : kWavesPerBlock; }
@@ -246,18 +247,39 @@ void launch_ddim_one(K k, bool split, size_t lds, int blocks, const DdimParams& 
     hipLaunchKernelGGL(k, blocks, split ? 64 * kDdimSplitWaves : 256, lds, s, p);
 }
 
-hipError_t launch_ddim(int shape, int dt, const DdimParams& p, int blocks, hipStream_t s) {
+// Split samplers: rounds of groups over the chip's `cap` blocks, then the
+// remaining tiles, singly if they are then one round.
+template <class KS, class K1>
+void launch_ddim_split(KS ks, K1 k1, size_t lds, size_t lds1, int cap, int cus,
+                       DdimParams p, hipStream_t s) {
+    const int n_tiles = (p.N + 31) / 32;
+    const int grouped = (int)split_grouped_tiles(n_tiles, kDdimSplitTiles, cap, cus);
+    if (grouped > 0) {
+        const int groups = (grouped + kDdimSplitTiles - 1) / kDdimSplitTiles;
+        DdimParams q = p;
+        if (grouped < n_tiles) q.N = 32 * grouped;
+        launch_ddim_one(ks, true, lds, groups < cap ? groups : cap, q, s);
+    }
+    if (grouped < n_tiles) {
+        p.tile0 = grouped;
+        launch_ddim_one(k1, true, lds1, n_tiles - grouped, p, s);
+    }
+}
+
+hipError_t launch_ddim(int shape, int dt, const DdimParams& p, int blocks, int cap, int cus, hipStream_t s) {
     switch (shape * 2 + dt) {
 #define X(id, dx, dc, w, nh)                                                                                       \
     case id * 2 + 0:                                                                                          \
         if (ddim_mode<w>() == kSplit)                                                                         \
-            launch_ddim_one(DDIM_SK(id, dx, dc, w, nh, DT_F32), true, ddim_split_lds<DT_F32, dx, dc, w, nh>(), blocks, p, s); \
+            launch_ddim_split(DDIM_SK(id, dx, dc, w, nh, DT_F32), DDIM_S1(id, dx, dc, w, nh, DT_F32),          \
+                              ddim_split_lds<DT_F32, dx, dc, w, nh>(), ddim_split_lds<DT_F32, dx, dc, w, nh, 1>(), cap, cus, p, s); \
         else                                                                                                  \
             launch_ddim_one(DDIM_K(id, dx, dc, w, nh, DT_F32), false, p.net.bytes, blocks, p, s);                  \
         break;                                                                                                \
     case id * 2 + 1:                                                                                          \
         if (ddim_mode<w>() == kSplit)                                                                         \
-            launch_ddim_one(DDIM_SK(id, dx, dc, w, nh, DT_BF16), true, ddim_split_lds<DT_BF16, dx, dc, w, nh>(), blocks, p, s); \
+            launch_ddim_split(DDIM_SK(id, dx, dc, w, nh, DT_BF16), DDIM_S1(id, dx, dc, w, nh, DT_BF16),        \
+                              ddim_split_lds<DT_BF16, dx, dc, w, nh>(), ddim_split_lds<DT_BF16, dx, dc, w, nh, 1>(), cap, cus, p, s); \
         else                                                                                                  \
             launch_ddim_one(DDIM_K(id, dx, dc, w, nh, DT_BF16), false, p.net.bytes, blocks, p, s);                 \
         break;

@@ -40,25 +40,25 @@ constexpr bool plan_split() {
 
 // LDS of the split rollout kernel beyond the activations: each owner wave's
 // first-layer operands and states ([slot][lane]), then the goal.
-template <class NT, int D_S>
+template <class NT, int D_S, int ST>
 struct PlanSplitLds {
-    static constexpr int IN = kPlanSplitTiles * SplitIn<NT>::BYTES;
-    static constexpr int STATE = kPlanSplitTiles * state_slots(D_S) * 64 * 4;
-    static constexpr int BYTES = kPlanSplitTiles * SplitLds<NT>::ACT + IN + STATE + 64 * 4;
+    static constexpr int IN = ST * SplitIn<NT>::BYTES;
+    static constexpr int STATE = ST * state_slots(D_S) * 64 * 4;
+    static constexpr int BYTES = ST * SplitLds<NT>::ACT + IN + STATE + 64 * 4;
 };
 
-template <int DT, int D_S, int N_ACT, int D_A, int D_W, int WIDTH, int NHID>
-__global__ __launch_bounds__(64 * kPlanSplitWaves) void plan_split_kernel(PlanParams p) {
+template <int DT, int D_S, int N_ACT, int D_A, int D_W, int WIDTH, int NHID, int ST>
+__global__ __launch_bounds__(64 * kPlanSplitWaves) void plan_split_kernel(PlanParams p, int unit0, int n_units) {
     if constexpr (!plan_split<DT, WIDTH, NHID>()) {
         return;  // the other networks run in plan_kernel
     } else {
-    constexpr int ST = kPlanSplitTiles;
+    constexpr int DEPTH = ST > 1 ? kPlanSplitDepth : kSingleTileDepth;
     constexpr int SS = state_slots(D_S), SA = action_slots(D_A), SW = noise_slots(D_W);
     // states wider than 32 come out of the network in two 32-row tiles: state
     // slot s is register s % 16 of output tile s / 16
     constexpr int NO = cdiv(D_S, 32);
     typedef Net<DT, WIDTH, NHID, in_slots(DT, D_S, D_A, D_W), WIDTH / 32, NO> NT;
-    typedef PlanSplitLds<NT, D_S> L;
+    typedef PlanSplitLds<NT, D_S, ST> L;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     char* const in_lds = smem + ST * SplitLds<NT>::ACT;
     const int lane = threadIdx.x & 63, g = lane >> 5, col = lane & 31;
@@ -84,11 +84,10 @@ __global__ __launch_bounds__(64 * kPlanSplitWaves) void plan_split_kernel(PlanPa
         return -(part + __shfl_xor(part, 32));
     };
     const int n_groups = (p.n_tiles + ST - 1) / ST;
-    const long n_units = (long)p.K * n_groups;
     const NetPtrs P = net_ptrs(p.net.base, p.net);
-    for (long u = blockIdx.x; u < n_units; u += gridDim.x) {
-        const int k = (int)(u / n_groups);
-        const int grp = (int)(u - (long)k * n_groups);
+    for (int u = unit0 + blockIdx.x; u < n_units; u += gridDim.x) {
+        const int k = u / n_groups;
+        const int grp = u - k * n_groups;
         const int tile = grp * ST + (owner ? wave : 0);
         const int i = tile * 32 + col;
         const bool valid = owner && i < p.N;
@@ -151,7 +150,7 @@ __global__ __launch_bounds__(64 * kPlanSplitWaves) void plan_split_kernel(PlanPa
                 b0 += (size_t)a * p.net.b0_stride;
             }
             float out[NO][16];
-            run_net_split_owned<NT, ST, kPlanSplitWaves, kPlanSplitDepth>(P, b0, in_lds, out, lane, g, wave, smem);
+            run_net_split_owned<NT, ST, kPlanSplitWaves, DEPTH>(P, b0, in_lds, out, lane, g, wave, smem);
             if (owner) {
                 float st[SS];
 #pragma unroll
@@ -445,15 +444,16 @@ size_t plan_stream_lds(int shape, int dt) {
 #define PROP_K(id, ds, na, da, dw, dox, dwz, w, nh, DT) propose_kernel<DT, ds, dw, w, nh, pass_mode<w>()>
 #define OBS_K(id, ds, na, da, dw, dox, dwz, w, nh, DT) observe_kernel<DT, ds, dwz, dox, w, nh, pass_mode<w>()>
 
-#define PLAN_SK(id, ds, na, da, dw, dox, dwz, w, nh, DT) plan_split_kernel<DT, ds, na, da, dw, w, nh>
+#define PLAN_SK(id, ds, na, da, dw, dox, dwz, w, nh, DT) plan_split_kernel<DT, ds, na, da, dw, w, nh, kPlanSplitTiles>
+#define PLAN_S1(id, ds, na, da, dw, dox, dwz, w, nh, DT) plan_split_kernel<DT, ds, na, da, dw, w, nh, 1>
 
-template <int DT, int D_S, int D_A, int D_W, int W, int NH>
+template <int DT, int D_S, int D_A, int D_W, int W, int NH, int ST = kPlanSplitTiles>
 constexpr size_t plan_split_lds() {
     if constexpr (!plan_split<DT, W, NH>()) {
         return 0;
     } else {
         typedef Net<DT, W, NH, in_slots(DT, D_S, D_A, D_W), W / 32, cdiv(D_S, 32)> NT;
-        return (size_t)PlanSplitLds<NT, D_S>::BYTES;
+        return (size_t)PlanSplitLds<NT, D_S, ST>::BYTES;
     }
 }
 
@@ -471,22 +471,38 @@ bool plan_split_shape(int shape, int dt) {
 }
 
 template <class K>
-void launch_plan_split_one(K k, size_t lds, int blocks, const PlanParams& p, hipStream_t s) {
+void launch_plan_split_one(K k, size_t lds, long blocks, const PlanParams& p, long unit0, long n_units, hipStream_t s) {
+    if (n_units <= unit0) return;
     if (lds > 65536) (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(k, blocks, 64 * kPlanSplitWaves, lds, s, p);
+    const long want = n_units - unit0;
+    hipLaunchKernelGGL(k, (int)(want < blocks ? want : blocks), 64 * kPlanSplitWaves, lds, s, p, (int)unit0, (int)n_units);
 }
 
-hipError_t launch_plan(int shape, int dt, const PlanParams& p, int blocks, hipStream_t s) {
+// Rounds of tile groups over the chip's `cap` blocks, then the tiles of the
+// remaining groups, singly if they are then one round.
+template <class KS, class K1>
+void launch_plan_split(KS ks, K1 k1, size_t lds, size_t lds1, long cap, int cus, const PlanParams& p, hipStream_t s) {
+    constexpr int ST = kPlanSplitTiles;
+    const long n_groups = (p.n_tiles + ST - 1) / ST, units = p.K * n_groups, tiles = (long)p.K * p.n_tiles;
+    const long whole = units / cap * cap, tile0 = whole / n_groups * p.n_tiles + whole % n_groups * ST;
+    const bool singly = tiles - tile0 <= cus;
+    launch_plan_split_one(ks, lds, cap, p, 0, singly ? whole : units, s);
+    if (singly) launch_plan_split_one(k1, lds1, cus, p, tile0, tiles, s);
+}
+
+hipError_t launch_plan(int shape, int dt, const PlanParams& p, int blocks, long cap, int cus, hipStream_t s) {
     if (plan_split_shape(shape, dt)) {
         switch (shape * 2 + dt) {
 #define X(id, ds, na, da, dw, dox, dwz, w, nh)                                                                      \
     case id * 2 + 0:                                                                                               \
-        launch_plan_split_one(PLAN_SK(id, ds, na, da, dw, dox, dwz, w, nh, DT_F32),                                 \
-                              plan_split_lds<DT_F32, ds, (na > 0 ? 0 : da), dw, w, nh>(), blocks, p, s);           \
+        launch_plan_split(PLAN_SK(id, ds, na, da, dw, dox, dwz, w, nh, DT_F32), PLAN_S1(id, ds, na, da, dw, dox, dwz, w, nh, DT_F32), \
+                          plan_split_lds<DT_F32, ds, (na > 0 ? 0 : da), dw, w, nh>(),                             \
+                          plan_split_lds<DT_F32, ds, (na > 0 ? 0 : da), dw, w, nh, 1>(), cap, cus, p, s);         \
         break;                                                                                                     \
     case id * 2 + 1:                                                                                               \
-        launch_plan_split_one(PLAN_SK(id, ds, na, da, dw, dox, dwz, w, nh, DT_BF16),                                \
-                              plan_split_lds<DT_BF16, ds, (na > 0 ? 0 : da), dw, w, nh>(), blocks, p, s);          \
+        launch_plan_split(PLAN_SK(id, ds, na, da, dw, dox, dwz, w, nh, DT_BF16), PLAN_S1(id, ds, na, da, dw, dox, dwz, w, nh, DT_BF16), \
+                          plan_split_lds<DT_BF16, ds, (na > 0 ? 0 : da), dw, w, nh>(),                             \
+                          plan_split_lds<DT_BF16, ds, (na > 0 ? 0 : da), dw, w, nh, 1>(), cap, cus, p, s);         \
         break;
             VOILA_SHAPES(X)
 #undef X

@@ -573,12 +573,13 @@ __global__ __launch_bounds__(512) void propose_batch_kernel(BatchProposeParams b
 // propose_tile) and writes its proposals s + f_T(s, a, w).
 constexpr int kPropSplitWaves = 8, kPropSplitDepth = 3;
 
-template <int DT, int D_S, int D_W, int WIDTH, int NHID>
+template <int DT, int D_S, int D_W, int WIDTH, int NHID, int ST>
 __global__ __launch_bounds__(64 * kPropSplitWaves) void propose_split_kernel(ProposeParams p) {
     if constexpr (!net_compiled(DT, WIDTH) || generic_compiled(DT, WIDTH, NHID)) {
         return;  // the other networks run in propose_kernel
     } else {
-    constexpr int ST = kPropSplitTiles, SS = state_slots(D_S), SW = noise_slots(D_W), NO = cdiv(D_S, 32);
+    constexpr int SS = state_slots(D_S), SW = noise_slots(D_W), NO = cdiv(D_S, 32);
+    constexpr int DEPTH = ST > 1 ? kPropSplitDepth : kSingleTileDepth;
     typedef Net<DT, WIDTH, NHID, in_slots(DT, D_S, 0, D_W), WIDTH / 32, NO> NT;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     char* const in_lds = smem + ST * SplitLds<NT>::ACT;
@@ -587,7 +588,7 @@ __global__ __launch_bounds__(64 * kPropSplitWaves) void propose_split_kernel(Pro
     const bool owner = wave < ST;
     const int n_groups = ((p.N + 31) / 32 + ST - 1) / ST;
     const NetPtrs P = net_ptrs(p.trans.base, p.trans);
-    for (int u = blockIdx.x; u < n_groups; u += gridDim.x) {
+    for (int u = p.tile0 / ST + blockIdx.x; u < n_groups; u += gridDim.x) {
         const int i = (u * ST + (owner ? wave : 0)) * 32 + col;
         const bool valid = owner && i < p.N;
         if (owner) {
@@ -614,7 +615,7 @@ __global__ __launch_bounds__(64 * kPropSplitWaves) void propose_split_kernel(Pro
             split_stage_inputs<NT>(in_lds + wave * SplitIn<NT>::BYTES, slots, lane);
         }
         float d[NO][16];
-        run_net_split_owned<NT, ST, kPropSplitWaves, kPropSplitDepth>(P, p.b0_trans, in_lds, d, lane, g, wave, smem);
+        run_net_split_owned<NT, ST, kPropSplitWaves, DEPTH>(P, p.b0_trans, in_lds, d, lane, g, wave, smem);
         if (valid)
 #pragma unroll
             for (int s = 0; s < SS; ++s) {
@@ -797,43 +798,61 @@ int lik_shape_hidden(int shape) {
     return 0;
 }
 
-#define PROPS_K(id, ds, na, da, dw, dox, dwz, w, nh, DT) propose_split_kernel<DT, ds, dw, w, nh>
+#define PROPS_K(id, ds, na, da, dw, dox, dwz, w, nh, DT) propose_split_kernel<DT, ds, dw, w, nh, kPropSplitTiles>
+#define PROPS_1(id, ds, na, da, dw, dox, dwz, w, nh, DT) propose_split_kernel<DT, ds, dw, w, nh, 1>
 
-template <int DT, int D_S, int D_W, int W, int NH>
+template <int DT, int D_S, int D_W, int W, int NH, int ST = kPropSplitTiles>
 constexpr size_t propose_split_lds() {
     if constexpr (!net_compiled(DT, W) || generic_compiled(DT, W, NH)) {
         return 0;
     } else {
         typedef Net<DT, W, NH, in_slots(DT, D_S, 0, D_W), W / 32, cdiv(D_S, 32)> NT;
-        return (size_t)kPropSplitTiles * (SplitLds<NT>::ACT + SplitIn<NT>::BYTES);
+        return (size_t)ST * (SplitLds<NT>::ACT + SplitIn<NT>::BYTES);
     }
 }
 
-hipError_t launch_propose_split(int shape, int dt, const ProposeParams& p, int blocks, hipStream_t s) {
+template <class K>
+void launch_propose_split_one(K k, size_t lds, int blocks, const ProposeParams& p, hipStream_t s) {
+    if (lds > 65536) (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL(k, blocks, 64 * kPropSplitWaves, lds, s, p);
+}
+
+// Rounds of tile groups over the chip's `cap` blocks, then the remaining
+// tiles, singly if they are then one round.
+template <class KS, class K1>
+void launch_propose_groups(KS ks, K1 k1, size_t lds, size_t lds1, int cap, int cus, ProposeParams p, hipStream_t s) {
+    const int n_tiles = (p.N + 31) / 32;
+    const int grouped = (int)split_grouped_tiles(n_tiles, kPropSplitTiles, cap, cus);
+    if (grouped > 0) {
+        const int groups = (grouped + kPropSplitTiles - 1) / kPropSplitTiles;
+        ProposeParams q = p;
+        if (grouped < n_tiles) q.N = 32 * grouped;
+        launch_propose_split_one(ks, lds, groups < cap ? groups : cap, q, s);
+    }
+    if (grouped < n_tiles) {
+        p.tile0 = grouped;
+        launch_propose_split_one(k1, lds1, n_tiles - grouped, p, s);
+    }
+}
+
+hipError_t launch_propose_split(int shape, int dt, const ProposeParams& p, int cap, int cus, hipStream_t s) {
     switch (shape * 2 + dt) {
-#define X(id, ds, na, da, dw, dox, dwz, w, nh)                                                                  \
-    case id * 2 + 0: {                                                                                         \
-        const size_t lds = propose_split_lds<DT_F32, ds, dw, w, nh>();                                          \
-        if (lds == 0) return hipErrorInvalidValue;                                                             \
-        if (lds > 65536)                                                                                       \
-            (void)hipFuncSetAttribute((const void*)PROPS_K(id, ds, na, da, dw, dox, dwz, w, nh, DT_F32),          \
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                   \
-        hipLaunchKernelGGL((PROPS_K(id, ds, na, da, dw, dox, dwz, w, nh, DT_F32)), blocks, 64 * kPropSplitWaves, \
-                           lds, s, p);                                                                         \
-        break;                                                                                                 \
-    }                                                                                                          \
-    case id * 2 + 1: {                                                                                         \
-        const size_t lds = propose_split_lds<DT_BF16, ds, dw, w, nh>();                                         \
-        if (lds == 0) return hipErrorInvalidValue;                                                             \
-        if (lds > 65536)                                                                                       \
-            (void)hipFuncSetAttribute((const void*)PROPS_K(id, ds, na, da, dw, dox, dwz, w, nh, DT_BF16),         \
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                   \
-        hipLaunchKernelGGL((PROPS_K(id, ds, na, da, dw, dox, dwz, w, nh, DT_BF16)), blocks, 64 * kPropSplitWaves, \
-                           lds, s, p);                                                                         \
-        break;                                                                                                 \
+#define V(id, ds, na, da, dw, dox, dwz, w, nh, DT)                                                                 \
+    if (propose_split_lds<DT, ds, dw, w, nh>() == 0) return hipErrorInvalidValue;                                  \
+    launch_propose_groups(PROPS_K(id, ds, na, da, dw, dox, dwz, w, nh, DT), PROPS_1(id, ds, na, da, dw, dox, dwz, w, nh, DT), \
+                          propose_split_lds<DT, ds, dw, w, nh>(), propose_split_lds<DT, ds, dw, w, nh, 1>(), cap, cus, p, s)
+#define X(id, ds, na, da, dw, dox, dwz, w, nh)                    \
+    case id * 2 + 0: {                                           \
+        V(id, ds, na, da, dw, dox, dwz, w, nh, DT_F32);          \
+        break;                                                   \
+    }                                                            \
+    case id * 2 + 1: {                                           \
+        V(id, ds, na, da, dw, dox, dwz, w, nh, DT_BF16);         \
+        break;                                                   \
     }
         VOILA_SHAPES(X)
 #undef X
+#undef V
         default:
             return hipErrorInvalidValue;
     }

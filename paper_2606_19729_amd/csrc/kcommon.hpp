@@ -335,6 +335,16 @@ template <int W> constexpr int pass_mode() { return W <= 64 ? kResident : W <= 2
 constexpr size_t kStreamLds = (size_t)VOILA_STREAM_NBUF * VOILA_STREAM_CHB;
 
 // Split-mode passes (one tile per block, LDS for activations and partials).
+// Tiles of a split evaluation (blocks of `st` tiles, `cap` of them at once) that
+// run in groups of st: whole rounds, and the rest too unless it fits the chip one
+// tile per block -- a block with one tile of a 1,024-wide network takes 0.65
+// of the time of one with two, as the weights' path into the CU, not the products, bounds both.
+inline long split_grouped_tiles(long n_tiles, int st, long cap, int cus) {
+    const long rest = n_tiles % (st * cap);
+    return rest <= cus ? n_tiles - rest : n_tiles;
+}
+constexpr int kSingleTileDepth = 4;  // k-steps of weights in flight of a block with one tile
+
 inline bool pass_split(int shape) { return kShapeInfo[shape].width > 64 && kShapeInfo[shape].width <= 256; }
 constexpr size_t kSplitLds = 48 * 1024;  // binary32 width 256: 32 KB activations + 16 KB partials
 template <class KernelT>

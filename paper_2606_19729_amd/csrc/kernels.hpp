@@ -79,6 +79,7 @@ struct ProposeParams {
     int N;
     double lambda;
     uint32_t key0, key1;
+    int tile0;               // first 32-particle tile of a split launch
 };
 
 // Observations of rows (k, i, t), k < K, i < N, t < H (K = H = 1: n plain rows).
@@ -204,6 +205,7 @@ struct NceParams {
 // output v): n_steps deterministic DDIM steps per sample.
 struct DdimParams {
     NetBlob net;          // state slots: x_tau; noise slots: the conditioning input
+    int tile0;            // first 32-sample tile of a split launch
     const float* states;  // [N][d_c] conditioning inputs
     const float* x1;      // [N][d_x] latent noise at tau = 1
     const float* b0;      // [n_steps][width] first-layer biases with the action and tau_k folded in
@@ -363,7 +365,8 @@ constexpr int kNormResMaxN = 8192;
 constexpr int kNormResThreads = 1024;
 
 // Kernel launchers (return the launch status).
-hipError_t launch_plan(int shape, int dt, const PlanParams& p, int blocks, hipStream_t s);
+// blocks: of the general kernel; cap: blocks the chip holds at once
+hipError_t launch_plan(int shape, int dt, const PlanParams& p, int blocks, long cap, int cus, hipStream_t s);
 hipError_t launch_q_reduce(const QReduceParams& p, hipStream_t s);
 // Small plans on half tiles: contributions [K][32 n_tiles] at q.partials, then Q.
 constexpr int kPlanHalfTiles = 1024;  // most tiles of such a plan
@@ -398,7 +401,7 @@ int ddim_in_slots(int shape, int dt);
 bool ddim_split(int shape);                        // evaluated by all waves of a block per group of tiles
 int ddim_tiles_per_block(int shape);
 hipError_t launch_ddim_prep(const DdimPrepParams& p, hipStream_t s);
-hipError_t launch_ddim(int shape, int dt, const DdimParams& p, int blocks, hipStream_t s);
+hipError_t launch_ddim(int shape, int dt, const DdimParams& p, int blocks, int cap, int cus, hipStream_t s);
 int ddim_blocks_per_cu(int shape, int dt);
 constexpr int kDdimMaxSteps = 4096;
 constexpr int kNceMaxBatch = 32768;  // B <= this (the score matrix holds B^2 binary32 values)
@@ -408,7 +411,7 @@ hipError_t launch_propose(int shape, int dt, const ProposeParams& p, int blocks,
 // Update stage 1 of the models of VOILA_LIK_SHAPES: proposals through the split
 // transition kernel (two 32-particle tiles per block), then the likelihood of
 // the proposals (one tile per block of four waves).
-hipError_t launch_propose_split(int shape, int dt, const ProposeParams& p, int blocks, hipStream_t s);
+hipError_t launch_propose_split(int shape, int dt, const ProposeParams& p, int cap, int cus, hipStream_t s);
 int propose_split_blocks_per_cu(int shape, int dt);
 constexpr int kPropSplitTiles = 2;
 hipError_t launch_lik_rows(int shape, int dt, const ProposeParams& p, int blocks, hipStream_t s);

@@ -239,3 +239,33 @@ def test_deep_large_counts_sampled(V):
     assert e_em.max() <= BOUND_ROLLOUT_EMUL
     qs = G.mean(axis=1)
     assert np.max(np.abs(q.cpu().numpy() - qs) / np.abs(qs)) <= 1e-5
+
+
+# ----------------------------------------------------------------------------- rounds of two tiles, then single ones
+@pytest.mark.parametrize("N", [33, 5472, 8192, 8225, 16419])
+def test_whole_rounds_then_single_tiles(V, N):
+    # blocks of two tiles (256 at once) for whole rounds and for a rest of more
+    # than 256 tiles, single tiles otherwise: the first rows of a belief come out
+    # the same bits whichever way their tile runs (5,472 x 3 candidates: 171
+    # tiles each, the rest starts inside the last candidate)
+    print(f"split evaluation, rounds and single tiles N={N}", flush=True)
+    n = 33
+    w = workloads.target_finding(seed=31, N=N, K=3, H=2)
+    m = V.Model(w.model, compute="bf16")
+    C = torch.as_tensor(w.cands, device="cuda")
+    o = (0.5 * np.random.default_rng(3).standard_normal(w.model.d_o)).astype(np.float32)
+    got = []
+    for rows in [n, N]:
+        q, G = V.plan(m, dev(w.states[:rows]), C, w.gamma, w.goal, seed=w.plan_seed, return_G=True)
+        up = V.update(m, dev(w.states[:rows]), w.update_action, o, lam=w.lam, seed=w.update_seed, U=1)
+        got.append((q, G, up["prop"], up["loglik"]))
+    torch.cuda.synchronize()
+    (_, Ga, pa, la), (q, G, p, l) = got
+    assert torch.equal(G[:, :n], Ga) and torch.equal(p[:n], pa) and torch.equal(l[:n], la)
+    assert torch.isfinite(G).all()
+    assert torch.allclose(q.double(), G.double().mean(1), rtol=1e-5, atol=0)
+    S, X1 = workloads.ddim_batch(N, seed=N)
+    den = V.Denoiser(workloads.denoiser(seed=33), 4, 4, 5, 0, compute="bf16")
+    x, xa = (V.ddim_sample(den, dev(S[:rows]), 3, dev(X1[:rows]), 2) for rows in [N, n])
+    torch.cuda.synchronize()
+    assert torch.isfinite(x).all() and torch.equal(x[:n], xa)
