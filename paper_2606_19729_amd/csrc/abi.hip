@@ -2411,8 +2411,11 @@ GradWs carve_grad(const voila_model_s* m, const voila_grad_opts_t* o, char* base
         return reinterpret_cast<float*>(p);
     };
     w.states = take((size_t)n_tiles * std::max(o->H, 1) * state_slots(m->d_s) * 64 * 4);
-    w.wpart = take((size_t)w.blocks * m->n_params * 4);
-    w.lpart = take((size_t)w.blocks * 4);
+    // (sized for a block per CU wherever that many tiles exist, so that the
+    // workspace of a larger batch always serves a smaller one)
+    const size_t rows = std::max(1, std::min(n_tiles, m->cus));
+    w.wpart = take(rows * m->n_params * 4);
+    w.lpart = take(rows * 4);
     w.apart = take((size_t)n_tiles * std::max(o->H, 1) * std::max(m->d_a, 1) * 4);
     w.bytes = off;
     return w;

@@ -263,3 +263,20 @@ def test_autograd_functions(V):
     _, g_ref, _ = oracle.rollout_grad(m, S0n, An, 6, oracle.DISTILL, targets=T, seed=31)
     got = np.concatenate([p.grad.numpy().ravel() for p in params])
     assert rel(got, flat_layers(g_ref)) <= TOL
+
+
+def test_workspace_sizes_grow_with_the_batch(V):
+    # a workspace made for a larger batch serves every smaller one, also where
+    # the number of workgroups falls (257 tiles run two per workgroup)
+    import ctypes
+    m, S0, A, _ = distill_inputs(32, 5)
+    vm = V.Model(m)
+    goal = (ctypes.c_float * 4)(0.0, 0.0, 0.0, 0.0)
+    s0, a = dev(S0), dev(A, torch.int32)
+    sizes = []
+    for tiles in [1, 2, 255, 256, 257, 300, 512, 513, 2048, 2049]:
+        o = V._GradOpts(32 * tiles, 5, 5, V._ptr(s0), V._ptr(a), 1, None, 0, V.VOILA_OBJ_DISTILL, V._ptr(s0), 1.0, goal,
+                        None, None, None)
+        sizes.append(int(V.lib.voila_rollout_grad_workspace_size(vm.handle, ctypes.byref(o))))
+    print("gradient workspaces", sizes, flush=True)
+    assert sizes[0] > 0 and all(x <= y for x, y in zip(sizes, sizes[1:]))
