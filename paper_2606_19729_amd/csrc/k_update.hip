@@ -957,9 +957,11 @@ hipError_t launch_fold_steps(const FoldStepsParams& p, hipStream_t s) {
     if (p.rows == 0) return hipSuccess;
     const size_t lds = (size_t)p.nf * (257 + kFoldRows) * sizeof(float);
     // from one row per CU on (below, a block per row fills no more CUs than this
-    // one's staging costs); the LDS without an attribute holds 61 columns, every
-    // compiled shape's
-    if (p.rows >= kFoldManyRows && lds <= 65536) {
+    // one's staging costs), and from 4,096 rows where they are narrower than the
+    // block (calls around a width-64 fold: 640 rows 89.4 against 90.3 us, 1,024
+    // 28.6 / 29.1, 4,096 100.5 / 98.9, 8,000 48.0 / 46.6); the LDS without an attribute holds 61
+    // columns, every compiled shape's
+    if (p.rows >= (p.width >= 256 ? kFoldManyRows : 4096) && lds <= 65536) {
         const int groups = (p.rows + kFoldRows - 1) / kFoldRows;
         hipLaunchKernelGGL(fold_rows_kernel, dim3((p.width + 255) / 256, groups < 512 ? groups : 512), 256, lds, s, p);
         return hipGetLastError();

@@ -191,3 +191,21 @@ def test_realistic_full_size_sampled(V):
         e_o = scaled_err(host(o[k, i]), ref_o)
         assert e_t <= TOL and e_o <= TOL, (k, i, e_t, e_o)
     print(f"  {len(pairs)} sampled rollouts within {TOL}", flush=True)
+
+
+@pytest.mark.parametrize("K,H", [(4095, 1), (4096, 1), (1171, 7)])
+def test_many_folded_rows(V, K, H):
+    # a first-layer bias row per (candidate, step): the largest count the kernel
+    # of a block per row takes, the smallest of the one for many rows, and a
+    # remainder of its eight rows; a bad value in the last row sets the status
+    for w in [workloads.small(seed=K, N=1, K=K, H=H), workloads.continuous(seed=K, N=1, K=K, H=H)]:
+        check_f32(V, w)
+    w = workloads.small(seed=K, N=1, K=K, H=H)
+    m = V.Model(w.model)
+    _, traj = V.plan(m, dev(w.states), cands_dev(w), w.gamma, w.goal, seed=1, return_traj=True)
+    bad = np.array(w.cands)
+    bad[-1, -1] = 5
+    st = torch.zeros(1, dtype=torch.int32, device="cuda")
+    V.plan_observe(m, traj, dev(bad, torch.int32), seed=1, status=st)
+    torch.cuda.synchronize()
+    assert int(st.item()) == V.VOILA_ERR_INVALID_ARG
