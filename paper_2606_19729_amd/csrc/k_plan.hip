@@ -7,6 +7,9 @@
 //                 evaluation, see device.hpp), with the noise drawn in registers
 //                 from Philox.  Small networks are staged in LDS once per block;
 //                 wide ones stream their fragments from L2.
+// plan_split_kernel  deep wide networks, each layer split over a block's waves.
+// plan_half_kernel   small plans, 16 particles per block (q_reduce_half_kernel
+//                 sums their contributions in q_reduce_kernel's order).
 // q_reduce_kernel fixed-order sum of the per-tile partial returns into Q.
 #include "plan_unit.hpp"
 

@@ -628,7 +628,7 @@ __global__ __launch_bounds__(64 * kPropSplitWaves) void propose_split_kernel(Pro
 
 // The likelihood of the proposals for those models, x = l / lambda (+ log
 // prior): the block's four waves split one 32-particle tile's layers
-// (run_net_split), as the update of width-256 networks does.
+// (run_net_split), as propose_kernel does at width 256.
 template <int DT, int D_S, int LW, int LNH>
 __global__ __launch_bounds__(256) void lik_rows_kernel(ProposeParams p) {
     static_assert(pass_mode<LW>() == kSplit, "likelihood widths above 64 and up to 256");
