@@ -1201,7 +1201,7 @@ PwWs carve_pw(char* base, voila_model_t m, int T, int M) {
     w.o_sel = reinterpret_cast<float*>(take((size_t)M * m->d_o * 4));
     w.b0_lik = reinterpret_cast<float*>(take((size_t)M * m->width * 4));
     w.tiles = reinterpret_cast<int32_t*>(take(((size_t)M + 1) * 4));
-    w.units = reinterpret_cast<int4*>(take(((size_t)T / 32 + M) * sizeof(int4)));
+    w.units = reinterpret_cast<int4*>(take((size_t)pw_unit_capacity(T, M) * sizeof(int4)));
     w.x = reinterpret_cast<double*>(take((size_t)T * 8));
     w.bytes = off;
     return w;

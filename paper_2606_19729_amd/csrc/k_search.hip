@@ -150,16 +150,8 @@ __global__ __launch_bounds__(64) void tree_backup_kernel(TreeParams p) {
 namespace {
 // Group m's successors [lo, lo + n) if the offsets are consistent and the
 // group fits one workgroup; otherwise the group is skipped and *status set.
-__device__ __forceinline__ bool pw_group(const PwParams& p, int m, int& lo, int& n) {
-    lo = p.seg[m];
-    const int hi = p.seg[m + 1];
-    n = hi - lo;
-    if (lo < 0 || hi < lo || hi > p.T || n > kPwMaxGroup) {
-        if (p.status) p.status[0] = 1;
-        n = 0;
-        return false;
-    }
-    return true;
+__device__ __forceinline__ void pw_group(const PwParams& p, int m, int& lo, int& n) {
+    if (!pw_rows(p.seg, m, p.T, lo, n) && p.status) p.status[0] = 1;
 }
 }  // namespace
 
@@ -171,8 +163,12 @@ __global__ __launch_bounds__(256) void pw_branch_kernel(PwParams p) {
     if (m >= p.M) return;
     int lo, n;
     pw_group(p, m, lo, n);
-    for (int q = l, nu = p.tiles[m + 1] - p.tiles[m]; q < nu; q += 32)
-        p.units[p.tiles[m] + q] = make_int4(m, lo + q * 32 * p.unit_tiles, lo + n, 0);
+    const int listed = p.tiles[p.M], at = p.tiles[m];
+    if (listed >= 0)  // at most as many units as there are records
+        for (int q = l, nu = pw_unit_count(n, 32 * p.unit_tiles); q < nu; q += 32) {
+            const PwUnit w = pw_unit(m, lo, n, q, 32 * p.unit_tiles);
+            p.units[at + q] = make_int4(w.group, w.first, w.end, 0);
+        }
     int wid = 0, br = -1;
     const int C = p.children[m];
     if (C < 0 || C > p.B) {
@@ -204,7 +200,8 @@ __global__ __launch_bounds__(256) void pw_branch_kernel(PwParams p) {
     }
 }
 
-// Block 0: exclusive prefix of the groups' likelihood work units.  The next
+// Block 0: exclusive prefix of the groups' likelihood work units, or -1 as its
+// last entry where they are not listed (pw_units.hpp).  The next
 // blocks: first successor of each group (the state a new branch's observation
 // is drawn at); the last ones: the observation network's bias rows (few groups;
 // many take fold_rows_kernel).  One launch, since none needs another's result.
@@ -224,33 +221,33 @@ __global__ __launch_bounds__(1024) void pw_prepare_kernel(PwParams p, FoldStepsP
         p.first[e] = n > 0 ? p.succ[(size_t)lo * p.d_s + c] : 0.0f;
         return;
     }
-    __shared__ int wtot[16];
+    __shared__ long wtot[16];
     const int tid = threadIdx.x, lane = tid & 63;
     const int per = (p.M + 1023) / 1024, rows = 32 * p.unit_tiles;
     const int a = tid * per, b = min(p.M, a + per);
-    int run = 0;
+    long run = 0;  // (groups that overlap may have more units than an int holds)
     for (int m = a; m < b; ++m) {
         int lo, n;
         pw_group(p, m, lo, n);
-        run += (n + rows - 1) / rows;
+        run += pw_unit_count(n, rows);
     }
-    int incl = run;
+    long incl = run;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
-        int o = __shfl_up(incl, d);
+        const long o = __shfl_up(incl, d);
         if (lane >= d) incl += o;
     }
     if (lane == 63) wtot[tid >> 6] = incl;
     __syncthreads();
-    int off = incl - run;
+    long off = incl - run;
     for (int w = 0; w < (tid >> 6); ++w) off += wtot[w];
     for (int m = a; m < b; ++m) {
         int lo, n;
         pw_group(p, m, lo, n);
-        p.tiles[m] = off;
-        off += (n + rows - 1) / rows;
+        p.tiles[m] = (int)off;
+        off += pw_unit_count(n, rows);
     }
-    if (tid == 1023) p.tiles[p.M] = off;
+    if (tid == 1023) p.tiles[p.M] = pw_listed(off, p.T, p.M);
 }
 
 // Likelihood of every successor against its group's chosen observation:
@@ -274,66 +271,76 @@ __global__ __launch_bounds__(256) void pw_lik_kernel(PwParams p) {
     const int wpb = blockDim.x >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const kconst int32_t* units = (const kconst int32_t*)p.units;
-    const long n_units = ((const kconst int32_t*)p.tiles)[p.M];
+    const int listed = ((const kconst int32_t*)p.tiles)[p.M];
     float* rowb = reinterpret_cast<float*>(smem + p.row_bias_lds) + wave * NTL::WIDTH;
     constexpr int RB = NTL::WIDTH / 64;  // bias floats per lane
     static_assert(NTL::WIDTH % 64 == 0 && RB <= 16, "bias row copy: whole lanes");
-    int nj[TPU];
-    bool nv[TPU];
-    float nst[TPU][SS], nbv[RB];
-    auto next_inputs = [&](long u) {
-        const bool ok = u < n_units;  // wave-uniform
-        const long at = ok ? 4 * u : 0;
-        const int4 rec = make_int4(units[at], units[at + 1], ok ? units[at + 2] : 0, 0);
-#pragma unroll
-        for (int q = 0; q < TPU; ++q) {
-            nj[q] = rec.y + 32 * q + col;
-            nv[q] = nj[q] < rec.z;
-#pragma unroll
-            for (int s = 0; s < SS; ++s) {
-                const int f = 2 * s + g;
-                nst[q][s] = (nv[q] && f < D_S) ? p.succ[(size_t)nj[q] * D_S + f] : 0.0f;
-            }
-        }
-        const float* brow = p.b0_lik + (size_t)rec.x * NTL::WIDTH;
-#pragma unroll
-        for (int q = 0; q < RB; ++q) nbv[q] = brow[q * 64 + lane];
-    };
     with_weights<NTL, MODE, 1, PAIRS ? VOILA_PLAN_STREAM_CHB : VOILA_STREAM_CHB>(smem, p.lik, [&](auto& src,
                                                                                             const NetPtrs& P) {
-        if (n_units > 0) next_inputs((long)blockIdx.x * wpb + wave);
-        // block-uniform loop (a streamed network's chunk barriers need every wave)
-        for (long ub = blockIdx.x; ub * wpb < n_units; ub += gridDim.x) {
-            float slots[TPU][NTL::IN_SLOTS];
-            int j[TPU];
-            bool valid[TPU];
+        // the units 0 .. n_units - 1 that unit_at gives
+        auto sweep = [&](long n_units, auto unit_at) {
+            if (n_units == 0) return;
+            int nj[TPU];
+            bool nv[TPU];
+            float nst[TPU][SS], nbv[RB];
+            auto next_inputs = [&](long u) {
+                const bool ok = u < n_units;  // wave-uniform
+                const PwUnit w = unit_at(ok ? u : 0);
+                const int left = ok ? w.end - w.first : 0;
 #pragma unroll
-            for (int q = 0; q < TPU; ++q) {
-                j[q] = nj[q];
-                valid[q] = nv[q];
+                for (int q = 0; q < TPU; ++q) {
+                    nj[q] = w.first + 32 * q + col;
+                    nv[q] = 32 * q + col < left;
 #pragma unroll
-                for (int s = 0; s < NTL::IN_SLOTS; ++s) slots[q][s] = 0.0f;
-#pragma unroll
-                for (int s = 0; s < SS; ++s) slots[q][s] = nst[q][s];
-            }
-#pragma unroll
-            for (int q = 0; q < RB; ++q) rowb[q * 64 + lane] = nbv[q];
-            next_inputs((ub + gridDim.x) * wpb + wave);
-            f32x16 o[TPU];
-            if constexpr (PAIRS) {
-                run_net_flat<NTL, 2, kPlanPassTiles>(src, P, rowb, slots, o, lane, g);
-            } else {
-                o[0] = run_net<NTL>(src, P, rowb, slots[0], lane, g);
-            }
-#pragma unroll
-            for (int q = 0; q < TPU; ++q)
-                if (g == 0 && valid[q]) {
-                    const float l = o[q][0];
-                    if (p.loglik) p.loglik[j[q]] = l;
-                    if (!isfinite(l) && p.status) p.status[0] = 5;
-                    p.x[j[q]] = (double)l / p.lambda;
+                    for (int s = 0; s < SS; ++s) {
+                        const int f = 2 * s + g;
+                        nst[q][s] = (nv[q] && f < D_S) ? p.succ[(size_t)nj[q] * D_S + f] : 0.0f;
+                    }
                 }
-        }
+                const float* brow = p.b0_lik + (size_t)w.group * NTL::WIDTH;
+#pragma unroll
+                for (int q = 0; q < RB; ++q) nbv[q] = brow[q * 64 + lane];
+            };
+            next_inputs((long)blockIdx.x * wpb + wave);
+            // block-uniform loop (a streamed network's chunk barriers need every wave)
+            for (long ub = blockIdx.x; ub * wpb < n_units; ub += gridDim.x) {
+                float slots[TPU][NTL::IN_SLOTS];
+                int j[TPU];
+                bool valid[TPU];
+#pragma unroll
+                for (int q = 0; q < TPU; ++q) {
+                    j[q] = nj[q];
+                    valid[q] = nv[q];
+#pragma unroll
+                    for (int s = 0; s < NTL::IN_SLOTS; ++s) slots[q][s] = 0.0f;
+#pragma unroll
+                    for (int s = 0; s < SS; ++s) slots[q][s] = nst[q][s];
+                }
+#pragma unroll
+                for (int q = 0; q < RB; ++q) rowb[q * 64 + lane] = nbv[q];
+                next_inputs((ub + gridDim.x) * wpb + wave);
+                f32x16 o[TPU];
+                if constexpr (PAIRS) {
+                    run_net_flat<NTL, 2, kPlanPassTiles>(src, P, rowb, slots, o, lane, g);
+                } else {
+                    o[0] = run_net<NTL>(src, P, rowb, slots[0], lane, g);
+                }
+#pragma unroll
+                for (int q = 0; q < TPU; ++q)
+                    if (g == 0 && valid[q]) {
+                        const float l = o[q][0];
+                        if (p.loglik) p.loglik[j[q]] = l;
+                        if (!isfinite(l) && p.status) p.status[0] = 5;
+                        p.x[j[q]] = (double)l / p.lambda;
+                    }
+            }
+        };
+        // (two loops: choosing between the forms in one took 0.8 % of the whole step)
+        if (listed >= 0)
+            sweep(listed, [&](long u) { return PwUnit{units[4 * u], units[4 * u + 1], units[4 * u + 2]}; });
+        else
+            sweep(pw_unlisted_units(p.M, 32 * TPU),
+                  [&](long u) { return pw_unlisted_unit(p.seg, p.T, u, 32 * TPU); });
     });
     }
 }

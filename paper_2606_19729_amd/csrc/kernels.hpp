@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "device.hpp"
+#include "pw_units.hpp"
 
 namespace voila {
 
@@ -168,8 +169,8 @@ struct PwParams {
     const float* o_new;       // [M][d_o] observation drawn at the first successor
     float* o_sel;             // [M][d_o] observation of the chosen branch (workspace)
     const float* b0_lik;      // [M][width] folded likelihood biases
-    int32_t* tiles;           // [M + 1] exclusive prefix of the groups' work-unit counts
-    int4* units;              // [units] group, first row, end of the group's rows of each likelihood work unit
+    int32_t* tiles;           // [M + 1] exclusive prefix of the groups' work-unit counts, -1 last if not listed
+    int4* units;              // [pw_unit_capacity] the listed work units (PwUnit)
     int unit_tiles;           // 32-row tiles per work unit (2: paired evaluation)
     uint32_t row_bias_lds;    // LDS offset of the per-wave bias rows (set by the launcher)
     double* x;                // [T] l / lambda
@@ -405,7 +406,6 @@ hipError_t launch_ddim(int shape, int dt, const DdimParams& p, int blocks, int c
 int ddim_blocks_per_cu(int shape, int dt);
 constexpr int kDdimMaxSteps = 4096;
 constexpr int kNceMaxBatch = 32768;  // B <= this (the score matrix holds B^2 binary32 values)
-constexpr int kPwMaxGroup = 8192;  // successors per group (one workgroup normalises and resamples a group)
 hipError_t launch_propose_half(int shape, int dt, const ProposeHalfParams& p, int blocks, hipStream_t s);
 hipError_t launch_propose(int shape, int dt, const ProposeParams& p, int blocks, hipStream_t s);
 // Update stage 1 of the models of VOILA_LIK_SHAPES: proposals through the split

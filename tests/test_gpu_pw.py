@@ -208,3 +208,55 @@ def test_groups_at_the_edges_of_tiles_and_workgroups(V, compute, copies):
     c["succ"] = (np.random.default_rng(67).standard_normal((sum(sizes), w.model.d_s)) * 0.8).astype(np.float32)
     print(f"pw step group edges {compute}, {len(sizes)} groups", flush=True)
     compare(V, w.model, c, compute)
+
+
+@pytest.mark.parametrize("compute", ["f32", "bf16"])
+@pytest.mark.parametrize("M", [3, 41])
+def test_offsets_that_fall_and_rise_again(V, compute, M):
+    # offsets 0, T, 0, T, ...: every second group holds all T successors, so
+    # the groups have more work units than successors / 32 + M.  The others
+    # are skipped with the status set; nothing past the workspace is written.
+    # All groups share one action, branch and offset, so the successors' values
+    # are the same whichever group writes them.
+    w = workloads.realistic(seed=68, N=8, K=1, H=1)
+    model, T = w.model, 8192
+    c = make_case(model, 68, M=M, d_max=8)
+    c["seg"] = (np.arange(M + 1) % 2 * T).astype(np.int32)
+    c["succ"] = (np.random.default_rng(69).standard_normal((T, model.d_s)) * 0.8).astype(np.float32)
+    for k in ("actions", "table", "U"):
+        c[k] = np.ascontiguousarray(np.broadcast_to(c[k][:1], c[k].shape))
+    c["children"], c["visits"] = np.ones(M, np.int32), np.ones(M, np.int32)
+    m = V.Model(model, compute=compute)
+    n = int(V.lib.voila_pw_step_workspace_size(m.handle, T, M))
+    ws = torch.full((n + 65536,), 0xA5, dtype=torch.uint8, device="cuda")
+    st = torch.zeros(1, dtype=torch.int32, device="cuda")
+    print(f"pw step falling offsets {compute} M {M}", flush=True)
+    res = V.pw_step(m, dev(c["succ"]), dev(c["seg"], torch.int32), dev(c["actions"]), dev(c["visits"], torch.int32),
+                    dev(c["children"], torch.int32), dev(c["table"]), dev(c["U"].view(np.int32), torch.int32), 1.0, 0.5,
+                    lam=0.8, seed=5, workspace=ws[:n], status=st)
+    torch.cuda.synchronize()
+    d = {k: host(v) for k, v in res.items()}
+    assert int(st.item()) == V.VOILA_ERR_INVALID_ARG
+    assert bool((ws[n:] == 0xA5).all())
+    assert not d["widen"].any() and np.array_equal(d["branch"], np.arange(M) % 2 * -1)
+    one = {k: c[k][:1] for k in ("actions", "visits", "children", "table", "U")}
+    r = oracle.pw_step(model, c["succ"], np.array([0, T], np.int32), one["actions"], one["visits"], one["children"],
+                       one["table"], 1.0, 0.5, 0.8, 5, one["U"], bf16=(compute == "bf16"))
+    assert scaled_err(d["loglik"], r["loglik"]) <= (TOL if compute == "f32" else BOUND_EMUL)
+    check_groups(c, d, 0.8, groups=range(0, M, 2))
+
+
+def test_offsets_that_fall_without_overlap(V):
+    # two groups that share nothing but come in falling order: both are
+    # evaluated, the one between them is skipped with the status set
+    w = workloads.small(seed=70)
+    c = make_case(w.model, 70, M=3, d_max=8)
+    c["seg"] = np.array([100, 300, 0, 100], np.int32)
+    c["succ"] = np.random.default_rng(71).standard_normal((300, 4)).astype(np.float32)
+    m = V.Model(w.model)
+    st = torch.zeros(1, dtype=torch.int32, device="cuda")
+    d = run_dev(V, m, c, status=st)
+    assert int(st.item()) == V.VOILA_ERR_INVALID_ARG
+    assert d["branch"][1] == -1 and d["widen"][1] == 0
+    assert (d["branch"][[0, 2]] >= 0).all()
+    check_groups(c, d, 0.8, groups=[0, 2])
