@@ -51,7 +51,7 @@ struct PlanSplitLds {
 };
 
 template <int DT, int D_S, int N_ACT, int D_A, int D_W, int WIDTH, int NHID, int ST>
-__global__ __launch_bounds__(64 * kPlanSplitWaves) void plan_split_kernel(PlanParams p, long unit0, long n_units) {
+__global__ __launch_bounds__(64 * kPlanSplitWaves) void plan_split_kernel(PlanParams p, uint32_t unit0, uint32_t n_units) {
     if constexpr (!plan_split<DT, WIDTH, NHID>()) {
         return;  // the other networks run in plan_kernel
     } else {
@@ -88,10 +88,11 @@ __global__ __launch_bounds__(64 * kPlanSplitWaves) void plan_split_kernel(PlanPa
     };
     const int n_groups = (p.n_tiles + ST - 1) / ST;
     const NetPtrs P = net_ptrs(p.net.base, p.net);
-    // (up to 2^31 - 1 units: the one past a block's last may not fit an int)
-    for (long u = unit0 + blockIdx.x; u < n_units; u += gridDim.x) {
-        const int k = (int)(u / n_groups);
-        const int grp = (int)(u - (long)k * n_groups);
+    // (up to 2^31 - 1 units: the one past a block's last may not fit an int; 64
+    // bits took 1 % of the kernel)
+    for (uint32_t u = unit0 + blockIdx.x; u < n_units; u += gridDim.x) {
+        const int k = (int)(u / (uint32_t)n_groups);
+        const int grp = (int)u - k * n_groups;
         const int tile = grp * ST + (owner ? wave : 0);
         const int i = tile * 32 + col;
         const bool valid = owner && i < p.N;
@@ -479,7 +480,7 @@ void launch_plan_split_one(K k, size_t lds, long blocks, const PlanParams& p, lo
     if (n_units <= unit0) return;
     if (lds > 65536) (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     const long want = n_units - unit0;
-    hipLaunchKernelGGL(k, (int)(want < blocks ? want : blocks), 64 * kPlanSplitWaves, lds, s, p, unit0, n_units);
+    hipLaunchKernelGGL(k, (int)(want < blocks ? want : blocks), 64 * kPlanSplitWaves, lds, s, p, (uint32_t)unit0, (uint32_t)n_units);
 }
 
 // Rounds of tile groups over the chip's `cap` blocks, then the tiles of the

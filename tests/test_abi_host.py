@@ -138,10 +138,11 @@ def test_plan_kernel_instances_split_by_precision():
     assert kinds["k_plan_bf16"] == {"1"}, kinds
 
 
-def test_split_rollout_units_are_counted_in_64_bits():
+def test_split_rollout_units_are_counted_past_31_bits():
     """voila_plan accepts up to 2^31 - 1 (candidate, particle) pairs, so with
     one particle per candidate the split rollout kernel's last unit lies within
-    one grid of 2^31: its first unit and its limit are 64-bit arguments."""
+    one grid of 2^31: its first unit and its limit are unsigned, so that the
+    unit past the last stays above the limit."""
     import shutil
     import subprocess
     obj = os.path.join(ROOT, "paper_2606_19729_amd", "_build", "k_plan.o")
@@ -149,4 +150,4 @@ def test_split_rollout_units_are_counted_in_64_bits():
         pytest.skip("objects of the last build or nm not available")
     out = subprocess.run(["nm", "-C", obj], capture_output=True, text=True, check=True).stdout
     args = set(re.findall(r"__device_stub__plan_split_kernel<[^>]*>\((.*)\)", out))
-    assert args == {"voila::PlanParams, long, long"}, args
+    assert args == {"voila::PlanParams, unsigned int, unsigned int"}, args
