@@ -2415,7 +2415,7 @@ GradWs carve_grad(const voila_model_s* m, const voila_grad_opts_t* o, char* base
     // workspace of a larger batch always serves a smaller one)
     const size_t rows = std::max(1, std::min(n_tiles, m->cus));
     w.wpart = take(rows * m->n_params * 4);
-    w.lpart = take(rows * 4);
+    w.lpart = take((size_t)w.blocks * w.waves * 4);
     w.apart = take((size_t)n_tiles * std::max(o->H, 1) * std::max(m->d_a, 1) * 4);
     w.bytes = off;
     return w;
@@ -2496,6 +2496,7 @@ voila_status_t voila_rollout_grad(voila_model_t m, const voila_grad_opts_t* o, v
     r.loss = o->d_loss_out;
     r.n_params = o->d_grad_params ? m->n_params : 0;
     r.n_waves = w.blocks;
+    r.n_loss = w.blocks * w.waves;
     r.H = o->H;
     r.d_a = m->d_a;
     r.tiles_per_seq = m->n_actions > 0 ? 1 : o->particles / 32;

@@ -380,20 +380,14 @@ __global__ __launch_bounds__(kGradMaxWaves * 64) void grad_kernel(GradParams p) 
                 if (2 * s + g < D_S) lam[s] += dx[s];
         }
     }
-    // ---- the block's partial: its waves' in wave order, gathered in LDS
-    __syncthreads();
-    float* sum = reinterpret_cast<float*>(smem);
+    // ---- the wave's objective (the waves are added up in binary64 later)
     float lsum = sum32(loss_acc);
     lsum += __shfl_xor(lsum, 32);
-    if (lane == 0 && wave < wpb) sum[wave] = lsum;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        float v = 0.0f;
-        for (int k = 0; k < wpb; ++k) v += sum[k];
-        p.lpart[blockIdx.x] = v;
-    }
+    if (lane == 0 && wave < wpb) p.lpart[(size_t)blockIdx.x * wpb + wave] = lsum;
     if (!p.want_params) return;
+    // ---- the block's partial gradient: its waves' in wave order, gathered in LDS
     // layout: W1 [64][D_IN], b1 [64], W2 [64][64], b2 [64], W3 [D_S][64], b3 [D_S]
+    float* sum = reinterpret_cast<float*>(smem);
     constexpr int oW1 = 0, ob1 = 64 * D_IN, oW2 = ob1 + 64, ob2 = oW2 + 64 * 64, oW3 = ob2 + 64, ob3 = oW3 + D_S * 64;
     for (int k = 0; k < wpb; ++k) {
         __syncthreads();
@@ -476,7 +470,7 @@ __global__ __launch_bounds__(kRedCols * kRedWaves) void grad_reduce_kernel(GradR
     }
     if (p.loss && (int)blockIdx.x == param_blocks) {
         double s = 0.0;
-        for (int w = threadIdx.x; w < p.n_waves; w += kRedCols * kRedWaves) s += (double)p.lpart[w];
+        for (int w = threadIdx.x; w < p.n_loss; w += kRedCols * kRedWaves) s += (double)p.lpart[w];
         part[wave][lane] = s;
         __syncthreads();
         if (wave == 0) {

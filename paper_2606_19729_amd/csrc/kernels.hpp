@@ -279,7 +279,7 @@ struct GradParams {
     const float* targets;      // [B][H][d_s] (distillation)
     float* states;             // [tiles][H][state slots][64] rollout states s_0 .. s_{H-1}, one lane slot each
     float* wpart;              // [blocks][n_params] parameter-gradient partials
-    float* lpart;              // [blocks] objective partials
+    float* lpart;              // [blocks][waves] objective partials
     float* apart;              // [tiles][H][d_a] action-gradient partials or NULL
     int B, H, particles, objective, want_params, n_params;
     int waves;                 // waves per block that take tiles (<= kGradMaxWaves)
@@ -315,6 +315,7 @@ struct GradReduceParams {
     float* grad_actions;
     float* loss;
     int n_params, n_waves, n_action_values, H, d_a, tiles_per_seq;
+    int n_loss;              // rows of lpart
     double scale;
 };
 

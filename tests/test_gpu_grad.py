@@ -280,3 +280,23 @@ def test_workspace_sizes_grow_with_the_batch(V):
         sizes.append(int(V.lib.voila_rollout_grad_workspace_size(vm.handle, ctypes.byref(o))))
     print("gradient workspaces", sizes, flush=True)
     assert sizes[0] > 0 and all(x <= y for x, y in zip(sizes, sizes[1:]))
+
+
+def test_objective_sums_waves_in_binary64(V):
+    """Each wave's share of the objective is a whole number: 2^24 for every
+    eighth tile of 32 rollouts, 1 for six of the others, 0 for the eighth.  A
+    binary32 sum of a block's eight loses the ones; all of them sum to a value
+    that binary32 holds.  (The network is zero, so rollouts stay where they start.)"""
+    tiles = 2048
+    mc = cont_model(seed=23)
+    zero = workloads.Model(**{**mc.__dict__, "trans": [(np.zeros_like(W), np.zeros_like(b)) for W, b in mc.trans]})
+    S0 = np.zeros((tiles, 32, 4), np.float32)
+    S0[0::8, :, :2] = 512.0
+    for k in range(1, 7):
+        S0[k::8, 0, 0] = 1.0
+    A = np.zeros((tiles, 1, 4), np.float32)
+    print("grad case: return, whole-number objective", flush=True)
+    J, _, _ = V.rollout_grad(V.Model(zero), dev(S0.reshape(-1, 4)), dev(A), 1, V.VOILA_OBJ_RETURN, gamma=1.0,
+                             goal=[0.0] * 4, particles=32, seed=7)
+    torch.cuda.synchronize()
+    assert J.item() == -(S0.astype(np.float64) ** 2).sum() / (32 * tiles)
