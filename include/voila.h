@@ -578,10 +578,16 @@ voila_status_t voila_batch_replay(voila_batch_t batch, void* stream);
  * Outputs: the objective, its gradient with respect to the transition
  * network's parameters (W1, b1, W2, b2, W3, b3 concatenated, each as
  * nn.Linear stores it) and, for continuous actions, with respect to the
- * action sequences.  The forward pass keeps every step's state in the
- * workspace (d_s floats per rollout and step) and the reverse sweep recomputes
- * each step's activations from it; `checkpoint` is checked and does not change
- * the result.
+ * action sequences.  The forward pass keeps every c-th state in the workspace
+ * (d_s floats per rollout) and the reverse sweep recomputes the states between
+ * and each step's activations from it.  c is the smallest interval, at most
+ * `checkpoint`, that the workspace holds; the result does not depend on it.
+ * voila_rollout_grad_workspace_size gives the size for the smallest interval
+ * within 4 GiB (for `checkpoint` if there is none).  A smaller workspace is
+ * accepted down to what the best interval up to `checkpoint` takes: ceil(H / c)
+ * states per rollout and c - 1 for each of the rollouts that run at once (up
+ * to 256 per CU), one partial gradient per 32 rollouts (up to one per CU), and
+ * max(d_a, 1) floats per 32 rollouts and step.
  * Binary32 models of networks with two hidden layers of width 64 only
  * (otherwise VOILA_ERR_UNSUPPORTED).  Results are deterministic (fixed-order
  * reductions).
@@ -591,7 +597,7 @@ voila_status_t voila_batch_replay(voila_batch_t batch, void* stream);
 
 typedef struct {
     int32_t B, H;               /* rollouts (>= 1), horizon (0..64)                            */
-    int32_t checkpoint;         /* >= 1; every step is kept whatever the interval               */
+    int32_t checkpoint;         /* largest interval between kept states (>= 1)                 */
     const float* d_s0;          /* [B][d_s]                                                     */
     const void* d_actions;      /* discrete: int32 [B][H]; continuous: float [B/particles][H][d_a] */
     int32_t particles;          /* rollouts per continuous sequence (multiple of 32 when the

@@ -9,8 +9,9 @@
 //
 // One wave owns a tile of 32 rollouts.  The forward pass keeps the states in
 // registers and writes every step's to the workspace (16 bytes per rollout and
-// step, in the lanes' own layout); the reverse sweep reads them back, last step
-// first, recomputes the step's hidden activations, and back-propagates the
+// step, in the lanes' own layout), or every C-th where the workspace is smaller;
+// the reverse sweep reads them back, last step first (a segment of C steps runs
+// again from its first state), recomputes the step's hidden activations, and back-propagates the
 // state adjoint through the layers with MFMAs whose A operands are the
 // *transposed* weights packed so that every adjoint comes out in exactly the
 // register layout of the matching forward activation (ReLU masks are
@@ -79,7 +80,10 @@ __device__ __forceinline__ void join_halves(const f32x4& d, float (&out)[2]) {
 // each) overlap one's LDS transposes with the other's products.  65,536
 // rollouts x 20 steps: the whole call 855 -> 557 us (about 340 us at the
 // matrix cores' rate).
-template <int D_S, int N_ACT, int D_A, int D_W>
+// SEG: the workspace holds every p.C-th state only.  The reverse sweep then runs
+// each segment of p.C steps forward again from its first state into the wave's
+// own segment buffer (the same products, so the same states).
+template <int D_S, int N_ACT, int D_A, int D_W, bool SEG>
 __global__ __launch_bounds__(kGradMaxWaves * 64) void grad_kernel(GradParams p) {
     constexpr int WIDTH = 64, NHID = 2, HT = 2;
     constexpr int D_AIN = N_ACT > 0 ? N_ACT : D_A;
@@ -217,7 +221,21 @@ __global__ __launch_bounds__(kGradMaxWaves * 64) void grad_kernel(GradParams p) 
         const int tile = (int)tl;
         const int b = tile * 32 + col;
         const bool valid = b < p.B;
-        float* keep = p.states + (size_t)tile * p.H * (SS * 64) + lane;  // s_t slots of this lane, t < H
+        // s_t slots of this lane, t < H; or rollouts' states (features 2 s + g of
+        // this lane's) at every C-th step and, of one segment, at the steps between
+        float* keep = p.states + (size_t)tile * p.H * (SS * 64) + lane;
+        const int cols = 4 * min(32, p.B - 32 * tile);  // floats of one step
+        float* ckpt = p.states + (size_t)128 * tile * p.NC + 4 * col + g;
+        float* between = p.seg + (size_t)128 * first_tile * (p.C - 1) + 4 * col + g;
+        auto put_state = [&](float* at, const float (&st)[SS]) {
+            if (valid)
+#pragma unroll
+                for (int s = 0; s < SS; ++s) at[2 * s] = st[s];
+        };
+        auto get_state = [&](const float* at, float (&st)[SS]) {
+#pragma unroll
+            for (int s = 0; s < SS; ++s) st[s] = valid ? at[2 * s] : 0.0f;
+        };
         float st[SS];
 #pragma unroll
         for (int s = 0; s < SS; ++s) {
@@ -226,8 +244,12 @@ __global__ __launch_bounds__(kGradMaxWaves * 64) void grad_kernel(GradParams p) 
         }
         // ---- forward (rollouts past B stay at the origin: finite, no weight in any sum)
         for (int t = 0; t < p.H; ++t) {
+            if constexpr (SEG) {
+                if (t % p.C == 0) put_state(ckpt + (size_t)(t / p.C) * cols, st);
+            } else {
 #pragma unroll
-            for (int s = 0; s < SS; ++s) keep[(size_t)(t * SS + s) * 64] = st[s];
+                for (int s = 0; s < SS; ++s) keep[(size_t)(t * SS + s) * 64] = st[s];
+            }
             float slots[NT::IN_SLOTS];
             make_slots(slots, st, b, valid, t);
             Act<DT_F32, HT> h1, h2;
@@ -259,8 +281,26 @@ __global__ __launch_bounds__(kGradMaxWaves * 64) void grad_kernel(GradParams p) 
                     lam[s] += (p.objective == 0 ? 2.0f * (float)p.scale : -2.0f * p.disc[t] * (float)p.scale) * e;
                 }
             }
+            if constexpr (SEG) {
+                const int r = t % p.C, t0 = t - r;
+                if (r == 0 || r == p.C - 1 || t == p.H - 1) get_state(ckpt + (size_t)(t0 / p.C) * cols, st);
+                else get_state(between + (size_t)(r - 1) * cols, st);
+                if (r == p.C - 1 || t == p.H - 1)
+                    for (int q = 0; q < r; ++q) {
+                        float in[NT::IN_SLOTS];
+                        make_slots(in, st, b, valid, t0 + q);
+                        Act<DT_F32, HT> a1, a2;
+                        hidden(in, a1, a2);
+                        const f32x4 d = output(a2.v);
 #pragma unroll
-            for (int s = 0; s < SS; ++s) st[s] = keep[(size_t)(t * SS + s) * 64];
+                        for (int s = 0; s < SS; ++s)
+                            if (2 * s + g < D_S && valid) st[s] += g ? d[2 * s + 1] : d[2 * s];
+                        put_state(between + (size_t)q * cols, st);
+                    }
+            } else {
+#pragma unroll
+                for (int s = 0; s < SS; ++s) st[s] = keep[(size_t)(t * SS + s) * 64];
+            }
             // the activations of step t again
             float slots[NT::IN_SLOTS];
             make_slots(slots, st, b, valid, t);
@@ -686,12 +726,14 @@ bool grad_supported(int shape) {
 hipError_t launch_grad(int shape, const GradParams& p, int blocks, size_t lds, hipStream_t s) {
     // at least four waves stage the networks, whatever number takes tiles
     const int threads = 64 * (p.waves < 4 ? 4 : p.waves);
+    auto launch = [&](void (*k)(GradParams)) {
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipLaunchKernelGGL(k, blocks, threads, lds, s, p);
+    };
     switch (shape) {
-#define X(id, ds, na, da, dw)                                                                                \
-    case id:                                                                                                \
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(grad_kernel<ds, na, da, dw>),                 \
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                     \
-        hipLaunchKernelGGL((grad_kernel<ds, na, da, dw>), blocks, threads, lds, s, p);                           \
+#define X(id, ds, na, da, dw)                                                                          \
+    case id:                                                                                          \
+        launch(p.C > 1 ? grad_kernel<ds, na, da, dw, true> : grad_kernel<ds, na, da, dw, false>);      \
         break;
         GRAD_SHAPES(X)
 #undef X

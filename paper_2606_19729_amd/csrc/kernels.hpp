@@ -277,11 +277,13 @@ struct GradParams {
     const void* actions;       // int32 [B][H] or float [B / particles][H][d_a]
     const float* noise;        // [B][H][d_w] or NULL
     const float* targets;      // [B][H][d_s] (distillation)
-    float* states;             // [tiles][H][state slots][64] rollout states s_0 .. s_{H-1}, one lane slot each
+    float* states;             // C = 1: [tiles][H][state slots][64] states s_0 .. s_{H-1}, one lane slot each;
+                               // C > 1: of a tile's rollouts [NC][rollouts][d_s], the states s_0, s_C, ...
+    float* seg;                // C > 1: of a wave's tile [C - 1][rollouts][d_s], the states within a segment
     float* wpart;              // [blocks][n_params] parameter-gradient partials
     float* lpart;              // [blocks][waves] objective partials
     float* apart;              // [tiles][H][d_a] action-gradient partials or NULL
-    int B, H, particles, objective, want_params, n_params;
+    int B, H, C, NC, particles, objective, want_params, n_params;
     int waves;                 // waves per block that take tiles (<= kGradMaxWaves)
     double scale;
     uint32_t key0, key1;

@@ -300,3 +300,71 @@ def test_objective_sums_waves_in_binary64(V):
                              goal=[0.0] * 4, particles=32, seed=7)
     torch.cuda.synchronize()
     assert J.item() == -(S0.astype(np.float64) ** 2).sum() / (32 * tiles)
+
+
+def workspace_of(V, vm, B, H, interval, d_a):
+    """Bytes of a workspace that keeps every interval-th state: those, the
+    other states of one segment per wave, the partial sums."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    tiles = (B + 31) // 32
+    waves = max(1, min(8, (tiles + cus - 1) // cus))
+    blocks = max(1, min((tiles + waves - 1) // waves, cus))
+    up = lambda n: (n + 255) // 256 * 256
+    if interval == 1:
+        n = up(tiles * H * 512)
+    else:
+        n = up(B * ((H + interval - 1) // interval) * 16) + up(min(B, 32 * blocks * waves) * (interval - 1) * 16)
+    return n + up(min(tiles, cus) * V.grad_param_count(vm) * 4) + up(blocks * waves * 4) + up(tiles * H * d_a * 4)
+
+
+@pytest.mark.parametrize("B", [1, 97, 200, 32 * 300 - 5, 32 * 2100 - 27])
+def test_checkpointed_workspaces_give_the_same_results(V, B):
+    """Workspaces for every checkpoint interval, down to the smallest accepted:
+    the segments run again give the same states, so the same bits."""
+    H = 13
+    m, S0, A, T = distill_inputs(B, H, seed=31, noise_seed=4)
+    vm = V.Model(m)
+    args = (vm, dev(S0), dev(A, torch.int32), H, V.VOILA_OBJ_DISTILL)
+    print(f"grad case: distillation, checkpointed workspaces, B={B}", flush=True)
+    loss, gp, _ = V.rollout_grad(*args, targets=dev(T), seed=4)
+    for c in [1, 2, 5, 12, 13]:
+        n = workspace_of(V, vm, B, H, c, 1)
+        ws = torch.full((n + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+        lo, g, _ = V.rollout_grad(*args, targets=dev(T), seed=4, checkpoint=c, workspace=ws[:n])
+        assert torch.equal(lo, loss) and torch.equal(g, gp), c
+        assert bool((ws[n:] == 0xA5).all()), c
+        if c == 1:
+            with pytest.raises(V.VoilaError) as e:
+                V.rollout_grad(*args, targets=dev(T), seed=4, checkpoint=c, workspace=ws[:n - 1])
+            assert e.value.status == V.VOILA_ERR_WORKSPACE
+
+
+def test_checkpointed_action_gradients(V):
+    P, K, H = 64, 40, 9
+    mc, rng = cont_model(seed=32), np.random.default_rng(32)
+    vm = V.Model(mc)
+    S0 = dev(rng.standard_normal((K * P, 4)))
+    A = dev(rng.uniform(-1, 1, (K, H, 4)))
+    kw = dict(gamma=0.9, goal=[1.0, 1.0, 0.0, 0.0], particles=P, seed=8, want_actions=True)
+    ref = V.rollout_grad(vm, S0, A, H, V.VOILA_OBJ_RETURN, **kw)
+    for c in [3, 4]:
+        ws = torch.empty(workspace_of(V, vm, K * P, H, c, 4), dtype=torch.uint8, device="cuda")
+        got = V.rollout_grad(vm, S0, A, H, V.VOILA_OBJ_RETURN, checkpoint=c, workspace=ws, **kw)
+        assert all(torch.equal(x, y) for x, y in zip(got, ref)), c
+
+
+def test_checkpoint_interval_bounds_the_workspace(V):
+    """At sizes whose states would take hundreds of GB the interval is what a
+    caller trades time for memory with (sizes only, nothing runs)."""
+    import ctypes
+    m, S0, A, _ = distill_inputs(32, 5)
+    vm = V.Model(m)
+    goal = (ctypes.c_float * 4)(0.0, 0.0, 0.0, 0.0)
+    s0, a = dev(S0), dev(A, torch.int32)
+    B, H = 1 << 28, 64
+    for c in [8, 16, 64]:
+        o = V._GradOpts(B, H, c, V._ptr(s0), V._ptr(a), 1, None, 0, V.VOILA_OBJ_DISTILL, V._ptr(s0), 1.0, goal, None,
+                        None, None)
+        n = int(V.lib.voila_rollout_grad_workspace_size(vm.handle, ctypes.byref(o)))
+        # checkpoints, one segment and the initial states per rollout, action partials, 32 MB of partial sums
+        assert n <= 16 * B * (H // c + c + 1) + B // 32 * H * 4 + (32 << 20), (c, n)
