@@ -334,9 +334,8 @@ def test_checkpointed_workspaces_give_the_same_results(V, B):
         assert torch.equal(lo, loss) and torch.equal(g, gp), c
         assert bool((ws[n:] == 0xA5).all()), c
         if c == 1:
-            with pytest.raises(V.VoilaError) as e:
+            with pytest.raises(V.VoilaError, match="workspace too small"):
                 V.rollout_grad(*args, targets=dev(T), seed=4, checkpoint=c, workspace=ws[:n - 1])
-            assert e.value.status == V.VOILA_ERR_WORKSPACE
 
 
 def test_checkpointed_action_gradients(V):
