@@ -642,7 +642,7 @@ bool plan_half_shape(int shape, int dt) {
 
 hipError_t launch_plan_half(int shape, const PlanParams& p, const QReduceParams& q, hipStream_t s) {
     const int blocks = 2 * p.K * p.n_tiles;
-    if (p.n_tiles > kPlanHalfTiles) return hipErrorInvalidValue;
+    if (!plan_half_shape(shape, DT_F32) || p.n_tiles > kPlanHalfTiles) return hipErrorInvalidValue;
     float* contribs = const_cast<float*>(q.partials);
     switch (shape) {
 #define X(id, ds, na, da, dw, dox, dwz, w, nh)                                                                          \

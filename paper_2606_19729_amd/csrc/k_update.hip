@@ -194,13 +194,17 @@ __device__ __forceinline__ void propose_tile(const NetPtrs& PT, const NetPtrs& P
     }
 }
 
+// Whether updates of a shape run this kernel: not those refused at model creation
+// (binary32 wider than 256), those of the split rollout kernel's networks, and
+// binary32 up to 256, which runs on half tiles at every size.
+template <int DT, int WIDTH, int NHID>
+constexpr bool propose_on_tiles() {
+    return generic_compiled(DT, WIDTH, NHID) && !(pass_mode<WIDTH>() == kSplit && DT == DT_F32);
+}
+
 template <int DT, int D_S, int D_W, int WIDTH, int NHID, int MODE>
 __global__ __launch_bounds__(256) void propose_kernel(ProposeParams p) {
-    if constexpr (!generic_compiled(DT, WIDTH, NHID) || (MODE == kSplit && DT == DT_F32)) {
-        // refused at model creation (binary32 wider than 256) or run by the
-        // split rollout kernel; binary32 up to 256 runs on half tiles
-        return;
-    } else {
+    static_assert(propose_on_tiles<DT, WIDTH, NHID>(), "run by another kernel");
     constexpr bool WLDS = MODE == kResident;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     if (WLDS) {
@@ -220,7 +224,6 @@ __global__ __launch_bounds__(256) void propose_kernel(ProposeParams p) {
     } else {
         for (int tile = blockIdx.x * wpb + (threadIdx.x >> 6); tile < n_tiles; tile += gridDim.x * wpb)
             propose_tile<DT, D_S, D_W, WIDTH, NHID>(PT, PL, p, tile, true, lane, g, col);
-    }
     }
 }
 
@@ -718,26 +721,37 @@ VOILA_IN_SLOTS(lik_in_slots, in_slots(dt, s.d_s, 0, 0))
 VOILA_IN_SLOTS(nce_in_slots, in_slots(dt, s.d_o, 0, 0))
 #undef VOILA_IN_SLOTS
 
-#define PROP_K(id, ds, na, da, dw, dox, dwz, w, nh, DT) propose_kernel<DT, ds, dw, w, nh, pass_mode<w>()>
-
 int pass_tiles_per_block(int shape) { return pass_split(shape) ? 1 : 4; }
+
+template <int DT, int D_S, int D_W, int W, int NH>
+hipError_t launch_propose_one(const ProposeParams& p, int blocks, size_t lds, hipStream_t s) {
+    if constexpr (!propose_on_tiles<DT, W, NH>()) {
+        return hipErrorInvalidValue;
+    } else {
+        hipLaunchKernelGGL((propose_kernel<DT, D_S, D_W, W, NH, pass_mode<W>()>), blocks, 256, lds, s, p);
+        return hipGetLastError();
+    }
+}
+template <int DT, int D_S, int D_W, int W, int NH>
+int propose_occupancy() {
+    if constexpr (!propose_on_tiles<DT, W, NH>())
+        return 1;
+    else
+        return occupancy(propose_kernel<DT, D_S, D_W, W, NH, pass_mode<W>()>, lds_for_width<W>() ? 2 * kLdsGuess : kSplitLds);
+}
 
 hipError_t launch_propose(int shape, int dt, const ProposeParams& p, int blocks, hipStream_t s) {
     const size_t lds = weights_in_lds(shape) ? (size_t)p.trans.bytes + p.lik.bytes : pass_split(shape) ? kSplitLds : 0;
     switch (shape * 2 + dt) {
-#define X(id, ds, na, da, dw, dox, dwz, w, nh)                                                              \
-    case id * 2 + 0:                                                                                       \
-        hipLaunchKernelGGL((PROP_K(id, ds, na, da, dw, dox, dwz, w, nh, DT_F32)), blocks, 256, lds, s, p);  \
-        break;                                                                                             \
-    case id * 2 + 1:                                                                                       \
-        hipLaunchKernelGGL((PROP_K(id, ds, na, da, dw, dox, dwz, w, nh, DT_BF16)), blocks, 256, lds, s, p); \
-        break;
+#define X(id, ds, na, da, dw, dox, dwz, w, nh)                                      \
+    case id * 2 + 0:                                                               \
+        return launch_propose_one<DT_F32, ds, dw, w, nh>(p, blocks, lds, s);       \
+    case id * 2 + 1:                                                               \
+        return launch_propose_one<DT_BF16, ds, dw, w, nh>(p, blocks, lds, s);
         VOILA_SHAPES(X)
 #undef X
-        default:
-            return hipErrorInvalidValue;
     }
-    return hipGetLastError();
+    return hipErrorInvalidValue;
 }
 
 #define PROPH_K(id, ds, na, da, dw, dox, dwz, w, nh, DT) propose_half_kernel<DT, ds, dw, w, nh>
@@ -772,11 +786,11 @@ hipError_t launch_propose_half(int shape, int dt, const ProposeHalfParams& p, in
 
 int propose_blocks_per_cu(int shape, int dt) {
     switch (shape * 2 + dt) {
-#define X(id, ds, na, da, dw, dox, dwz, w, nh)                                                                   \
-    case id * 2 + 0:                                                                                            \
-        return occupancy(PROP_K(id, ds, na, da, dw, dox, dwz, w, nh, DT_F32), lds_for_width<w>() ? 2 * kLdsGuess : kSplitLds); \
-    case id * 2 + 1:                                                                                            \
-        return occupancy(PROP_K(id, ds, na, da, dw, dox, dwz, w, nh, DT_BF16), lds_for_width<w>() ? 2 * kLdsGuess : kSplitLds);
+#define X(id, ds, na, da, dw, dox, dwz, w, nh)                     \
+    case id * 2 + 0:                                              \
+        return propose_occupancy<DT_F32, ds, dw, w, nh>();        \
+    case id * 2 + 1:                                              \
+        return propose_occupancy<DT_BF16, ds, dw, w, nh>();
         VOILA_SHAPES(X)
 #undef X
     }

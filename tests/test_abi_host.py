@@ -151,3 +151,16 @@ def test_split_rollout_units_are_counted_past_31_bits():
     out = subprocess.run(["nm", "-C", obj], capture_output=True, text=True, check=True).stdout
     args = set(re.findall(r"__device_stub__plan_split_kernel<[^>]*>\((.*)\)", out))
     assert args == {"voila::PlanParams, unsigned int, unsigned int"}, args
+
+
+def test_no_update_kernel_without_work():
+    """Updates of binary32 networks of width 256 run on half tiles; the kernel
+    on 32-row tiles has no instance for them that would return at once."""
+    import shutil
+    import subprocess
+    obj = os.path.join(ROOT, "paper_2606_19729_amd", "_build", "k_update.o")
+    if shutil.which("nm") is None or not os.path.exists(obj):
+        pytest.skip("objects of the last build or nm not available")
+    out = subprocess.run(["nm", "-C", obj], capture_output=True, text=True, check=True).stdout
+    kinds = set(re.findall(r"__device_stub__propose_kernel<(\d), \d+, \d+, (\d+),", out))
+    assert ("1", "256") in kinds and ("0", "64") in kinds and ("0", "256") not in kinds, kinds
