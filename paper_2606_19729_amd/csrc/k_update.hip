@@ -999,7 +999,7 @@ int norm_res_slices(const NormResParams& p) {
     const struct {
         const void* at;
         size_t bytes;
-    } in[] = {{p.x, 8 * n}, {p.loglik, 4 * n}, {p.prior_w, 8 * n}, {p.w_in, 8 * n}},
+    } in[] = {{p.x, 8 * n}, {p.loglik, 4 * n}, {p.prior_w, 8 * n}, {p.w_in, 8 * n}, {p.src, p.dst ? 4 * n * p.row_floats : 0}},
       out[] = {{p.w_out, 8 * n}, {p.stats, 16}, {p.idx_out, 4 * n}, {p.dst, p.src ? 4 * n * p.row_floats : 0}};
     for (const auto& o : out)
         for (const auto& i : in)

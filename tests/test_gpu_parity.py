@@ -395,3 +395,22 @@ def test_update_is_deterministic():
     torch.cuda.synchronize()
     for k in ["states", "idx", "w", "loglik", "stats"]:
         assert torch.equal(a[k], b[k]), k
+
+
+@pytest.mark.parametrize("N", [256, 257, 1000, 8192])
+def test_resample_indices_written_over_the_rows(N):
+    # the indices go where the first rows lie: every one is stored before any
+    # row is gathered, so the rows gathered are the overwritten ones
+    rng = np.random.default_rng(N)
+    wv = rng.dirichlet(np.ones(N))
+    rows = rng.standard_normal((N, 4)).astype(np.float32)
+    src = dev(rows)
+    idx = src.view(torch.int32).reshape(-1)[:N]
+    dst = torch.empty_like(src)
+    say(f"  resample N={N}, indices over the first rows")
+    V.resample(dev(wv, torch.float64), 98765, src=src, dst=dst, idx=idx)
+    torch.cuda.synchronize()
+    ref = oracle.resample(wv, 98765)
+    assert np.array_equal(idx.cpu().numpy(), ref)
+    rows.view(np.int32).reshape(-1)[:N] = ref
+    assert np.array_equal(dst.cpu().numpy().view(np.int32), rows[ref].view(np.int32))
