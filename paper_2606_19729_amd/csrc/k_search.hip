@@ -639,7 +639,7 @@ hipError_t launch_pw_branch(const PwParams& p, hipStream_t s) {
 
 hipError_t launch_pw_prepare(const PwParams& p, const FoldStepsParams& fold, hipStream_t s) {
     const int first_blocks = (p.M * p.d_s + 1023) / 1024;
-    const bool here = fold.rows < kFoldManyRows;
+    const bool here = !fold_takes_rows(fold);
     const int fold_blocks = here ? (int)(((long)fold.rows * fold.width + 1023) / 1024) : 0;
     hipLaunchKernelGGL(pw_prepare_kernel, 1 + first_blocks + fold_blocks, 1024, 0, s, p, fold, first_blocks);
     const hipError_t e = hipGetLastError();

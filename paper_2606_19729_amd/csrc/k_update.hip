@@ -967,17 +967,22 @@ hipError_t launch_norm_res_batch(const NormResParams* d_ps, int n_inst, const ui
     return hipGetLastError();
 }
 
+// Whether the kernel for many rows folds p: from one row per CU on (below, a
+// block per row fills no more CUs than this one's staging costs), and from 4,096
+// rows where they are narrower than the block (calls around a width-64 fold: 640
+// rows 89.4 against 90.3 us, 1,024 28.6 / 29.1, 4,096 100.5 / 98.9, 8,000 48.0 /
+// 46.6); the LDS without an attribute holds 61 columns, every compiled shape's.
+size_t fold_rows_lds(const FoldStepsParams& p) { return (size_t)p.nf * (257 + kFoldRows) * sizeof(float); }
+bool fold_takes_rows(const FoldStepsParams& p) {
+    return p.rows >= (p.width >= 256 ? 256 : 4096) && fold_rows_lds(p) <= 65536;
+}
+
 hipError_t launch_fold_steps(const FoldStepsParams& p, hipStream_t s) {
     if (p.rows == 0) return hipSuccess;
-    const size_t lds = (size_t)p.nf * (257 + kFoldRows) * sizeof(float);
-    // from one row per CU on (below, a block per row fills no more CUs than this
-    // one's staging costs), and from 4,096 rows where they are narrower than the
-    // block (calls around a width-64 fold: 640 rows 89.4 against 90.3 us, 1,024
-    // 28.6 / 29.1, 4,096 100.5 / 98.9, 8,000 48.0 / 46.6); the LDS without an attribute holds 61
-    // columns, every compiled shape's
-    if (p.rows >= (p.width >= 256 ? kFoldManyRows : 4096) && lds <= 65536) {
+    if (fold_takes_rows(p)) {
         const int groups = (p.rows + kFoldRows - 1) / kFoldRows;
-        hipLaunchKernelGGL(fold_rows_kernel, dim3((p.width + 255) / 256, groups < 512 ? groups : 512), 256, lds, s, p);
+        hipLaunchKernelGGL(fold_rows_kernel, dim3((p.width + 255) / 256, groups < 512 ? groups : 512), 256,
+                           fold_rows_lds(p), s, p);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(fold_steps_kernel, dim3((p.width + 255) / 256, p.rows < 65535 ? p.rows : 65535), 256, 0, s, p);

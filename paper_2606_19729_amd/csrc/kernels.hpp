@@ -377,9 +377,9 @@ constexpr int kPlanHalfTiles = 1024;  // most tiles of such a plan
 bool plan_half_shape(int shape, int dt);
 hipError_t launch_plan_half(int shape, const PlanParams& p, const QReduceParams& q, hipStream_t s);
 hipError_t launch_fold_steps(const FoldStepsParams& p, hipStream_t s);
+bool fold_takes_rows(const FoldStepsParams& p);  // by the kernel for many rows
 hipError_t launch_fold_pair(const FoldStepsParams& a, const FoldStepsParams& b, hipStream_t s);
 // Grouped progressive-widening stages.
-constexpr int kFoldManyRows = 256;  // rows from which the folds take a kernel for many rows
 hipError_t launch_pw_prepare(const PwParams& p, const FoldStepsParams& fold, hipStream_t s);
 hipError_t launch_pw_branch(const PwParams& p, hipStream_t s);
 hipError_t launch_pw_lik(int shape, int dt, const PwParams& p, int blocks, hipStream_t s);

@@ -260,3 +260,12 @@ def test_offsets_that_fall_without_overlap(V):
     assert d["branch"][1] == -1 and d["widen"][1] == 0
     assert (d["branch"][[0, 2]] >= 0).all()
     check_groups(c, d, 0.8, groups=[0, 2])
+
+
+@pytest.mark.parametrize("M", [257, 4095, 4096])
+def test_small_networks_fold_either_way(V, M):
+    # width 64: bias rows folded beside the work-unit prefix, from 4,096 groups
+    # on by the kernel for many rows
+    w = workloads.small(seed=72)
+    print(f"pw step small f32, {M} groups", flush=True)
+    compare(V, w.model, make_case(w.model, 72, M=M, d_max=6), "f32")
