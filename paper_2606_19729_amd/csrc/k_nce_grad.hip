@@ -23,26 +23,20 @@ template <class N> struct BwdStreamShape {
     static constexpr int NFO = 0;
 };
 
-template <int DT> struct Elem;
-template <> struct Elem<DT_F32> { typedef float type; };
-
 // Binary32 values as B operands without the ReLU (adjoints may be negative).
 template <int HT>
 __device__ __forceinline__ void set_plain(Act<DT_F32, HT>& a, const f32x16 (&acc)[HT]) {
 #pragma unroll
     for (int t = 0; t < HT; ++t) a.v[t] = acc[t];
 }
-// Element (t, i) of an operand set (the value the matrix cores consume).
-template <int HT>
-__device__ __forceinline__ float act_at(const Act<DT_F32, HT>& a, int t, int i) { return a.v[t][i]; }
 
-template <int DT, int D_O, int WIDTH, int NHID>
+template <int D_O, int WIDTH, int NHID>
 __global__ __launch_bounds__(256) void nce_wide_bwd_kernel(NceWideParams p) {
+    constexpr int DT = DT_F32;
     typedef Net<DT, WIDTH, NHID, in_slots(DT, D_O, 0, 0), WIDTH / 32> NT;
     typedef BwdStreamShape<NT> SH;
     typedef typename Frag<DT>::type FT;
     typedef FragIdx<NT> FI;
-    typedef typename Elem<DT>::type ET;
     constexpr int HT = NT::HT, SO = state_slots(D_O);
 #ifndef VOILA_NCE_BWD_DEPTH
 #define VOILA_NCE_BWD_DEPTH 4
@@ -100,13 +94,13 @@ __global__ __launch_bounds__(256) void nce_wide_bwd_kernel(NceWideParams p) {
         // adjoints and G are zero)
         const long ul = u - p.u0;
         auto put_all = [&](int a, const Act<DT, HT>& v) {
-            ET* base = reinterpret_cast<ET*>(p.act) + (((size_t)a * p.uc + ul) * WIDTH + 4 * g) * 32 + col +
+            float* base = reinterpret_cast<float*>(p.act) + (((size_t)a * p.uc + ul) * WIDTH + 4 * g) * 32 + col +
                        opaque_zero();
             if (ok)
 #pragma unroll
                 for (int t = 0; t < HT; ++t)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) base[(32 * t + 8 * (r >> 2) + (r & 3)) * 32] = (ET)act_at(v, t, r);
+                    for (int r = 0; r < 16; ++r) base[(32 * t + 8 * (r >> 2) + (r & 3)) * 32] = v.v[t][r];
         };
         f32x16 acc[HT];
         Act<DT, HT> act;
@@ -171,40 +165,19 @@ __global__ __launch_bounds__(256) void nce_wide_bwd_kernel(NceWideParams p) {
 // ---------------------------------------------------------------------------
 // stage 2: weight derivatives as split-K products over the chunk's pairs
 // ---------------------------------------------------------------------------
-template <int DT> struct WgCfg;
-template <> struct WgCfg<DT_F32> {
-    static constexpr int KC = 32, PAD = 1, VEC = 4;  // pairs per staged chunk, row padding, elements per load
-};
-template <int DT> struct WgVec;
-template <> struct WgVec<DT_F32> { typedef f32x4 type; };
-// VEC consecutive elements of a feature-major row (zero past the chunk's
-// last pair).
-template <int DT>
-__device__ __forceinline__ typename WgVec<DT>::type load_vec(const typename Elem<DT>::type* src, int n_ok) {
-    typedef typename WgVec<DT>::type VT;
-    constexpr int VEC = WgCfg<DT>::VEC;
-    if (n_ok >= VEC) return *reinterpret_cast<const VT*>(src);
-    VT v;
+constexpr int kWgPairs = 32, kWgVec = 4;       // pairs per staged chunk (one unit), elements per load
+constexpr int kWgStride = kWgPairs + 1;        // floats of a staged row (odd: no two rows on one bank)
+
+// Writes a load's elements into an LDS row (of an odd stride: no vector store).
+__device__ __forceinline__ void store_row(float* dst, const f32x4& v) {
 #pragma unroll
-    for (int q = 0; q < VEC; ++q) v[q] = q < n_ok ? src[q] : (typename Elem<DT>::type)0.0f;
-    return v;
+    for (int q = 0; q < kWgVec; ++q) dst[q] = v[q];
+}
+// A / B operand of k-step s: row r of the staged tile, pair 2 s + (lane / 32)
+__device__ __forceinline__ float staged(const float* t, int row, int s, int lane) {
+    return t[row * kWgStride + 2 * s + (lane >> 5)];
 }
 
-// Writes VEC operand elements into an LDS row.
-template <int DT>
-__device__ __forceinline__ void store_vec(typename Elem<DT>::type* dst, const typename WgVec<DT>::type& v) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) dst[q] = v[q];  // rows are padded to an odd stride: no vector store
-}
-
-template <int DT> struct WgFrag;
-template <> struct WgFrag<DT_F32> {
-    // A / B operand of k-step s: row r of the staged tile, pair 2 s + (lane / 32)
-    __device__ static __forceinline__ float load(const float* t, int row, int s, int lane) {
-        return t[row * (WgCfg<DT_F32>::KC + WgCfg<DT_F32>::PAD) + 2 * s + (lane >> 5)];
-    }
-    static constexpr int KSTEPS = WgCfg<DT_F32>::KC / 2;
-};
 // One weight derivative over this workgroup's units [v0, v1) of the chunk:
 // C[m][n] = sum_p A[m][p] B[n][p] with A the layer's output adjoints (formed
 // from the last hidden layer, G and w_out when FORMED) and B its inputs (the
@@ -218,27 +191,23 @@ template <> struct WgFrag<DT_F32> {
 // flight during them.  16,000 units in binary32: 1.67 -> 1.30 ms (0.96 at the
 // matrix rate).
 constexpr int kWgWaves = 8;
-template <int DT, int WIDTH, int NB, bool FORMED, bool XIN>
+template <int WIDTH, int NB, bool FORMED, bool XIN>
 __device__ __forceinline__ void wgrad_pass(const NceWgradParams& p, int a_idx, int b_idx, int n_in, int w_off,
                                            int b_off, int o_off, long v0, long v1, char* smem) {
-    typedef typename Elem<DT>::type ET;
-    typedef WgCfg<DT> CF;
-    typedef typename WgVec<DT>::type VT;
-    constexpr int KC = CF::KC, VEC = CF::VEC, STR = KC + CF::PAD;
-    constexpr int UPC = KC / 32;                             // units per staged chunk
+    constexpr int KC = kWgPairs, VEC = kWgVec, STR = kWgStride;
     constexpr int WR = NB == WIDTH ? 2 : 4, WC = kWgWaves / WR;  // waves along rows / columns of C
     constexpr int RT = WIDTH / 32 / WR, CT = NB / 32 / WC;  // 32x32 tiles per wave
     constexpr int PR = KC / VEC;                             // loads per staged row
     constexpr int TH = 64 * kWgWaves, RS = TH / PR;           // threads, staged rows per sweep
     constexpr int A_IT = WIDTH * PR / TH, B_IT = NB * PR / TH;
     static_assert(PR == 8 && WIDTH * PR % TH == 0 && NB * PR % TH == 0, "staging map");
-    ET* const As = reinterpret_cast<ET*>(smem);  // two buffers of [WIDTH][STR] adjoints, [NB][STR] inputs
+    float* const As = reinterpret_cast<float*>(smem);  // two buffers of [WIDTH][STR] adjoints, [NB][STR] inputs
     constexpr int BUF = (WIDTH + NB) * STR;
     const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, col = lane & 31;
     const int wave = tid >> 6, wr = wave / WC, wc = wave % WC;
     const int cg = tid & 7;            // this thread's column group of a staged row
     const int r0 = tid >> 3;           // its first staged row (then every RS-th)
-    const int ku = cg * VEC / 32, c0 = cg * VEC % 32;  // unit within the staged chunk, first column
+    const int c0 = cg * VEC;           // its first column
     const int d_in = n_in;
     const int aw = p.n_actions > 0 ? p.n_actions : p.d_a;
     const int jtiles = (p.B + 31) / 32;
@@ -257,27 +226,26 @@ __device__ __forceinline__ void wgrad_pass(const NceWgradParams& p, int a_idx, i
         for (int it = 0; it < A_IT; ++it) wv[it] = p.w_out[r0 + RS * it];
     }
 
-    VT ra[A_IT], rb[B_IT];
+    f32x4 ra[A_IT], rb[B_IT];
     float gv[VEC];
     auto fetch = [&](long v) {
-        const long uu = v + ku;  // this thread's unit (local to the chunk)
-        const bool in = uu < v1;
+        const bool in = v < v1;
         // pairs of this thread's columns: row i, columns j0 .. j0 + VEC - 1
-        const long ug = p.u0 + uu;
+        const long ug = p.u0 + v;
         const int i = (int)(ug / jtiles), j0 = (int)(ug - (long)i * jtiles) * 32 + c0;
         if constexpr (FORMED) {
 #pragma unroll
             for (int e = 0; e < VEC; ++e) gv[e] = (in && j0 + e < p.B) ? p.grad[(size_t)i * p.B + j0 + e] : 0.0f;
         }
-        const ET* Ab = reinterpret_cast<const ET*>(p.act) +
-                       (((size_t)a_idx * p.uc + (in ? uu : 0)) * WIDTH + r0) * 32 + c0 + opaque_zero();
+        const float* Ab = reinterpret_cast<const float*>(p.act) +
+                          (((size_t)a_idx * p.uc + (in ? v : 0)) * WIDTH + r0) * 32 + c0 + opaque_zero();
 #pragma unroll
         for (int it = 0; it < A_IT; ++it) {
             if (in) {
-                ra[it] = *reinterpret_cast<const VT*>(Ab + it * RS * 32);
+                ra[it] = *reinterpret_cast<const f32x4*>(Ab + it * RS * 32);
             } else {
 #pragma unroll
-                for (int e = 0; e < VEC; ++e) ra[it][e] = (ET)0.0f;
+                for (int e = 0; e < VEC; ++e) ra[it][e] = 0.0f;
             }
         }
         if constexpr (XIN) {
@@ -293,58 +261,58 @@ __device__ __forceinline__ void wgrad_pass(const NceWgradParams& p, int a_idx, i
 #pragma unroll
                 for (int e = 0; e < VEC; ++e) {
                     const int j = j0 + e;
-                    float v = 0.0f;
+                    float x = 0.0f;
                     if (in && j < p.B && r < d_in) {
                         if (r < p.d_s) {
-                            v = p.states[(size_t)i * p.d_s + r];
+                            x = p.states[(size_t)i * p.d_s + r];
                         } else if (r < p.d_s + aw) {
-                            if (p.n_actions > 0) v = (r - p.d_s == a) ? 1.0f : 0.0f;
-                            else v = reinterpret_cast<const float*>(p.actions)[(size_t)i * p.d_a + (r - p.d_s)];
+                            if (p.n_actions > 0) x = (r - p.d_s == a) ? 1.0f : 0.0f;
+                            else x = reinterpret_cast<const float*>(p.actions)[(size_t)i * p.d_a + (r - p.d_s)];
                         } else {
-                            v = p.obs[(size_t)j * p.d_o + (r - p.d_s - aw)];
+                            x = p.obs[(size_t)j * p.d_o + (r - p.d_s - aw)];
                         }
                     }
-                    rb[it][e] = (ET)v;
+                    rb[it][e] = x;
                 }
             }
         } else {
-            const ET* Bb = reinterpret_cast<const ET*>(p.act) +
-                           (((size_t)b_idx * p.uc + (in ? uu : 0)) * WIDTH + r0) * 32 + c0 + opaque_zero();
+            const float* Bb = reinterpret_cast<const float*>(p.act) +
+                              (((size_t)b_idx * p.uc + (in ? v : 0)) * WIDTH + r0) * 32 + c0 + opaque_zero();
 #pragma unroll
             for (int it = 0; it < B_IT; ++it) {
                 if (in) {
-                    rb[it] = *reinterpret_cast<const VT*>(Bb + it * RS * 32);
+                    rb[it] = *reinterpret_cast<const f32x4*>(Bb + it * RS * 32);
                 } else {
 #pragma unroll
-                    for (int e = 0; e < VEC; ++e) rb[it][e] = (ET)0.0f;
+                    for (int e = 0; e < VEC; ++e) rb[it][e] = 0.0f;
                 }
             }
         }
     };
     // forms the adjoint and its sums here, behind the products, so that the
     // loads stay in flight during them
-    auto stage = [&](ET* at) {
+    auto stage = [&](float* at) {
 #pragma unroll
         for (int it = 0; it < A_IT; ++it) {
             if constexpr (FORMED) {
                 // delta = G w_out on the active units of the last hidden layer
 #pragma unroll
                 for (int e = 0; e < VEC; ++e) {
-                    const float h = (float)ra[it][e];
+                    const float h = ra[it][e];
                     so[it] = __builtin_fmaf(gv[e], h, so[it]);
-                    ra[it][e] = (ET)(h > 0.0f ? wv[it] * gv[e] : 0.0f);
+                    ra[it][e] = h > 0.0f ? wv[it] * gv[e] : 0.0f;
                 }
                 if (r0 == 0 && it == 0)
 #pragma unroll
                     for (int e = 0; e < VEC; ++e) sg += gv[e];
             }
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) sd[it] += (float)ra[it][e];
+            for (int e = 0; e < VEC; ++e) sd[it] += ra[it][e];
         }
 #pragma unroll
-        for (int it = 0; it < A_IT; ++it) store_vec<DT>(at + (r0 + RS * it) * STR + cg * VEC, ra[it]);
+        for (int it = 0; it < A_IT; ++it) store_row(at + (r0 + RS * it) * STR + cg * VEC, ra[it]);
 #pragma unroll
-        for (int it = 0; it < B_IT; ++it) store_vec<DT>(at + (WIDTH + r0 + RS * it) * STR + cg * VEC, rb[it]);
+        for (int it = 0; it < B_IT; ++it) store_row(at + (WIDTH + r0 + RS * it) * STR + cg * VEC, rb[it]);
     };
     if (v0 < v1) {
         fetch(v0);
@@ -352,23 +320,23 @@ __device__ __forceinline__ void wgrad_pass(const NceWgradParams& p, int a_idx, i
     }
     __syncthreads();
     int cur = 0;
-    for (long v = v0; v < v1; v += UPC, cur ^= 1) {
-        const ET* const at = As + cur * BUF;
-        const ET* const bt = at + WIDTH * STR;
-        if (v + UPC < v1) fetch(v + UPC);  // next chunk into registers while this one multiplies
+    for (long v = v0; v < v1; ++v, cur ^= 1) {
+        const float* const at = As + cur * BUF;
+        const float* const bt = at + WIDTH * STR;
+        if (v + 1 < v1) fetch(v + 1);  // next chunk into registers while this one multiplies
 #pragma unroll
-        for (int s = 0; s < WgFrag<DT>::KSTEPS; ++s) {
-            typename Frag<DT>::type af[RT], bf[CT];
+        for (int s = 0; s < KC / 2; ++s) {
+            float af[RT], bf[CT];
 #pragma unroll
-            for (int a = 0; a < RT; ++a) af[a] = WgFrag<DT>::load(at, 32 * (wr * RT + a) + col, s, lane);
+            for (int a = 0; a < RT; ++a) af[a] = staged(at, 32 * (wr * RT + a) + col, s, lane);
 #pragma unroll
-            for (int b = 0; b < CT; ++b) bf[b] = WgFrag<DT>::load(bt, 32 * (wc * CT + b) + col, s, lane);
+            for (int b = 0; b < CT; ++b) bf[b] = staged(bt, 32 * (wc * CT + b) + col, s, lane);
 #pragma unroll
             for (int a = 0; a < RT; ++a)
 #pragma unroll
                 for (int b = 0; b < CT; ++b) acc[a][b] = mfma(af[a], bf[b], acc[a][b]);
         }
-        if (v + UPC < v1) stage(As + (cur ^ 1) * BUF);  // read by no wave since the last barrier
+        if (v + 1 < v1) stage(As + (cur ^ 1) * BUF);  // read by no wave since the last barrier
         __syncthreads();
     }
     // partial sums of this workgroup (written by the first chunk, added to afterwards)
@@ -416,7 +384,7 @@ __device__ __forceinline__ void wgrad_pass(const NceWgradParams& p, int a_idx, i
     __syncthreads();
 }
 
-template <int DT, int WIDTH, int NHID, int XW>
+template <int WIDTH, int NHID, int XW>
 __global__ __launch_bounds__(64 * kWgWaves) void nce_wide_wgrad_kernel(NceWgradParams p) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const long per = p.per_split;
@@ -429,15 +397,15 @@ __global__ __launch_bounds__(64 * kWgWaves) void nce_wide_wgrad_kernel(NceWgradP
 #pragma unroll
     for (int l = 2; l <= NHID; ++l) off[l] = off[l - 1] + WIDTH * WIDTH + WIDTH;
     // last hidden layer: adjoint formed from h_NHID and G; input h_{NHID-1}; output layer's sums
-    wgrad_pass<DT, WIDTH, WIDTH, true, false>(p, NHID - 1, NHID - 2, WIDTH, off[NHID - 1],
+    wgrad_pass<WIDTH, WIDTH, true, false>(p, NHID - 1, NHID - 2, WIDTH, off[NHID - 1],
                                               off[NHID - 1] + WIDTH * WIDTH, off[NHID], q0, q1, smem);
     // hidden->hidden layers L = NHID - 2 .. 1: stored adjoint delta_{L+1}, input h_L
 #pragma unroll
     for (int L = NHID - 2; L >= 1; --L)
-        wgrad_pass<DT, WIDTH, WIDTH, false, false>(p, NHID + L, L - 1, WIDTH, off[L], off[L] + WIDTH * WIDTH, 0,
+        wgrad_pass<WIDTH, WIDTH, false, false>(p, NHID + L, L - 1, WIDTH, off[L], off[L] + WIDTH * WIDTH, 0,
                                                    q0, q1, smem);
     // first layer: adjoint delta_1, input [s'_i, a_i, o_j]
-    wgrad_pass<DT, WIDTH, XW, false, true>(p, NHID, 0, d_in, off[0], off[0] + WIDTH * d_in, 0, q0, q1, smem);
+    wgrad_pass<WIDTH, XW, false, true>(p, NHID, 0, d_in, off[0], off[0] + WIDTH * d_in, 0, q0, q1, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -448,7 +416,7 @@ constexpr size_t bwd_lds() {
     typedef Net<DT_F32, 256, 3, in_slots(DT_F32, 32, 0, 0), 8> NT;
     return (size_t)StreamSrc<BwdStreamShape<NT>>::LDS_BYTES;
 }
-constexpr size_t wgrad_lds() { return (size_t)2 * 2 * 256 * (WgCfg<DT_F32>::KC + WgCfg<DT_F32>::PAD) * 4; }
+constexpr size_t wgrad_lds() { return (size_t)2 * 2 * 256 * kWgStride * 4; }
 }  // namespace
 
 bool nce_wide_supported(int shape) { return shape == 1; }
@@ -463,23 +431,23 @@ hipError_t launch_nce_wide_bwd(int shape, const NceWideParams& p0, int blocks, h
     NceWideParams p = p0;
     const size_t lds = nce_wide_bwd_lds();
     p.lds_bias = (uint32_t)bwd_lds();
-    (void)hipFuncSetAttribute((const void*)nce_wide_bwd_kernel<DT_F32, 32, 256, 3>,
+    (void)hipFuncSetAttribute((const void*)nce_wide_bwd_kernel<32, 256, 3>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL((nce_wide_bwd_kernel<DT_F32, 32, 256, 3>), blocks, 256, lds, s, p);
+    hipLaunchKernelGGL((nce_wide_bwd_kernel<32, 256, 3>), blocks, 256, lds, s, p);
     return hipGetLastError();
 }
 
 hipError_t launch_nce_wide_wgrad(int shape, const NceWgradParams& p, int blocks, hipStream_t s) {
     if (shape != 1) return hipErrorInvalidValue;
-    (void)hipFuncSetAttribute((const void*)nce_wide_wgrad_kernel<DT_F32, 256, 3, 64>,
+    (void)hipFuncSetAttribute((const void*)nce_wide_wgrad_kernel<256, 3, 64>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)wgrad_lds());
-    hipLaunchKernelGGL((nce_wide_wgrad_kernel<DT_F32, 256, 3, 64>), blocks, 64 * kWgWaves, wgrad_lds(), s, p);
+    hipLaunchKernelGGL((nce_wide_wgrad_kernel<256, 3, 64>), blocks, 64 * kWgWaves, wgrad_lds(), s, p);
     return hipGetLastError();
 }
 
-int nce_wide_bwd_blocks_per_cu() { return occupancy(nce_wide_bwd_kernel<DT_F32, 32, 256, 3>, nce_wide_bwd_lds()); }
+int nce_wide_bwd_blocks_per_cu() { return occupancy(nce_wide_bwd_kernel<32, 256, 3>, nce_wide_bwd_lds()); }
 int nce_wide_wgrad_blocks_per_cu() {
-    return occupancy_t(nce_wide_wgrad_kernel<DT_F32, 256, 3, 64>, 64 * kWgWaves, wgrad_lds());
+    return occupancy_t(nce_wide_wgrad_kernel<256, 3, 64>, 64 * kWgWaves, wgrad_lds());
 }
 
 }  // namespace voila
