@@ -662,8 +662,9 @@ def bench_gemm_reference(torch, reps):
 
 
 def bench_grad(V, torch, reps):
-    """Adjoint through 65,536 rollouts x 20 steps (checkpoint every 5): distillation
-    gradient w.r.t. the 5,316 parameters; return gradient w.r.t. [1024, 20, 4] actions."""
+    """Adjoint through 65,536 rollouts x 20 steps (checkpoint interval up to 5; the
+    default workspace holds every state): distillation gradient w.r.t. the 5,316
+    parameters; return gradient w.r.t. [1024, 20, 4] actions."""
     import workloads
     dev = torch.device("cuda", 0)
     rng = np.random.default_rng(5)

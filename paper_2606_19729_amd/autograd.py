@@ -3,7 +3,7 @@
 ``MeanReturn.apply(actions, model, s0, H, gamma, goal, particles, seed)`` is
 the mean discounted return of rollouts driven by continuous action sequences;
 its backward hands the gradient computed by the adjoint kernel (the forward
-launch runs the checkpointed forward and the reverse sweep together) to
+launch runs the rollouts and their reverse sweep together) to
 autograd.  ``DistillLoss.apply(*flat_weights, desc, s0, actions, targets, H,
 seed)`` is the rollout distillation loss as a function of the transition
 network's weights; each call packs the given weights into a device model.

@@ -1711,7 +1711,7 @@ voila_status_t voila_info_nce_grad(voila_model_t m, const float* d_states, const
             r.wpart = parts[l];
             r.grad_params = dst;
             r.n_params = n[l];
-            r.n_waves = rows[l];
+            r.n_rows = rows[l];
             VOILA_CHECK_HIP(launch_grad_reduce(r, s));
             dst += n[l];
         }
@@ -1764,7 +1764,7 @@ voila_status_t voila_info_nce_grad(voila_model_t m, const float* d_states, const
         r.wpart = w.wpart;
         r.grad_params = d_param_grad_out;
         r.n_params = m->n_lik_params;
-        r.n_waves = w.blocks;
+        r.n_rows = w.blocks;
         VOILA_CHECK_HIP(launch_grad_reduce(r, s));
         return VOILA_OK;
     }
@@ -1786,7 +1786,7 @@ voila_status_t voila_info_nce_grad(voila_model_t m, const float* d_states, const
     r.wpart = w.wpart;
     r.grad_params = d_param_grad_out;
     r.n_params = m->n_lik_params;
-    r.n_waves = w.blocks;
+    r.n_rows = w.blocks;
     VOILA_CHECK_HIP(launch_grad_reduce(r, s));
     return VOILA_OK;
 }
@@ -2522,7 +2522,7 @@ voila_status_t voila_rollout_grad(voila_model_t m, const voila_grad_opts_t* o, v
     r.grad_actions = o->d_grad_actions;
     r.loss = o->d_loss_out;
     r.n_params = o->d_grad_params ? m->n_params : 0;
-    r.n_waves = w.blocks;
+    r.n_rows = w.blocks;
     r.n_loss = w.blocks * w.waves;
     r.H = o->H;
     r.d_a = m->d_a;

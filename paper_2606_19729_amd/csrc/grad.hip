@@ -77,9 +77,10 @@ __device__ __forceinline__ void join_halves(const f32x4& d, float (&out)[2]) {
 // action adjoints) take 4-row products and dW1 (at most 16 columns) 16 x 16
 // ones; with 32-row tiles, and with the states recomputed from checkpoints
 // every five steps, the same step took 526.  Two waves per SIMD (256 registers
-// each) overlap one's LDS transposes with the other's products.  65,536
+// each, 124 bytes per lane spilled: 105 MB written per launch of which the states are
+// 21) overlap one's LDS transposes with the other's products.  65,536
 // rollouts x 20 steps: the whole call 855 -> 557 us (about 340 us at the
-// matrix cores' rate).
+// matrix cores' rate, which are 53 % busy).
 // SEG: the workspace holds every p.C-th state only.  The reverse sweep then runs
 // each segment of p.C steps forward again from its first state into the wave's
 // own segment buffer (the same products, so the same states).
@@ -464,7 +465,7 @@ __global__ __launch_bounds__(kGradMaxWaves * 64) void grad_kernel(GradParams p) 
     for (int q = threadIdx.x; q < p.n_params; q += blockDim.x) out[q] = sum[q];
 }
 
-// Fixed-order sums of the per-wave partials: parameters, objective, actions.
+// Fixed-order sums of the partials: parameters, objective, actions.
 // The partials are read once and nothing else is done, so the kernel is bound
 // by the loads in flight: a block takes 64 consecutive parameters (one 256-byte
 // segment of each row) with 16 waves, wave w summing rows w, w + 16, ... in
@@ -482,10 +483,10 @@ __global__ __launch_bounds__(kRedCols * kRedWaves) void grad_reduce_kernel(GradR
         const float* col = p.wpart + (ok ? q : 0);
         float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
         int w = wave;
-        for (; w + 3 * kRedWaves < p.n_waves; w += 4 * kRedWaves)
+        for (; w + 3 * kRedWaves < p.n_rows; w += 4 * kRedWaves)
 #pragma unroll
             for (int e = 0; e < 4; ++e) s[e] += col[(size_t)(w + e * kRedWaves) * p.n_params];
-        for (; w < p.n_waves; w += kRedWaves) s[0] += col[(size_t)w * p.n_params];
+        for (; w < p.n_rows; w += kRedWaves) s[0] += col[(size_t)w * p.n_params];
         float(*fp)[kRedCols] = reinterpret_cast<float(*)[kRedCols]>(part);
         fp[wave][lane] = (s[0] + s[1]) + (s[2] + s[3]);
         __syncthreads();

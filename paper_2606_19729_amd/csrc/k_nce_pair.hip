@@ -36,7 +36,8 @@ struct PairStores {
 // rollout kernel, the work of each finished pass is spread over the products
 // of the next one, in the order of a compile-time sequence (left
 // free within a fragment-step: pacing the vector instructions by five or eight
-// per product was 5 % slower).  Matrix cores busy 50 %.  B = 4,096: 9.9 ms
+// per product was 5 % slower).  Matrix cores busy 50 %; 68 bytes per lane are
+// spilled.  B = 4,096: 9.9 ms
 // for the 262,144 pair-units, where one unit per wave with 2-byte stores and
 // 612 bytes of spills took 25.4 ms.
 template <int D_O>
@@ -139,7 +140,8 @@ __global__ __launch_bounds__(256) void nce_pair_bwd_kernel(NcePairParams p) {
                 set_word(tmp[j / 4], j % 4, bf16x2_of(a, b) & spread16(m));
             }
         };
-        // half h of the tile's exchange of rows and columns
+        // half h of the tile's exchange of rows and columns (an infinite value
+        // times the zeros makes NaN of its pair's whole tile)
         auto transpose = [&](auto qi, auto sti, auto tti, auto hi) {
             constexpr int q = decltype(qi)::value, st = decltype(sti)::value, tt = decltype(tti)::value;
             constexpr int h = decltype(hi)::value, L = q / NP, t = PT * (q % NP) + tt;

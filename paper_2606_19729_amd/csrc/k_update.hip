@@ -26,7 +26,7 @@ __global__ __launch_bounds__(256) void fold_pair_kernel(FoldStepsParams a, FoldS
     if (r < p.width) fold_element(p, 0, r);
 }
 
-// The same for many rows: a block stages its 256 rows of the columns in LDS,
+// fold_steps_kernel for many rows: a block stages its 256 rows of the columns in LDS,
 // transposed (read once, coalesced, instead of once per row with a stride of nf
 // floats), and the values of eight rows at a time, checked and rounded once
 // instead of by every thread.  4,096 rows of 36 columns: 29 -> 12 us.
@@ -238,11 +238,11 @@ __global__ __launch_bounds__(256) void propose_kernel(ProposeParams p) {
 // load for both) of k-step g4 / 2, half g4 % 2.  Each product sums its k values
 // in ascending order and the output layer's quarters are added in wave order,
 // so the results are the tiles' bit for bit.  The weights come as one sequence
-// over the layers of both networks, kHalfDepth k-step pairs ahead and across
+// over the layers of both networks, DEPTH k-step pairs ahead and across
 // the layer barriers; the first layer's action and observation are folded by
 // the block itself (256 + 256 rows by 512 threads) while the first fragments
 // arrive, instead of by two launches before it.  Bound by the chain of k-steps
-// of the six hidden products and the layer barriers (matrix cores 40 % busy):
+// of the six hidden products and the layer barriers (matrix cores 34 % busy):
 // 4,096 particles in binary32 33.8 us, 76 + 10 on 32-row tiles.
 template <int DT> struct HalfOps;
 template <> struct HalfOps<DT_F32> {

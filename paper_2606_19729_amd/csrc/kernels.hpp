@@ -310,14 +310,14 @@ hipError_t launch_nce_grad(int shape, const NceGradParams& p, int blocks, size_t
 int nce_grad_blocks_per_cu(int shape, size_t lds);
 
 struct GradReduceParams {
-    const float* wpart;
-    const float* lpart;
-    const float* apart;
+    const float* wpart;      // [n_rows][n_params] parameter-gradient partials
+    const float* lpart;      // [n_loss] objective partials
+    const float* apart;      // [tiles][H][d_a] action-gradient partials
     float* grad_params;
     float* grad_actions;
     float* loss;
-    int n_params, n_waves, n_action_values, H, d_a, tiles_per_seq;
-    int n_loss;              // rows of lpart
+    int n_params, n_rows, n_action_values, H, d_a, tiles_per_seq;
+    int n_loss;
     double scale;
 };
 
