@@ -685,10 +685,11 @@ voila_status_t voila_model_destroy(voila_model_t m) {
 // ---------------------------------------------------------------------------
 // plan
 // ---------------------------------------------------------------------------
+// Workspace: the tiles' sums, then those of half tiles for plans small enough.
+static size_t plan_tiles_ws(size_t tiles) { return align_up(tiles * sizeof(float), 256); }
 static size_t plan_ws(int N, int K) {
-    const size_t n_tiles = ((size_t)N + 31) / 32;
-    const size_t tiles = (size_t)K * n_tiles;
-    return align_up(std::max(tiles, 32 * std::min<size_t>(tiles, kPlanHalfTiles)) * sizeof(float), 256);
+    const size_t tiles = (size_t)K * (((size_t)N + 31) / 32);
+    return plan_tiles_ws(tiles) + plan_tiles_ws(2 * std::min<size_t>(tiles, kPlanHalfTiles));
 }
 
 size_t voila_plan_workspace_size(voila_model_t model, int32_t N, int32_t K, int32_t H) {
@@ -714,7 +715,7 @@ voila_status_t voila_plan(voila_model_t m, const float* d_states, const double* 
     if (!d_states || !d_q_out || (!d_cands && H > 0)) return fail(VOILA_ERR_INVALID_ARG, "NULL device buffer");
     const int n_tiles = (N + 31) / 32;
     const long tiles = (long)K * n_tiles;
-    if (!ws || ws_bytes < align_up((size_t)tiles * sizeof(float), 256))
+    if (!ws || ws_bytes < plan_tiles_ws(tiles))
         return fail(VOILA_ERR_WORKSPACE, "plan workspace too small");
     DeviceGuard guard(m->device);
     if (!guard.ok) return fail(VOILA_ERR_DEVICE, "hipSetDevice failed");
@@ -747,10 +748,14 @@ voila_status_t voila_plan(voila_model_t m, const float* d_states, const double* 
     q.scale = d_belief_w ? 1.0f : (float)(1.0 / (double)N);
     // Half tiles up to three 32-particle tiles per CU, where the tile kernel has
     // less than a wave per SIMD (20 steps, tiles of 32: 128 30 against 83 us, 512
-    // 53 / 82, 1,024 98 / 83); the tile kernel also serves workspaces that hold
-    // the tiles' partial sums only.
-    if (plan_half_shape(m->shape, m->dt) && tiles <= std::min(kPlanHalfTiles, 3 * m->cus) &&
-        ws_bytes >= 32 * (size_t)tiles * sizeof(float)) {
+    // 53 / 82, 1,024 98 / 83); up to one per CU for plans of under four steps, which do
+    // not make up for every block's own weights (768 tiles: one step 14.5 / 13.9,
+    // two 17.3 / 15.7, three 18.9 / 18.6, five 24.1 / 25.7).  The tile kernel also serves
+    // workspaces that hold the tiles' sums only.
+    if (plan_half_shape(m->shape, m->dt) && tiles <= std::min(kPlanHalfTiles, (H > 3 ? 3 : 1) * m->cus) &&
+        ws_bytes >= plan_tiles_ws(tiles) + 2 * (size_t)tiles * sizeof(float)) {
+        p.partials += plan_tiles_ws(tiles) / sizeof(float);
+        q.partials = p.partials;
         VOILA_CHECK_HIP(launch_plan_half(m->shape, p, q, s));
         return VOILA_OK;
     }

@@ -8,9 +8,9 @@
 //                 from Philox.  Small networks are staged in LDS once per block;
 //                 wide ones stream their fragments from L2.
 // plan_split_kernel  deep wide networks, each layer split over a block's waves.
-// plan_half_kernel   small plans, 16 particles per block (q_reduce_half_kernel
-//                 sums their contributions in q_reduce_kernel's order).
-// q_reduce_kernel fixed-order sum of the per-tile partial returns into Q.
+// plan_half_kernel   small plans, 16 particles per block.
+// q_reduce_kernel fixed-order sum of the per-tile (or per-half-tile) partial
+//                 returns into Q.
 #include "plan_unit.hpp"
 
 namespace voila {
@@ -196,8 +196,11 @@ __global__ __launch_bounds__(64 * kPlanSplitWaves) void plan_split_kernel(PlanPa
 // hidden units, so nothing waits for a third barrier) and holds the states.
 // Noise, actions and first-layer bias rows are prepared kHalfSteps steps at a
 // time, one (particle, step) per thread.  All sums run in plan_kernel's order,
-// so the returns are the same bits; the contributions are left per particle
-// for q_reduce_half_kernel.
+// so the returns are the same bits.  The block takes every second particle of a
+// tile: the tile's sum adds the even and the odd particles' sums last, so a half
+// tile's is one value and q_reduce_kernel adds the two (with the contributions
+// left per particle for it, one candidate of 24,576 took 63 us at 5 steps, 27 in
+// plan_kernel).
 constexpr int kHalfSteps = 16;
 
 template <int DT, int D_S, int D_A, int D_W, int WIDTH, int NHID>
@@ -207,7 +210,7 @@ constexpr bool plan_half() {
 }
 
 template <int DT, int D_S, int N_ACT, int D_A, int D_W, int WIDTH, int NHID>
-__global__ __launch_bounds__(256, 2) void plan_half_kernel(PlanParams p, float* contribs) {
+__global__ __launch_bounds__(256, 2) void plan_half_kernel(PlanParams p) {
     if constexpr (!plan_half<DT, D_S, D_A, D_W, WIDTH, NHID>()) {
         return;  // not chosen for the other networks
     } else {
@@ -246,7 +249,7 @@ __global__ __launch_bounds__(256, 2) void plan_half_kernel(PlanParams p, float* 
     };
     const int n_half = 2 * p.n_tiles;
     const int u = blockIdx.x;
-    const int k = u / n_half, half = u - k * n_half, i = half * 16 + n;
+    const int k = u / n_half, i0 = (u - k * n_half) / 2 * 32 + (u & 1), i = i0 + 2 * n;
     const bool valid = i < p.N;
     float st = valid && g4 < D_S ? p.states[(size_t)i * D_S + g4] : 0.0f;
     float G = 0.0f;
@@ -256,7 +259,7 @@ __global__ __launch_bounds__(256, 2) void plan_half_kernel(PlanParams p, float* 
         // every wave is past the second barrier of the previous step, after
         // which it reads none of these
         if (const int j = tid / 16, m = tid % 16, t = t0 + j; j < tn) {
-            const int im = half * 16 + m;
+            const int im = i0 + 2 * m;
             float z[4];
             if (p.noise) {
                 const float* src = p.noise + (((size_t)k * p.N + (im < p.N ? im : 0)) * p.H + t) * D_W;
@@ -329,9 +332,12 @@ __global__ __launch_bounds__(256, 2) void plan_half_kernel(PlanParams p, float* 
             disc *= p.gamma;
         }
     }
-    if (wave == 0 && g4 == 0) {
-        if (p.returns && valid) p.returns[(size_t)k * p.N + i] = G;
-        contribs[(size_t)u * 16 + n] = valid ? (p.belief_w ? (float)p.belief_w[i] * G : G) : 0.0f;
+    if (wave == 0) {
+        if (p.returns && valid && g4 == 0) p.returns[(size_t)k * p.N + i] = G;
+        float v = valid ? (p.belief_w ? (float)p.belief_w[i] * G : G) : 0.0f;
+#pragma unroll
+        for (int m = 8; m >= 1; m >>= 1) v += __shfl_xor(v, m);  // sum32's order without its last step
+        if (lane == 0) p.partials[u] = v;
     }
     }
 }
@@ -388,30 +394,16 @@ __global__ __launch_bounds__(512, 4) void plan_batch_kernel(BatchPlanParams bp) 
 
 __global__ __launch_bounds__(64) void reset_counter_kernel(int* counter) { if (threadIdx.x == 0) *counter = 0; }
 
+template <bool HALVES>
 __global__ __launch_bounds__(256) void q_reduce_kernel(QReduceParams p) {
     const int lane = threadIdx.x & 63;
     const int k = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
     if (k >= p.K) return;
     float s = 0.0f;
-    for (int j = lane; j < p.n_tiles; j += 64) s += p.partials[(size_t)k * p.n_tiles + j];
-    s += __shfl_xor(s, 32);
-    s = sum32(s);
-    if (lane == 0) p.q[k] = s * p.scale;
-}
-
-// q_reduce_kernel's sums from the particles' contributions [K][32 n_tiles]: a
-// block per candidate forms the tiles' partial sums first.
-__global__ __launch_bounds__(256) void q_reduce_half_kernel(QReduceParams p) {
-    __shared__ float part[kPlanHalfTiles];
-    const int lane = threadIdx.x & 63, k = blockIdx.x;
-    for (int j = threadIdx.x >> 5; j < p.n_tiles; j += 8) {
-        const float v = sum32(p.partials[((size_t)k * p.n_tiles + j) * 32 + (threadIdx.x & 31)]);
-        if ((threadIdx.x & 31) == 0) part[j] = v;
+    for (int j = lane; j < p.n_tiles; j += 64) {
+        const size_t at = (size_t)k * p.n_tiles + j;
+        s += HALVES ? p.partials[2 * at] + p.partials[2 * at + 1] : p.partials[at];
     }
-    __syncthreads();
-    if (threadIdx.x >= 64) return;
-    float s = 0.0f;
-    for (int j = lane; j < p.n_tiles; j += 64) s += part[j];
     s += __shfl_xor(s, 32);
     s = sum32(s);
     if (lane == 0) p.q[k] = s * p.scale;
@@ -640,12 +632,11 @@ bool plan_half_shape(int shape, int dt) {
 
 hipError_t launch_plan_half(int shape, const PlanParams& p, const QReduceParams& q, hipStream_t s) {
     const int blocks = 2 * p.K * p.n_tiles;
-    if (!plan_half_shape(shape, DT_F32) || p.n_tiles > kPlanHalfTiles) return hipErrorInvalidValue;
-    float* contribs = const_cast<float*>(q.partials);
+    if (!plan_half_shape(shape, DT_F32)) return hipErrorInvalidValue;
     switch (shape) {
-#define X(id, ds, na, da, dw, dox, dwz, w, nh)                                                                          \
-    case id:                                                                                                           \
-        hipLaunchKernelGGL((PLANH_K(id, ds, na, (na > 0 ? 0 : da), dw, dox, dwz, w, nh)), blocks, 256, 0, s, p, contribs); \
+#define X(id, ds, na, da, dw, dox, dwz, w, nh)                                                                \
+    case id:                                                                                                 \
+        hipLaunchKernelGGL((PLANH_K(id, ds, na, (na > 0 ? 0 : da), dw, dox, dwz, w, nh)), blocks, 256, 0, s, p); \
         break;
         VOILA_SHAPES(X)
 #undef X
@@ -653,7 +644,7 @@ hipError_t launch_plan_half(int shape, const PlanParams& p, const QReduceParams&
             return hipErrorInvalidValue;
     }
     if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-    hipLaunchKernelGGL(q_reduce_half_kernel, p.K, 256, 0, s, q);
+    hipLaunchKernelGGL(q_reduce_kernel<true>, (p.K + 3) / 4, 256, 0, s, q);
     return hipGetLastError();
 }
 
@@ -665,7 +656,7 @@ hipError_t launch_reset_counter(int* d_counter, hipStream_t s) {
 hipError_t launch_q_reduce(const QReduceParams& p, hipStream_t s) {
     const int blocks = (p.K + 3) / 4;
     if (blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(q_reduce_kernel, blocks, 256, 0, s, p);
+    hipLaunchKernelGGL(q_reduce_kernel<false>, blocks, 256, 0, s, p);
     return hipGetLastError();
 }
 

@@ -50,7 +50,7 @@ struct PlanParams {
     const float* noise;      // [K][N][H][d_w] or NULL
     float* returns;          // [K][N] or NULL
     float* traj;             // [K][N][H][d_s] rollout states s_1..s_H, or NULL
-    float* partials;         // [K][n_tiles]
+    float* partials;         // [K][n_tiles], on half tiles [K][n_tiles][2]
     int32_t* status;         // or NULL
     int N, K, H, n_tiles;
     double gamma;
@@ -372,7 +372,7 @@ constexpr int kNormResThreads = 1024;
 // blocks: of the general kernel; cap: blocks the chip holds at once
 hipError_t launch_plan(int shape, int dt, const PlanParams& p, int blocks, long cap, int cus, hipStream_t s);
 hipError_t launch_q_reduce(const QReduceParams& p, hipStream_t s);
-// Small plans on half tiles: contributions [K][32 n_tiles] at q.partials, then Q.
+// Small plans on half tiles: their sums [K][n_tiles][2] at the partials, then Q.
 constexpr int kPlanHalfTiles = 1024;  // most tiles of such a plan
 bool plan_half_shape(int shape, int dt);
 hipError_t launch_plan_half(int shape, const PlanParams& p, const QReduceParams& q, hipStream_t s);

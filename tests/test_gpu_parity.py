@@ -414,3 +414,18 @@ def test_resample_indices_written_over_the_rows(N):
     assert np.array_equal(idx.cpu().numpy(), ref)
     rows.view(np.int32).reshape(-1)[:N] = ref
     assert np.array_equal(dst.cpu().numpy().view(np.int32), rows[ref].view(np.int32))
+
+
+@pytest.mark.parametrize("K,N,H", [(1, 24576, 1), (2, 12257, 3), (3, 8192, 5)])
+def test_few_candidates_on_half_tiles(K, N, H):
+    # hundreds of half tiles to a candidate, against the tile kernel bit for bit
+    w = workloads.small(seed=K, K=K, N=N, H=H)
+    m = V.Model(w.model)
+    S, C = dev(w.states), torch.as_tensor(w.cands, device="cuda")
+    say(f"  plan on half tiles K={K} N={N} H={H}")
+    a = V.plan(m, S, C, w.gamma, w.goal, seed=w.plan_seed, return_G=True, return_traj=True)
+    small_ws = torch.empty((K * ((N + 31) // 32) * 4 + 255) // 256 * 256, dtype=torch.uint8, device="cuda")
+    b = V.plan(m, S, C, w.gamma, w.goal, seed=w.plan_seed, return_G=True, return_traj=True, workspace=small_ws)
+    torch.cuda.synchronize()
+    for x, y in zip(a, b):
+        assert torch.equal(x, y)
