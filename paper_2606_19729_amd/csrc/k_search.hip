@@ -504,9 +504,9 @@ __global__ __launch_bounds__(kPwThreads) void pw_norm_res_small_kernel(PwParams 
     }
 }
 
-// The same for groups of more than kPwSmall successors, one workgroup of 1,024
+// The same for groups of more than `above` successors, one workgroup of 1,024
 // threads per group (the single-belief procedure on the group's rows).
-__global__ __launch_bounds__(kNormResThreads) void pw_norm_res_kernel(PwParams pw) {
+__global__ __launch_bounds__(kNormResThreads) void pw_norm_res_kernel(PwParams pw, int above) {
     __shared__ double buf[kNormResMaxN];
     __shared__ int ids[kNormResMaxN];
     __shared__ double redd[kNRWaves];
@@ -514,7 +514,7 @@ __global__ __launch_bounds__(kNormResThreads) void pw_norm_res_kernel(PwParams p
     for (int m = blockIdx.x; m < pw.M; m += gridDim.x) {
         int lo, n;
         pw_group(pw, m, lo, n);
-        if (n <= kPwSmall) continue;
+        if (n <= above) continue;
         int c = 0;
         while ((1 << c) < n) ++c;
         NormResParams p{};
@@ -648,10 +648,24 @@ hipError_t launch_pw_prepare(const PwParams& p, const FoldStepsParams& fold, hip
 
 hipError_t launch_pw_norm_res(const PwParams& p, int cus, hipStream_t s) {
     if (p.M == 0 || cus == 0) return hipSuccess;
+    // a group can only be larger when there are that many successors
+    const bool large = p.T > kPwSmall;
+    // The kernel for large groups takes all of them where a CU has one (16 groups of
+    // up to 2,048 successors of the realistic network, whole step in bfloat16: 58 us,
+    // 74 with the small ones in a launch before), and where the average says that
+    // some are large, as those then are a second, hardly filled launch: from 512 on
+    // for two rounds of groups over the CUs (512 of up to 1,100, small networks: 79 us
+    // against 94, of up to 1,000 77 either way, of up to 300 realistic 89 / 85), later
+    // for more (700 of up to 1,100 101 / 109, of up to 1,000 95 / 88; 1,000 of up to
+    // 1,270 134 / 145, of up to 1,100 131 / 128).
+    const int rounds = (p.M + cus - 1) / cus, mean = p.T / p.M;
+    if (large && (rounds == 1 || mean >= 448 + 32 * (rounds < 4 ? rounds : 4))) {
+        hipLaunchKernelGGL(pw_norm_res_kernel, p.M < cus ? p.M : cus, kNormResThreads, 0, s, p, 0);
+        return hipGetLastError();
+    }
     const int cap = 8 * cus;
     hipLaunchKernelGGL(pw_norm_res_small_kernel, p.M < cap ? p.M : cap, kPwThreads, 0, s, p);
-    // a group can only be larger when there are that many successors
-    if (p.T > kPwSmall) hipLaunchKernelGGL(pw_norm_res_kernel, p.M < cus ? p.M : cus, kNormResThreads, 0, s, p);
+    if (large) hipLaunchKernelGGL(pw_norm_res_kernel, p.M < cus ? p.M : cus, kNormResThreads, 0, s, p, kPwSmall);
     return hipGetLastError();
 }
 
