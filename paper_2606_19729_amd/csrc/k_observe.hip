@@ -19,10 +19,12 @@ struct ObsRow {
     bool valid;   // this lane's particle exists
 };
 
-// This lane's row of tile unit u (index arithmetic only).
+// This lane's row of tile unit u (index arithmetic only).  ONE_GROUPS: the launch
+// may be one of row_groups (not those for the rows of whole rollouts).
+template <bool ONE_GROUPS>
 __device__ __forceinline__ ObsRow observe_row(const ObserveParams& p, long u, int n_tiles, int col) {
     ObsRow w;
-    if (p.row_groups) {
+    if (ONE_GROUPS && p.row_groups) {
         // one row per group: the tile's columns are 32 groups (a tile per group
         // would hold one row: 82 us for 4,096 groups of the realistic network)
         const int k = (int)u * 32 + col;
@@ -77,10 +79,10 @@ __device__ __forceinline__ void observe_slots(const ObserveParams& p, const ObsR
 }
 
 // Inputs [s', w_Z] of this lane's row of tile unit u in first-layer slot order.
-template <int D_S, int D_WZ, int IN_SLOTS>
+template <int D_S, int D_WZ, bool ONE_GROUPS, int IN_SLOTS>
 __device__ __forceinline__ ObsRow observe_inputs(const ObserveParams& p, long u, int n_tiles, int g, int col,
                                                  float (&slots)[IN_SLOTS]) {
-    const ObsRow w = observe_row(p, u, n_tiles, col);
+    const ObsRow w = observe_row<ONE_GROUPS>(p, u, n_tiles, col);
     float st[state_slots(D_S)];
     observe_states<D_S>(p, w, g, st);
     observe_slots<D_S, D_WZ>(p, w, g, st, slots);
@@ -149,7 +151,7 @@ __global__ __launch_bounds__(256) void observe_kernel(ObserveParams p) {
             for (int q = 0; q < TPU; ++q) {
                 // a tile past the group's last reads that tile and writes nothing
                 const int tile = t0 + q < n_tiles ? t0 + q : t0;
-                nw[q] = observe_row(p, grp * n_tiles + tile, n_tiles, col);
+                nw[q] = observe_row<false>(p, grp * n_tiles + tile, n_tiles, col);
                 nw[q].valid = nw[q].valid && ok && t0 + q < n_tiles;
                 observe_states<D_S>(p, nw[q], g, nst[q]);
             }
@@ -200,7 +202,7 @@ __global__ __launch_bounds__(256) void observe_kernel(ObserveParams p) {
         const long n_here = p.row_groups ? ((long)p.K + 31) / 32 : n_units;
         for (long u = first; u < n_here; u += (long)gridDim.x * tpb) {
             float slots[NTO::IN_SLOTS];
-            const ObsRow w = observe_inputs<D_S, D_WZ>(p, u, n_tiles, g, col, slots);
+            const ObsRow w = observe_inputs<D_S, D_WZ, true>(p, u, n_tiles, g, col, slots);
             const float* b0 = p.b0 + (size_t)w.grp * p.b0_stride;
             f32x16 o;
             if constexpr (MODE == kSplit) {
@@ -253,7 +255,7 @@ __global__ __launch_bounds__(64 * kObsSplitWaves) void observe_split_kernel(Obse
             // a tile past the last of the group reads row 0 and writes nothing
             const int tile = tp * ST + wave;
             float slots[NT::IN_SLOTS];
-            w = observe_inputs<D_S, D_WZ>(p, grp * n_tiles + (tile < n_tiles ? tile : 0), n_tiles, g, col, slots);
+            w = observe_inputs<D_S, D_WZ, false>(p, grp * n_tiles + (tile < n_tiles ? tile : 0), n_tiles, g, col, slots);
             w.valid = w.valid && tile < n_tiles;
             split_stage_inputs<NT>(in_lds + wave * SplitIn<NT>::BYTES, slots, lane);
         }
