@@ -37,33 +37,37 @@ PEAK_BF16_TFLOPS = 2500.0
 #   hbm_bytes      FETCH_SIZE x 2 + WRITE_SIZE per launch (the factors are what the two
 #                  counters read for an elementwise kernel of 256 MiB in + 256 MiB out)
 MEASURED = {
-    "sources_sha256_16": "c7dd443124fe6725",
+    "sources_sha256_16": "81c7aa8950849394",
     "kernels": {
-        "plan_kernel f32 realistic": {"mfma_busy": 0.890, "valu_per_mfma": 0.53, "valu_issue": 0.03,
-                                      "hbm_bytes": (5627 * 2 + 1024) * 1024},
-        "plan_kernel bf16 realistic": {"mfma_busy": 0.613, "valu_per_mfma": 2.69, "valu_issue": 0.17,
+        "plan_kernel f32 realistic": {"mfma_busy": 0.892, "valu_per_mfma": 0.53, "valu_issue": 0.03,
+                                      "hbm_bytes": (5628 * 2 + 1024) * 1024},
+        "plan_kernel bf16 realistic": {"mfma_busy": 0.621, "valu_per_mfma": 2.69, "valu_issue": 0.17,
                                        "hbm_bytes": (4223 * 2 + 512) * 1024},
-        "plan_batch_kernel bf16": {"mfma_busy": 0.511, "valu_per_mfma": 10.75, "valu_issue": 0.58,
+        "plan_batch_kernel bf16": {"mfma_busy": 0.510, "valu_per_mfma": 10.75, "valu_issue": 0.57,
                                    "valu_per_tile_step": 150, "mfma_per_tile_step": 14.0,
-                                   "hbm_bytes": (88821 * 2 + 76897) * 1024},
-        "plan_kernel bf16 width 1024": {"mfma_busy": 0.598, "valu_per_mfma": 1.47, "valu_issue": 0.10,
-                                        "hbm_bytes": (9510 * 2 + 1024) * 1024},
-        "plan_split_kernel bf16 4 x 1024": {"mfma_busy": 0.473, "valu_per_mfma": 1.86, "valu_issue": 0.10,
-                                            "l2_hit": 0.749, "hbm_bytes": (260881759 * 2 + 164361) * 1024},
-        "plan_split_kernel bf16 target finding": {"mfma_busy": 0.457, "valu_per_mfma": 1.97, "valu_issue": 0.10,
-                                                  "l2_hit": 0.788, "hbm_bytes": (925838188 * 2 + 4277267) * 1024},
-        "observe_kernel f32 realistic rollouts": {"mfma_busy": 0.854, "valu_per_mfma": 0.52},
-        "observe_kernel bf16 realistic rollouts": {"mfma_busy": 0.431, "valu_per_mfma": 3.08},
-        "observe_split_kernel bf16 4 x 1024": {"mfma_busy": 0.468, "valu_per_mfma": 1.86, "l2_hit": 0.742},
-        "observe_split_kernel bf16 target finding": {"mfma_busy": 0.452, "valu_per_mfma": 1.97, "l2_hit": 0.843},
-        "nce_wide_bwd_kernel f32": {"mfma_busy": 0.705, "valu_per_mfma": 0.77},
-        "nce_wide_wgrad_kernel f32": {"mfma_busy": 0.548, "valu_per_mfma": 0.91},
-        "nce_wide_bwd_kernel bf16": {"mfma_busy": 0.144, "valu_per_mfma": 7.23},
-        "nce_wide_wgrad_kernel bf16": {"mfma_busy": 0.109, "valu_per_mfma": 12.35},
-        "ddim_split_kernel 5 x 1024": {"mfma_busy": 0.476, "valu_per_mfma": 1.82},
-        "ddim_split_kernel 5 x 512": {"mfma_busy": 0.437, "valu_per_mfma": 2.76},
-        "ddim_split_kernel 5 x 512, 64-d latent": {"mfma_busy": 0.404, "valu_per_mfma": 3.37},
-        "lg_resample_kernel 2^24": {"hbm_bytes": (541267 * 2 + 1114115) * 1024},
+                                   "hbm_bytes": (88904 * 2 + 76907) * 1024},
+        "plan_kernel bf16 width 1024": {"mfma_busy": 0.604, "valu_per_mfma": 1.47, "valu_issue": 0.10,
+                                        "hbm_bytes": (9511 * 2 + 1024) * 1024},
+        "plan_split_kernel bf16 4 x 1024": {"mfma_busy": 0.623, "valu_per_mfma": 0.88, "valu_issue": 0.06,
+                                            "l2_hit": 0.968, "hbm_bytes": (32073914 * 2 + 164352) * 1024},
+        "plan_split_kernel bf16 target finding": {"mfma_busy": 0.609, "valu_per_mfma": 1.00, "valu_issue": 0.06,
+                                                  "l2_hit": 0.968, "hbm_bytes": (132981669 * 2 + 4263002) * 1024},
+        "observe_kernel f32 realistic rollouts": {"mfma_busy": 0.853, "valu_per_mfma": 0.52},
+        "observe_kernel bf16 realistic rollouts": {"mfma_busy": 0.432, "valu_per_mfma": 3.08},
+        "observe_split_kernel bf16 4 x 1024": {"mfma_busy": 0.628, "valu_per_mfma": 0.88, "l2_hit": 0.968},
+        "observe_split_kernel bf16 target finding": {"mfma_busy": 0.590, "valu_per_mfma": 0.99, "l2_hit": 0.966},
+        "nce_wide_bwd_kernel f32": {"mfma_busy": 0.713, "valu_per_mfma": 0.77},
+        "nce_wide_wgrad_kernel f32": {"mfma_busy": 0.713, "valu_per_mfma": 1.07},
+        "nce_pair_bwd_kernel bf16": {"mfma_busy": 0.499, "valu_per_mfma": 4.02},
+        "nce_pair_wgrad_kernel bf16": {"mfma_busy": 0.377, "valu_per_mfma": 6.91},
+        "grad_kernel f32 distillation": {"mfma_busy": 0.573, "valu_per_mfma": 1.49},
+        "grad_kernel f32 return": {"mfma_busy": 0.623, "valu_per_mfma": 1.74},
+        "pw_lik_kernel f32": {"mfma_busy": 0.872, "valu_per_mfma": 0.47},
+        "pw_lik_kernel bf16": {"mfma_busy": 0.511, "valu_per_mfma": 3.16},
+        "ddim_split_kernel 5 x 1024": {"mfma_busy": 0.637, "valu_per_mfma": 0.86},
+        "ddim_split_kernel 5 x 512": {"mfma_busy": 0.498, "valu_per_mfma": 2.31},
+        "ddim_split_kernel 5 x 512, 64-d latent": {"mfma_busy": 0.462, "valu_per_mfma": 2.93},
+        "lg_resample_kernel 2^24": {"hbm_bytes": (541264 * 2 + 1114116) * 1024},
     },
 }
 
@@ -75,8 +79,10 @@ SECTION_COUNTERS = {
     "deep_bf16": ["plan_split_kernel bf16 4 x 1024", "observe_split_kernel bf16 4 x 1024"],
     "target_finding_bf16": ["plan_split_kernel bf16 target finding", "observe_split_kernel bf16 target finding"],
     "plan_observe": ["observe_kernel f32 realistic rollouts", "observe_kernel bf16 realistic rollouts"],
-    "info_nce": ["nce_wide_bwd_kernel f32", "nce_wide_wgrad_kernel f32", "nce_wide_bwd_kernel bf16",
-                 "nce_wide_wgrad_kernel bf16"],
+    "info_nce": ["nce_wide_bwd_kernel f32", "nce_wide_wgrad_kernel f32", "nce_pair_bwd_kernel bf16",
+                 "nce_pair_wgrad_kernel bf16"],
+    "gradients": ["grad_kernel f32 distillation", "grad_kernel f32 return"],
+    "pw_step": ["pw_lik_kernel f32", "pw_lik_kernel bf16"],
     "ddim": ["ddim_split_kernel 5 x 1024", "ddim_split_kernel 5 x 512", "ddim_split_kernel 5 x 512, 64-d latent"],
 }
 
