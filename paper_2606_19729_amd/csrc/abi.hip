@@ -874,11 +874,29 @@ voila_status_t voila_update(voila_model_t m, const float* d_states, const double
     DeviceGuard guard(m->device);
     if (!guard.ok) return fail(VOILA_ERR_DEVICE, "hipSetDevice failed");
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    const bool half = half_tiles(m, N);
+    if (half) {
+        // every block folds the action and the observation for itself, so where one
+        // of them lies in an output of the stage it is taken from the bias rows'
+        // place in the workspace, which half tiles leave free
+        const size_t a_bytes = 4 * (size_t)(m->n_actions > 0 ? 1 : m->d_a), o_bytes = 4 * (size_t)m->d_o;
+        auto written = [&](const void* at, size_t bytes) {
+            return !buffers_apart(at, bytes, d_prop_out, 4 * (size_t)N * m->d_s) ||
+                   !buffers_apart(at, bytes, d_loglik_out, 4 * (size_t)N);
+        };
+        if (written(d_action, a_bytes)) {
+            VOILA_CHECK_HIP(hipMemcpyAsync(w.b0_trans, d_action, a_bytes, hipMemcpyDeviceToDevice, s));
+            d_action = w.b0_trans;
+        }
+        if (written(d_obs, o_bytes)) {
+            VOILA_CHECK_HIP(hipMemcpyAsync(w.b0_lik, d_obs, o_bytes, hipMemcpyDeviceToDevice, s));
+            d_obs = w.b0_lik;
+        }
+    }
     const FoldStepsParams ft =
         fold_one(m, m->fold_w_trans, m->fold_b_trans, m->nf_trans, d_action, nullptr, w.b0_trans, d_status);
     const FoldStepsParams fl =
         fold_one(m, m->fold_w_lik, m->fold_b_lik, m->nf_lik, d_action, d_obs, w.b0_lik, d_status, m->lik_width);
-    const bool half = half_tiles(m, N);
     if (!half) VOILA_CHECK_HIP(launch_fold_pair(ft, fl, s));
     ProposeParams p{};
     p.trans = m->trans_upd;

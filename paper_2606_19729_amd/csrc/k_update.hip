@@ -997,10 +997,6 @@ constexpr int kNormResShare = 256;
 int norm_res_slices(const NormResParams& p) {
     if (!p.do_resample) return 1;
     const size_t n = (size_t)p.N;
-    auto apart = [](const void* a, size_t na, const void* b, size_t nb) {
-        const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
-        return !a || !b || x + na <= y || y + nb <= x;
-    };
     const struct {
         const void* at;
         size_t bytes;
@@ -1008,7 +1004,7 @@ int norm_res_slices(const NormResParams& p) {
       out[] = {{p.w_out, 8 * n}, {p.stats, 16}, {p.idx_out, 4 * n}, {p.dst, p.src ? 4 * n * p.row_floats : 0}};
     for (const auto& o : out)
         for (const auto& i : in)
-            if (!apart(o.at, o.bytes, i.at, i.bytes)) return 1;
+            if (!buffers_apart(o.at, o.bytes, i.at, i.bytes)) return 1;
     return (p.N + kNormResShare - 1) / kNormResShare;
 }
 

@@ -108,6 +108,12 @@ struct FoldStepsParams {
     int32_t* status;     // or NULL
 };
 
+// Whether two buffers share no byte (an absent one shares none).
+inline bool buffers_apart(const void* a, size_t na, const void* b, size_t nb) {
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return !a || !b || x + na <= y || y + nb <= x;
+}
+
 // The update's first stage on half tiles, with the folds of its first-layer
 // biases (at most kHalfCols columns each) done by its blocks.
 constexpr int kHalfCols = 64;

@@ -416,6 +416,48 @@ def test_resample_indices_written_over_the_rows(N):
     assert np.array_equal(dst.cpu().numpy().view(np.int32), rows[ref].view(np.int32))
 
 
+@pytest.mark.parametrize("compute", ["f32", "bf16"])
+def test_update_reads_its_inputs_from_its_outputs(compute):
+    # the action lies in the proposals and the observation in the
+    # log-likelihoods: both are read before either is written
+    w = workloads.realistic(N=1000, K=1, H=1)
+    m = V.Model(w.model, compute=compute)
+    args = dict(lam=w.lam, seed=5, U=77)
+    obs = dev(np.linspace(-1, 1, w.model.d_o))
+    act = torch.as_tensor(np.asarray(w.update_action), device="cuda").reshape(-1)
+    act = act.to(torch.int32 if w.model.n_actions else torch.float32)
+    S = dev(w.states)
+    ref = V.update(m, S, act, obs, **args)
+    prop, loglik = torch.empty_like(ref["prop"]), torch.empty_like(ref["loglik"])
+    act_in = prop.view(-1)[1600 : 1600 + act.numel()].view(act.dtype)
+    obs_in = loglik[400 : 400 + obs.numel()]
+    ws = m.update_workspace(1000)
+
+    def call():
+        return V.update(m, S, act_in, obs_in, out=dict(bufs, prop=prop, loglik=loglik), workspace=ws, **args)
+
+    bufs = {k: torch.empty_like(ref[k]) for k in ["states", "idx", "w", "stats"]}
+    graph = torch.cuda.CUDAGraph()
+    say(f"  update {compute}, inputs inside its outputs")
+    for replay in range(4):
+        act_in.copy_(act)
+        obs_in.copy_(obs)
+        torch.cuda.synchronize()
+        if replay == 0:
+            got = call()
+            torch.cuda.synchronize()
+        else:
+            if replay == 1:
+                with torch.cuda.graph(graph):
+                    got = call()
+            graph.replay()
+            torch.cuda.synchronize()
+        for k in ["states", "idx", "w", "stats", "prop", "loglik"]:
+            assert torch.equal(got[k], ref[k]), (k, replay)
+        for k in got:
+            got[k].zero_()
+
+
 @pytest.mark.parametrize("K,N,H", [(1, 24576, 1), (2, 12257, 3), (3, 8192, 5)])
 def test_few_candidates_on_half_tiles(K, N, H):
     # hundreds of half tiles to a candidate, against the tile kernel bit for bit
